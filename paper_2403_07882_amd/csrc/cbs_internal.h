@@ -78,7 +78,8 @@ struct Item {
     int64_t beg, end;
 };
 
-constexpr int kItemElems = 4096;      // scalar elements per work item
+constexpr int kItemElems = 4096;      // most scalar elements per work item
+constexpr int kItemElemsMin = 512;    // least, on small systems (item_elems)
 constexpr int kVecThreads = 256;      // threads per element-wise workgroup
 
 // per-system scalar slots of the Krylov loops: scal[slot * n_sys + s]
