@@ -79,7 +79,7 @@ def parse():
     ap.add_argument("--solver", choices=["bicgstab", "fgmres", "gmres"], default="bicgstab")
     ap.add_argument("--skip-fp64", action="store_true")
     ap.add_argument("--tail-rows", type=int, default=0,
-                    help="V-cycle tail in one workgroup from levels of at most this many block rows "
+                    help="V-cycle tail as one dense operator from levels of at most this many block rows per system "
                          "(0 = library default, -1 = off)")
     ap.add_argument("--row-split", type=int, default=0,
                     help="threads per scalar row on levels under 32,768 block rows (0 = automatic)")

@@ -116,12 +116,15 @@ typedef struct cbs_options {
                                 scalar row (1, 2, 4, 8 or 16); 0 = chosen from
                                 the level's mean row length. Changes only the
                                 order of the row sums                [0] */
-    int32_t tail_rows;       /* AMG V-cycle: from the first level of at most
-                                this many block rows (all systems together)
+    int32_t tail_rows;       /* AMG V-cycle: from the first level on which no
+                                system has more than this many block rows
                                 down to the coarsest and back, the cycle runs
-                                in one workgroup (one kernel instead of about
-                                five per level); 0 = 256, < 0 = never. Changes
-                                only the order of the row sums       [0] */
+                                as one dense FP64 operator per system, formed
+                                at setup (one kernel instead of about five
+                                per level; at most 32 MB of operators, else
+                                it starts further down); 0 = 256, < 0 =
+                                never. Changes only the order of the row
+                                sums                                 [0] */
     int32_t schedule;        /* schedule of the block-row kernels (blocks
                                 loaded per step, non-temporal matrix loads):
                                 0 = timed on the level-0 operator at setup
@@ -144,7 +147,7 @@ typedef struct cbs_options {
                                 level is the coarsest runs it once, since
                                 that level is solved exactly. 0 = V-cycle;
                                 beyond the depth: every level (W-cycle).
-                                The single-workgroup tail starts below these
+                                The tail (tail_rows) starts below these
                                 levels                               [0] */
     double coarse_omega;     /* block-Jacobi damping on every level below the
                                 finest; 0 = omega there too (the paper

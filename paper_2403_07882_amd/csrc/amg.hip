@@ -1758,6 +1758,7 @@ void amg_setup(cbs_system *h) {
         L0.sell.sched64 = choose_sched(n, L0.sell, false, L0.sell.v64.get(), o.schedule, st);
         L0.sell.sched64.split = row_split_for(L0.sell, L0.nnzb, o.row_split);
         h->op_complexity = 1.0;
+        h->tail.level = -1;
         return;
     }
 
@@ -1995,6 +1996,9 @@ void amg_setup(cbs_system *h) {
                                             std::to_string(ev[1 + q]));
     if (ev[0] & 32) cbs_throw(CBS_ERR_SINGULAR, "coarsest-level matrix is singular");
     pt.mark("coarse");
+    tail_plan(h, reuse);
+    tail_form(h, false);
+    pt.mark("tail");
 }
 
 // Transposed level values for the adjoint solve: A^T(i,j) = A(j,i)^T through
@@ -2003,7 +2007,7 @@ void amg_build_transposed(cbs_system *h) {
     if (h->transposed_ready) return;
     hipStream_t st = h->stream;
     const int n = h->n;
-    const bool mixed = h->opt.precision == CBS_PRECISION_MIXED;
+    const bool mixed = h->opt.precision == CBS_PRECISION_MIXED, amg = h->opt.precond == CBS_PREC_AMG;
     const int nlev = (int)h->lev.size();
     HIPCHK(hipMemsetAsync(h->dflag.get(), 0, sizeof(int32_t), st));
     for (int q = 0; q < nlev; ++q) {
@@ -2052,6 +2056,7 @@ void amg_build_transposed(cbs_system *h) {
     // FP32 cannot hold some scaled value: the transposed sweeps keep D^{-T}
     const bool overflow = read_int(h->dflag.get(), st) & 64;
     for (auto &L : h->lev) L.scaledT = mixed && L.scaled && !overflow;
+    if (amg) tail_form(h, true);
     h->transposed_ready = true;
 }
 

@@ -117,10 +117,13 @@ inline double level_omega(const cbs_options &o, int l) {
     return (l > 0 && o.coarse_omega > 0.0) ? o.coarse_omega : o.omega;
 }
 
-// V-cycle tail (tail.hip): default block-row limit of its first level, and the
-// most levels (coarsest included) it takes
+// V-cycle tail (tail.hip): default limit of a system's block rows on its first
+// level, the most levels (coarsest included) it takes, and the most bytes its
+// dense operators may hold together (the eight L2 caches: beyond them the
+// product costs more than the launches it saves)
 constexpr int32_t kTailRowsDefault = 256;
 constexpr int kTailMax = 8;
+constexpr int64_t kTailOpBytes = (int64_t)32 << 20;
 
 // Schedule of the block-row kernels: blocks loaded per step (1, 2, 4) and
 // whether matrix values are loaded non-temporally; picked by autotuning.
@@ -237,6 +240,27 @@ struct Coarse {
     int32_t max_m = 0;
 };
 
+// One workgroup of the tail's product: rows o0 .. of a system's operator
+struct TailBlk {
+    int32_t row0, m;                     // the system's first block row on the tail's first level; its unknowns
+    int32_t o0, pad;
+    int64_t off;                         // first value of its operator
+};
+
+// The V-cycle tail: the cycle from `level` down as dense per-system operators
+// (op: forward, opT: of the transposed hierarchy), column by column
+struct Tail {
+    int level = -1;                      // first level, -1: none
+    int32_t nblk = 0, max_m = 0;
+    int32_t ncols = 1, wgs = 0;          // columns per workgroup that forms the operators, and workgroups
+    int64_t vals = 0;                    // values of all operators
+    DArr<double> op, opT;
+    DArr<TailBlk> blk;
+    DArr<int64_t> off;                   // first value of each system's operator
+    DArr<int32_t> roff;                  // first row of every system on every tail level, then each
+                                         // system's first workgroup of the forming kernel
+};
+
 // ---------------------------------------------------------------- handle
 struct cbs_system {
     int32_t N = 0, F = 0, n = 0, n_sys = 1;
@@ -260,6 +284,7 @@ struct cbs_system {
     cbs_options opt{};
     std::vector<Level> lev;
     Coarse coarse;
+    Tail tail;
     double op_complexity = 1.0;
     // Krylov workspace (FP64, N*n each)
     DArr<double> r, rh, p, v, ph, s, sh, t, w;
@@ -404,13 +429,13 @@ template <typename TA, typename TB>
 void launch_cast(int64_t m, const TA *a, TB *b, hipStream_t st);
 void launch_coarse_solve(cbs_system *h, bool transposed, const void *b, void *x, bool fp32);
 void launch_block_apply(int n, int32_t N, const double *Dinv, const double *r, double *z, hipStream_t st);
-// V-cycle tail (tail.hip): the first level (>= 1) from which the rest of the
-// cycle runs in one workgroup for level vectors of tsize bytes per value, or
-// -1; and that launch, given the residual of the level above (the result
-// lands in the first tail level's x)
-int tail_level_for(const cbs_system *h, size_t tsize);
+// V-cycle tail (tail.hip): tail_plan chooses the level it starts at (h->tail;
+// kept: the hierarchy's pattern is that of the last plan), tail_form forms its operators from the level matrices, and launch_tail runs
+// it on the residual of the level above (result: x of the first tail level)
+void tail_plan(cbs_system *h, bool kept);
+void tail_form(cbs_system *h, bool tr);
 template <typename T>
-void launch_tail(cbs_system *h, bool tr, int l0, const T *rfine);
+void launch_tail(cbs_system *h, bool tr, const T *rfine, T *x);
 // block Gauss-Seidel on the cnt rows of one colour, held at positions
 // p0 .. p0 + cnt of the colour-ordered copy S, in place, with the pivot
 // inverses Dinv (D or E): form 0 x_i = P_i^{-1} (b_i - sum_{j != i} A_ij x_j),

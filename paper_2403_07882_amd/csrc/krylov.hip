@@ -683,7 +683,7 @@ void vcycle(cbs_system *h, bool tr, int l, T *b, T *x, const T *rfine, const dou
         const Level &F = h->lev[l - 1];
         launch_restrict<T>(n, L.N, F.agg_ptr.get(), F.agg_mem.get(), rfine, b, st);
     };
-    if (!zero && (rfine || b64 || l == 0 || l == nlev - 1 || l == tail_level_for(h, sizeof(T))))
+    if (!zero && (rfine || b64 || l == 0 || l == nlev - 1 || l == h->tail.level))
         cbs_throw(CBS_ERR_ARG, "V-cycle from a start: not on this level");
     // the coarse correction: the next level's cycle, twice on the w_levels
     // finest levels (the second run from the first one's result), once where
@@ -692,8 +692,8 @@ void vcycle(cbs_system *h, bool tr, int l, T *b, T *x, const T *rfine, const dou
         vcycle<T>(h, tr, l + 1, bc, xc, r);
         if (l < o.w_levels && l + 2 < nlev) vcycle<T>(h, tr, l + 1, bc, xc, nullptr, nullptr, nullptr, false);
     };
-    if (rfine && l == tail_level_for(h, sizeof(T))) {        // the rest of the cycle in one workgroup
-        launch_tail<T>(h, tr, l, rfine);
+    if (rfine && l == h->tail.level) {                       // the rest of the cycle at once
+        launch_tail<T>(h, tr, rfine, x);
         return;
     }
     if (l == nlev - 1) {

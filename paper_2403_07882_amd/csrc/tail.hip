@@ -1,81 +1,65 @@
 // tail.hip -- the coarse end of the AMG V-cycle (Sec. 2.2: the
-// aggregation-AMG preconditioner) in one workgroup.
+// aggregation-AMG preconditioner) as one dense operator per system.
 //
-// Below a few hundred block rows a level's kernels are too small to fill even
-// one CU, and every step of the cycle there (restriction, each smoothing
-// sweep, the residual, the prolongation, the coarsest solve) costs one kernel
-// launch, about 4.5 us on gfx950 even inside a captured graph, most of it
-// spent waiting on chains of dependent loads.  From the first such level down
-// to the coarsest and back, one workgroup of 1024 threads runs the same steps
-// in the same order with workgroup barriers in between.  Everything but the
-// matrix values lives in LDS for the whole cycle: the level vectors, the
-// sliced-ELL patterns (slice offsets, widths, column indices) and the
-// aggregate maps, copied in once at the start.  The values are read from L2
-// with several blocks in flight per thread, so a step waits on about one
-// memory latency instead of one per block.  The arithmetic of each step is
-// that of the multi-kernel path (row sums split over threads and added in the
-// same order; only the number of partial sums per row differs), so the two
-// agree up to rounding order.
+// Below a few hundred block rows a level's kernels are too small to fill the
+// chip, and every step of the cycle there (restriction, each smoothing sweep,
+// the residual, the prolongation, the coarsest solve) waits on launches and
+// chains of dependent loads: about 4.5 us per launch inside a captured graph,
+// and 27-45 us for all of it run by one workgroup with its vectors in LDS.
+// From the first such level down to the coarsest and back the cycle is a
+// fixed linear map of that level's right side, though, and the map changes
+// only with the matrix.  cbs_setup therefore forms it once per system by
+// running the cycle on the columns of the identity, in FP64 whatever the
+// precision of the hierarchy (k_tail_operator), and a V-cycle applies it with
+// one launch (k_tail_apply: the restriction and a dense product).  The result
+// is the cycle's up to rounding; in mixed precision it is closer to the exact
+// cycle than FP32 sweeps are.
+//
+// MI355X, FP32 hierarchy of the 41x39x35-cell 4x4 system (tail of 107, 27 and
+// 6 rows): one workgroup 31.7 us per cycle, the operator 5.9 us, formed in
+// 99 us per setup; FP64, 960 cells (241, 62 and 16 rows): 34.9 ->
+// 6.6 us, formed in 108 us.
 #include "cbs_internal.h"
+
+#include <algorithm>
 
 namespace {
 
-constexpr int kTailThreads = 1024;
-// LDS for the staged vectors and index arrays: what a workgroup may hold
-// (160 KB on gfx950) less the two static reduction arrays (8 KB in FP32,
-// 16 KB in FP64) and 1 KB of margin
+constexpr int kTailThreads = 1024;         // threads of the workgroups that form the operator
+constexpr int kTailRowsPerWg = 16;         // scalar rows per workgroup of the product: one 128-byte
+                                           // line of a column of the operator
+constexpr int kTailApplyThreads = 512;
 constexpr int64_t kTailLdsReserve = 1024;
 
-template <typename T> struct TAcc { using type = double; };
-template <> struct TAcc<float> { using type = float; };
-
-// index arrays of a level staged into LDS, in this order
-enum { IA_SOFF, IA_SW, IA_SCOL, IA_SOFFO, IA_SWO, IA_SCOLO, IA_APTR, IA_AMEM, IA_AGG, IA_COUNT };
-constexpr int kTailCopies = IA_COUNT * kTailMax;
-
-// one level of the tail; offsets are elements into the LDS regions
-template <typename T>
+// one level of the tail
 struct TailLvl {
-    const T *val;                 // values of the full sliced pattern (residual, unscaled sweeps)
-    const T *sval;                // values of the row-scaled off-diagonal pattern (scaled sweeps)
-    const double *Dinv;           // FP64 inverses of the diagonal blocks
-    int32_t ia[IA_COUNT];         // int-region offsets: patterns, restriction lists (rows of
-                                  // the finer level per row here), aggregate map (row here ->
-                                  // row of the next coarser level)
-    int32_t vb, vx, vt, vr, vc;   // vector-region offsets: right side, solution, sweep buffer,
-                                  // residual, Dinv b
-    int32_t N;                    // block rows
-    int32_t lc, lco;              // log2 slice heights of the two patterns
-    int32_t sp, spo;              // threads per scalar row on the two patterns
-    int32_t scaled;               // sweeps on the row-scaled pattern against c (else with Dinv)
+    const double *val, *Dinv;              // sliced FP64 values, inverses of the diagonal blocks
+    const int32_t *soff, *sw, *scol;       // sliced pattern
+    const int32_t *aptr, *amem, *agg;      // rows of the finer level per row here; row of the coarser level
+    int32_t lc;
 };
 
-template <typename T>
 struct TailArgs {
-    TailLvl<T> lv[kTailMax];              // smoothed levels, coarsest last (lv[nl])
-    const int32_t *csrc[kTailCopies];     // index arrays to stage, in int-region order
-    int32_t cpre[kTailCopies + 1];        // their prefix offsets in the int region
-    const T *rfine;                       // residual of the level above the tail
-    T *xout;                              // where the first tail level's solution goes
-    const double *cinv;                   // coarsest: per-system dense inverses
-    const int64_t *coff;                  // element offset of each inverse
-    const int32_t *cm;                    // order of each system's coarsest matrix
-    const int64_t *croff;                 // first scalar row of each system
+    TailLvl lv[kTailMax];                  // smoothed levels, coarsest last (lv[nl])
+    const int32_t *roff;                   // first row of system s on tail level k: roff[k * (nsys + 1) + s]
+    const double *cinv;                    // coarsest: per-system dense inverses
+    const int64_t *coff;
+    const int32_t *cm;
+    const int64_t *opoff;                  // first value of each system's operator
+    const int32_t *wgoff;                  // first workgroup of each system
+    double *op;
     double omega;
     int32_t nl, nu1, nu2, nsys;
-    int32_t ncopy, nints;                 // staged arrays and their total length
-    int32_t ints_off;                     // byte offset of the int region in LDS
 };
-static_assert(sizeof(TailArgs<double>) <= 4096, "V-cycle tail arguments exceed the kernel-argument limit");
+static_assert(sizeof(TailArgs) <= 4096, "V-cycle tail arguments exceed the kernel-argument limit");
+
+// leading dimension of an operator of order m (its columns start on 128-byte lines)
+__host__ __device__ inline int64_t tail_ld(int64_t m) { return (m + kTailRowsPerWg - 1) / kTailRowsPerWg * kTailRowsPerWg; }
 
 // row r of one block: n contiguous values (16-byte loads for n = 4)
-template <int n, typename T>
-__device__ inline void tail_load_row(const T *__restrict__ p, T (&v)[n]) {
-    if constexpr (n == 4 && sizeof(T) == 4) {
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        const f4 a = *reinterpret_cast<const f4 *>(p);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    } else if constexpr (n == 4 && sizeof(T) == 8) {
+template <int n>
+__device__ inline void tail_load_row(const double *__restrict__ p, double (&v)[n]) {
+    if constexpr (n == 4) {
         typedef double d2 __attribute__((ext_vector_type(2)));
         const d2 a = *reinterpret_cast<const d2 *>(p), b = *(reinterpret_cast<const d2 *>(p) + 1);
         v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
@@ -85,411 +69,435 @@ __device__ inline void tail_load_row(const T *__restrict__ p, T (&v)[n]) {
     }
 }
 
-// copy every index array into the int region, eight elements per thread in
-// flight
-template <typename T>
-__device__ void tail_stage(const TailArgs<T> &a, int32_t *dst) {
-    constexpr int U = 8;
-    const int t = threadIdx.x;
-    for (int32_t g0 = 0; g0 < a.nints; g0 += kTailThreads * U) {
-        int32_t v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t g = g0 + u * kTailThreads + t;
-            v[u] = 0;
-            if (g < a.nints) {
-                int c = 0;
-                while (a.cpre[c + 1] <= g) ++c;      // the array holding element g
-                v[u] = a.csrc[c][g - a.cpre[c]];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t g = g0 + u * kTailThreads + t;
-            if (g < a.nints) dst[g] = v[u];
-        }
-    }
-    __syncthreads();
-}
+// one system's rows of a level, and where its vectors (doubles, NC columns side
+// by side) and staged index lists (integers) start in LDS
+struct TailRows {
+    int32_t row0, N, sl0;                  // first row, rows, first slice
+    int32_t b, x, r;
+    int32_t soff, sw, aptr, amem, agg;
+};
 
-// y = op(from) over all rows of a level; every thread of the workgroup calls
-// it.  MODE 1: y = b - A from; 2: y = from + omega Dinv (b - A from);
-// 4: y = from + omega (b - from - A from) on the row-scaled values (b = Dinv b).
-// sp threads share each scalar row and take its blocks kk, kk + sp, ... (U
-// loaded before they are summed, in that order); the partial sums meet in LDS
-// and are added in kk order.
-template <int n, typename T, int MODE>
-__device__ void tail_rows(const int32_t *soff, const int32_t *sw, const int32_t *scol, int lc,
-                          const T *__restrict__ val, int sp, int32_t N, const T *from, const T *b, T *y,
-                          const double *__restrict__ Dinv, double omega, typename TAcc<T>::type *spart,
-                          typename TAcc<T>::type *sres) {
-    using A = typename TAcc<T>::type;
-    // blocks in flight per thread (more only adds loads of padding: one CU's
-    // bandwidth, not the latency, then sets the time)
+// r = b - A x over one system's rows of a level.  sp adjacent lanes share a
+// scalar row and take its blocks kk, kk + sp, ... (four loaded before they
+// are summed); their partial sums meet by shuffles.
+template <int n, int NC>
+__device__ __forceinline__ void tail_residual(const TailLvl &L, const TailRows &S, double *vs, const int32_t *is) {
     constexpr int nn = n * n, U = 4;
-    const int tpr = n * sp, R = kTailThreads / tpr;
-    const int t = threadIdx.x;
-    const int lr = t / tpr, kr = t - lr * tpr;
-    const int kk = kr / n, r = kr - kk * n;
-    for (int32_t i0 = 0; i0 < N; i0 += R) {
-        const int32_t i = i0 + lr;
-        const bool act = lr < R && i < N;
-        const int32_t o = i * n + r;
-        A acc = 0;
-        if (act) {
-            const int32_t sl = i >> lc, ii = i - (sl << lc);
-            const int32_t base = soff[sl] + ii, w = sw[sl];
+    const double *x = vs + S.x, *b = vs + S.b;
+    double *r = vs + S.r;
+    const int32_t *soff = is + S.soff, *sw = is + S.sw;
+    int sp = 1;
+    while (sp < 16 && S.N * n * sp * 2 <= kTailThreads) sp *= 2;
+    const int lane_row = threadIdx.x / sp, kk = threadIdx.x & (sp - 1), R = kTailThreads / sp;
+    const int32_t m = S.N * n;
+    for (int32_t o0 = 0; o0 < m; o0 += R) {
+        const int32_t o = o0 + lane_row;
+        double acc[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[c] = 0.0;
+        if (o < m) {
+            const int32_t i = o / n, rr = o - i * n, gi = S.row0 + i;
+            const int32_t sl = gi >> L.lc, base = soff[sl - S.sl0] + (gi - (sl << L.lc)), w = sw[sl - S.sl0];
             for (int32_t k = kk; k < w; k += sp * U) {
                 int32_t j[U];
-                T bv[U][n];
+                double bv[U][n];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int32_t kq = k + u * sp;
-                    const bool ok = kq < w;
-                    const int32_t e = base + ((ok ? kq : kk) << lc);
-                    j[u] = ok ? scol[e] : -1;
-                    tail_load_row<n, T>(val + (int64_t)e * nn + r * n, bv[u]);
+                    const int64_t e = base + ((int64_t)(kq < w ? kq : kk) << L.lc);
+                    j[u] = L.scol[e];
+                    if (kq >= w) j[u] = -1;
+                    tail_load_row<n>(L.val + e * nn + rr * n, bv[u]);
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u)
                     if (j[u] >= 0) {
-                        const T *xj = from + j[u] * n;
+                        const double *xj = x + (j[u] - S.row0) * n * NC;
 #pragma unroll
-                        for (int c = 0; c < n; ++c) acc += (A)bv[u][c] * (A)xj[c];
+                        for (int q = 0; q < n; ++q)
+#pragma unroll
+                            for (int c = 0; c < NC; ++c) acc[c] += bv[u][q] * xj[q * NC + c];
                     }
             }
         }
-        spart[t] = acc;
-        __syncthreads();
-        if (act && kk == 0) {
-            A sum = 0;
-            for (int q = 0; q < sp; ++q) sum += spart[lr * tpr + q * n + r];
-            const A res = (A)b[o] - sum;
-            if (MODE == 1) {
-                y[o] = (T)res;
-            } else if (MODE == 4) {
-                const A xo = (A)from[o];
-                y[o] = (T)(xo + (A)omega * (res - xo));
-            } else {
-                sres[lr * n + r] = res;
-            }
-        }
-        if (MODE == 2) {
-            __syncthreads();
-            if (act && kk == 0) {
-                const double *Di = Dinv + (int64_t)i * nn + r * n;
-                double z = 0.0;
+        for (int s = sp >> 1; s > 0; s >>= 1)
 #pragma unroll
-                for (int c = 0; c < n; ++c) z += Di[c] * (double)sres[lr * n + c];
-                y[o] = (T)((A)from[o] + (A)(omega * z));
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// b = R rf (rows of the finer level summed in member order); then, when
-// sweep0, x = omega Dinv b, and when c is given, c = Dinv b.
-template <int n, typename T>
-__device__ void tail_restrict(int32_t nc, const int32_t *aptr, const int32_t *amem, const T *rf, T *b,
-                              const double *__restrict__ Dinv, double omega, T *x, T *c, bool sweep0,
-                              typename TAcc<T>::type *sb) {
-    using A = typename TAcc<T>::type;
-    constexpr int nn = n * n;
-    constexpr int R = kTailThreads / n;
-    const int t = threadIdx.x;
-    const int lr = t / n, q = t - lr * n;
-    const bool dinv = sweep0 || c != nullptr;
-    for (int32_t i0 = 0; i0 < nc; i0 += R) {
-        const int32_t I = i0 + lr;
-        const bool act = lr < R && I < nc;
-        const int32_t o = I * n + q;
-        A s = 0;
-        if (act)
-            for (int32_t m = aptr[I]; m < aptr[I + 1]; ++m) s += (A)rf[amem[m] * n + q];
-        const T bv = (T)s;
-        if (act) b[o] = bv;
-        if (dinv) {
-            sb[t] = (A)bv;
-            __syncthreads();
-            if (act) {
-                const double *Di = Dinv + (int64_t)I * nn + q * n;
-                double z = 0.0;
+            for (int c = 0; c < NC; ++c) acc[c] += __shfl_xor(acc[c], s, 64);
+        if (o < m && kk == 0)
 #pragma unroll
-                for (int k = 0; k < n; ++k) z += Di[k] * (double)sb[lr * n + k];
-                if (sweep0) x[o] = (T)((A)0 + (A)(omega * z));
-                if (c) c[o] = (T)z;
-            }
-            __syncthreads();
+            for (int c = 0; c < NC; ++c) r[o * NC + c] = b[o * NC + c] - acc[c];
+    }
+    __syncthreads();
+}
+
+// x += omega Dinv r, or from a zero guess (ZERO) x = omega Dinv b
+template <int n, int NC, bool ZERO>
+__device__ __forceinline__ void tail_correct(const TailLvl &L, const TailRows &S, double *vs, double omega) {
+    const double *v = vs + (ZERO ? S.b : S.r);
+    double *x = vs + S.x;
+    for (int32_t o = threadIdx.x; o < S.N * n; o += kTailThreads) {
+        const int32_t i = o / n, rr = o - i * n;
+        double d[n];
+        tail_load_row<n>(L.Dinv + ((int64_t)(S.row0 + i) * n + rr) * n, d);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            double z = 0.0;
+#pragma unroll
+            for (int q = 0; q < n; ++q) z += d[q] * v[(i * n + q) * NC + c];
+            x[o * NC + c] = (ZERO ? 0.0 : x[o * NC + c]) + omega * z;
         }
     }
     __syncthreads();
 }
 
-template <typename T>
-__device__ void tail_fill(int32_t m, T *x) {
-    for (int32_t g = threadIdx.x; g < m; g += kTailThreads) x[g] = (T)0;
-    __syncthreads();
-}
-
-// x += P e: every row takes the correction of its aggregate
-template <int n, typename T>
-__device__ void tail_prolong(int32_t N, const int32_t *agg, const T *e, T *x) {
-    for (int32_t g = threadIdx.x; g < N * n; g += kTailThreads) {
-        const int32_t i = g / n;
-        const int q = g - i * n;
-        x[g] += e[agg[i] * n + q];
-    }
-    __syncthreads();
-}
-
-// coarsest level: x_s = inv_s b_s for every system s, in FP64
-template <typename T>
-__device__ void tail_coarse(int32_t m_all, const double *__restrict__ inv, const int64_t *__restrict__ off,
-                            const int32_t *__restrict__ msz, const int64_t *__restrict__ roff, int32_t nsys,
-                            const T *b, T *x) {
-    for (int32_t g = threadIdx.x; g < m_all; g += kTailThreads) {
-        int32_t lo = 0, hi = nsys - 1;             // last system whose first row is <= g
-        while (lo < hi) {
-            const int32_t mid = (lo + hi + 1) >> 1;
-            if (roff[mid] <= g) lo = mid;
-            else hi = mid - 1;
-        }
-        const int32_t r0 = (int32_t)roff[lo];
-        const int m = msz[lo];
-        const double *M = inv + off[lo] + (int64_t)(g - r0) * m;
-        double acc = 0.0;
-        for (int c = 0; c < m; ++c) acc += M[c] * (double)b[r0 + c];
-        x[g] = (T)acc;
-    }
-    __syncthreads();
-}
-
-template <int n, typename T>
-__device__ void tail_sweep(const TailLvl<T> &L, const int32_t *is, T *vs, double omega, const T *from, T *to,
-                           typename TAcc<T>::type *spart, typename TAcc<T>::type *sres) {
-    if (L.scaled)
-        tail_rows<n, T, 4>(is + L.ia[IA_SOFFO], is + L.ia[IA_SWO], is + L.ia[IA_SCOLO], L.lco, L.sval, L.spo, L.N,
-                           from, vs + L.vc, to, nullptr, omega, spart, sres);
-    else
-        tail_rows<n, T, 2>(is + L.ia[IA_SOFF], is + L.ia[IA_SW], is + L.ia[IA_SCOL], L.lc, L.val, L.sp, L.N, from,
-                           vs + L.vb, to, L.Dinv, omega, spart, sres);
-}
-
-// The V-cycle below the level above the tail, same steps as the multi-kernel
-// path: per level on the way down a zero-guess sweep fused with the
-// restriction, nu1 - 1 more sweeps, the residual; the coarsest solve; per
-// level on the way up the prolongation and nu2 sweeps.  Each level's result
-// ends in its x (the sweeps alternate between x and t, starting on the one
-// that makes the last sweep write x); the first level's x is copied out.
-template <int n, typename T>
-__global__ __launch_bounds__(kTailThreads) void k_tail(const TailArgs<T> a) {
-    using A = typename TAcc<T>::type;
+// Columns q0 .. q0 + NC of one system's operator: the cycle of the tail on
+// unit right sides.  The level vectors and index lists of the system are in
+// LDS; matrix values and columns are read from L2, each block row once for
+// the NC columns.  Bound by those reads and by the barriers between steps.
+template <int n, int NC>
+__global__ __launch_bounds__(kTailThreads) void k_tail_operator(const TailArgs a) {
     extern __shared__ __align__(16) char smem[];
-    __shared__ A spart[kTailThreads];
-    __shared__ A sres[kTailThreads];
-    T *vs = reinterpret_cast<T *>(smem);
-    int32_t *is = reinterpret_cast<int32_t *>(smem + a.ints_off);
-    tail_stage<T>(a, is);
-    const int nl = a.nl;
-    const int switches = (a.nu1 >= 1 ? a.nu1 - 1 : 0) + a.nu2;
-    const int pre_swaps = a.nu1 >= 1 ? a.nu1 - 1 : 0;
-    for (int k = 0; k < nl; ++k) {
-        const TailLvl<T> &L = a.lv[k];
-        T *cur = vs + ((switches % 2 == 0) ? L.vx : L.vt);
-        T *oth = vs + ((switches % 2 == 0) ? L.vt : L.vx);
-        const T *rf = k == 0 ? a.rfine : vs + a.lv[k - 1].vr;
-        const int32_t *aptr = is + L.ia[IA_APTR], *amem = is + L.ia[IA_AMEM];
-        T *c = L.scaled ? vs + L.vc : nullptr;
-        if (a.nu1 >= 1) {
-            tail_restrict<n, T>(L.N, aptr, amem, rf, vs + L.vb, L.Dinv, a.omega, cur, c, true, sres);
-            for (int s = 1; s < a.nu1; ++s) {
-                tail_sweep<n, T>(L, is, vs, a.omega, cur, oth, spart, sres);
-                T *tmp = cur; cur = oth; oth = tmp;
-            }
-        } else {
-            tail_restrict<n, T>(L.N, aptr, amem, rf, vs + L.vb, L.Dinv, a.omega, nullptr, a.nu2 > 0 ? c : nullptr,
-                                false, sres);
-            tail_fill<T>(L.N * n, cur);
-        }
-        tail_rows<n, T, 1>(is + L.ia[IA_SOFF], is + L.ia[IA_SW], is + L.ia[IA_SCOL], L.lc, L.val, L.sp, L.N, cur,
-                           vs + L.vb, vs + L.vr, nullptr, 0.0, spart, sres);
+    __shared__ TailRows sS[kTailMax];
+    double *vs = reinterpret_cast<double *>(smem);
+    const int nl = a.nl, t = threadIdx.x;
+    // the workgroup's system (the last whose first workgroup is not past it) and columns
+    int s = 0;
+    for (int hi = a.nsys - 1; s < hi;) {
+        const int mid = (s + hi + 1) >> 1;
+        if (a.wgoff[mid] <= (int32_t)blockIdx.x) s = mid;
+        else hi = mid - 1;
     }
-    {
-        const TailLvl<T> &C = a.lv[nl];
-        const T *rf = nl == 0 ? a.rfine : vs + a.lv[nl - 1].vr;
-        tail_restrict<n, T>(C.N, is + C.ia[IA_APTR], is + C.ia[IA_AMEM], rf, vs + C.vb, nullptr, 0.0, nullptr,
-                            nullptr, false, sres);
-        tail_coarse<T>(C.N * n, a.cinv, a.coff, a.cm, a.croff, a.nsys, vs + C.vb, vs + C.vx);
+    const int32_t q0 = ((int32_t)blockIdx.x - a.wgoff[s]) * NC;
+    int32_t nv = 0;                                  // doubles of the vectors
+    for (int k = 0; k <= nl; ++k) {
+        const int32_t *ro = a.roff + k * (a.nsys + 1) + s;
+        nv += (k < nl ? 3 : 2) * (ro[1] - ro[0]) * n * NC;
+    }
+    int32_t *is = reinterpret_cast<int32_t *>(vs + nv);
+    if (t == 0) {
+        int32_t v = 0, p = 0;
+        for (int k = 0; k <= nl; ++k) {
+            const int32_t *ro = a.roff + k * (a.nsys + 1) + s;
+            TailRows S{};
+            S.row0 = ro[0];
+            S.N = ro[1] - ro[0];
+            S.sl0 = S.row0 >> a.lv[k].lc;
+            S.b = v; v += S.N * n * NC;
+            S.x = v; v += S.N * n * NC;
+            S.r = v; v += k < nl ? S.N * n * NC : 0;
+            if (k < nl) {
+                const int32_t ns = ((S.row0 + S.N - 1) >> a.lv[k].lc) - S.sl0 + 1;
+                S.soff = p; p += ns;
+                S.sw = p; p += ns;
+                S.agg = p; p += S.N;
+            }
+            if (k > 0) {
+                S.aptr = p; p += S.N + 1;
+                S.amem = p; p += sS[k - 1].N;
+            }
+            sS[k] = S;
+        }
+    }
+    __syncthreads();
+    for (int k = 0; k <= nl; ++k) {
+        const TailRows S = sS[k];
+        const TailLvl &L = a.lv[k];
+        if (k < nl) {
+            const int32_t ns = ((S.row0 + S.N - 1) >> L.lc) - S.sl0 + 1, c0 = sS[k + 1].row0;
+            for (int32_t e = t; e < ns; e += kTailThreads) {
+                is[S.soff + e] = L.soff[S.sl0 + e];
+                is[S.sw + e] = L.sw[S.sl0 + e];
+            }
+            for (int32_t e = t; e < S.N; e += kTailThreads) is[S.agg + e] = L.agg[S.row0 + e] - c0;
+        }
+        if (k > 0) {
+            const int32_t p0 = L.aptr[S.row0], f0 = sS[k - 1].row0, nf = sS[k - 1].N;
+            for (int32_t e = t; e <= S.N; e += kTailThreads) is[S.aptr + e] = L.aptr[S.row0 + e] - p0;
+            for (int32_t e = t; e < nf; e += kTailThreads) is[S.amem + e] = L.amem[p0 + e] - f0;
+        }
+    }
+    const int32_t m = sS[0].N * n;
+    for (int32_t e = t; e < m * NC; e += kTailThreads) vs[sS[0].b + e] = e / NC == q0 + e % NC ? 1.0 : 0.0;
+    __syncthreads();
+    for (int k = 0; k < nl; ++k) {
+        const TailRows S = sS[k], C = sS[k + 1];
+        const TailLvl &L = a.lv[k];
+        if (a.nu1 >= 1) {
+            tail_correct<n, NC, true>(L, S, vs, a.omega);
+            for (int q = 1; q < a.nu1; ++q) {
+                tail_residual<n, NC>(L, S, vs, is);
+                tail_correct<n, NC, false>(L, S, vs, a.omega);
+            }
+            tail_residual<n, NC>(L, S, vs, is);
+        } else {
+            for (int32_t e = t; e < S.N * n * NC; e += kTailThreads) {
+                vs[S.x + e] = 0.0;
+                vs[S.r + e] = vs[S.b + e];
+            }
+            __syncthreads();
+        }
+        // b of the next level: the residual summed over each aggregate
+        for (int32_t e = t; e < C.N * n * NC; e += kTailThreads) {
+            const int32_t I = e / (n * NC), q = e - I * n * NC;
+            double v = 0.0;
+            for (int32_t p = is[C.aptr + I]; p < is[C.aptr + I + 1]; ++p) v += vs[S.r + is[C.amem + p] * n * NC + q];
+            vs[C.b + e] = v;
+        }
+        __syncthreads();
+    }
+    {   // coarsest: the dense inverse
+        const TailRows S = sS[nl];
+        const int mc = a.cm[s];
+        const double *M = a.cinv + a.coff[s];
+        for (int32_t o = t; o < mc; o += kTailThreads) {
+            double acc[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[c] = 0.0;
+#pragma unroll 4
+            for (int q = 0; q < mc; ++q) {
+                const double v = M[(int64_t)o * mc + q];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) acc[c] += v * vs[S.b + q * NC + c];
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c) vs[S.x + o * NC + c] = acc[c];
+        }
+        __syncthreads();
     }
     for (int k = nl - 1; k >= 0; --k) {
-        const TailLvl<T> &L = a.lv[k];
-        T *cur = vs + ((switches % 2 == 0) ? L.vx : L.vt);
-        T *oth = vs + ((switches % 2 == 0) ? L.vt : L.vx);
-        if (pre_swaps % 2 == 1) { T *tmp = cur; cur = oth; oth = tmp; }
-        tail_prolong<n, T>(L.N, is + L.ia[IA_AGG], vs + a.lv[k + 1].vx, cur);
-        for (int s = 0; s < a.nu2; ++s) {
-            tail_sweep<n, T>(L, is, vs, a.omega, cur, oth, spart, sres);
-            T *tmp = cur; cur = oth; oth = tmp;
+        const TailRows S = sS[k];
+        const int32_t xc = sS[k + 1].x;
+        for (int32_t e = t; e < S.N * n * NC; e += kTailThreads) {
+            const int32_t i = e / (n * NC);
+            vs[S.x + e] += vs[xc + is[S.agg + i] * n * NC + (e - i * n * NC)];
+        }
+        __syncthreads();
+        for (int q = 0; q < a.nu2; ++q) {
+            tail_residual<n, NC>(a.lv[k], S, vs, is);
+            tail_correct<n, NC, false>(a.lv[k], S, vs, a.omega);
         }
     }
-    const T *x0 = vs + a.lv[0].vx;
-    for (int32_t g = threadIdx.x; g < a.lv[0].N * n; g += kTailThreads) a.xout[g] = x0[g];
+    const int64_t ld = tail_ld(m);
+    double *op = a.op + a.opoff[s];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        if (q0 + c < m)
+            for (int32_t o = t; o < m; o += kTailThreads) op[(q0 + c) * ld + o] = vs[sS[0].x + o * NC + c];
 }
 
-template <typename T> T *vp(DArr<char> &a) { return reinterpret_cast<T *>(a.get()); }
-
-// threads per scalar row in the tail: the largest power of two up to 16 that
-// keeps every row of the level in one pass of the workgroup
-int32_t tail_split(int32_t N, int n) {
-    int32_t sp = 1;
-    while (sp < 16 && (int64_t)N * n * sp * 2 <= kTailThreads) sp *= 2;
-    return sp;
+// kTailRowsPerWg scalar rows of one system's operator times the restricted
+// residual of the finer level.  Every workgroup forms the whole right side of
+// its system (a few KB of gathers); its 16 lanes per column read one line of
+// the operator each step.
+template <int n, typename T>
+__global__ __launch_bounds__(kTailApplyThreads) void k_tail_apply(const TailBlk *__restrict__ blk,
+                                                                  const double *__restrict__ op,
+                                                                  const int32_t *__restrict__ aptr,
+                                                                  const int32_t *__restrict__ amem,
+                                                                  const T *__restrict__ rf, T *__restrict__ x) {
+    extern __shared__ __align__(16) char smem[];
+    double *b = reinterpret_cast<double *>(smem);
+    __shared__ double red[kTailApplyThreads / 64][kTailRowsPerWg];
+    constexpr int J = kTailApplyThreads / kTailRowsPerWg, U = 4;
+    const TailBlk d = blk[blockIdx.x];
+    const int t = threadIdx.x, i = t & (kTailRowsPerWg - 1), jj = t / kTailRowsPerWg;
+    const int64_t ld = tail_ld(d.m);
+    for (int32_t g = t; g < d.m; g += kTailApplyThreads) {
+        const int32_t I = d.row0 + g / n, q = g % n, p0 = aptr[I], p1 = aptr[I + 1];
+        // members are summed in order, U rows in flight
+        T s = 0;
+        for (int32_t p = p0; p < p1; p += U) {
+            T v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = rf[(int64_t)amem[min(p + u, p1 - 1)] * n + q];
+#pragma unroll
+            for (int u = 0; u < U; ++u) s += p + u < p1 ? v[u] : (T)0;
+        }
+        b[g] = (double)s;
+    }
+    __syncthreads();
+    const double *Ti = op + d.off + d.o0 + i;
+    double acc = 0.0;
+#pragma unroll 8
+    for (int32_t j = jj; j < d.m; j += J) acc += Ti[j * ld] * b[j];
+    acc += __shfl_xor(acc, 16, 64);
+    acc += __shfl_xor(acc, 32, 64);
+    if ((t & 63) < kTailRowsPerWg) red[t >> 6][i] = acc;
+    __syncthreads();
+    if (t < kTailRowsPerWg && d.o0 + t < d.m) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < kTailApplyThreads / 64; ++w) v += red[w][t];
+        x[(int64_t)d.row0 * n + d.o0 + t] = (T)v;
+    }
 }
 
-// Lay the tail starting at level l0 out in LDS (vectors of T, then the index
-// arrays) and fill the layout part of the arguments; returns the bytes of LDS
-// it needs.  With a == nullptr only the size is computed.
-template <typename T>
-int64_t tail_plan(const cbs_system *h, int l0, bool tr, TailArgs<T> *a) {
-    constexpr bool fp32 = sizeof(T) == sizeof(float);
-    const int n = h->n;
+// LDS of k_tail_operator for the largest system when the tail starts at l0
+// and NC columns run together
+int64_t tail_lds(const cbs_system *h, int l0, int NC) {
     const int nlev = (int)h->lev.size();
-    const int nl = nlev - 1 - l0;
-    auto scaled = [&](const Level &L) { return fp32 && (tr ? L.scaledT : L.scaled); };
-    int64_t nvec = 0;                                  // elements of T
-    for (int k = 0; k <= nl; ++k) {
-        const Level &L = h->lev[l0 + k];
-        const bool sc = k < nl && scaled(L);
-        const int nv = k == nl ? 2 : (sc ? 5 : 4);
-        const int64_t m = (int64_t)L.N * n;
-        if (a) {
-            TailLvl<T> &d = a->lv[k];
-            d.vb = (int32_t)nvec;
-            d.vx = (int32_t)(nvec + m);
-            if (k < nl) { d.vt = (int32_t)(nvec + 2 * m); d.vr = (int32_t)(nvec + 3 * m); }
-            if (sc) d.vc = (int32_t)(nvec + 4 * m);
+    int64_t most = 0;
+    for (int s = 0; s < h->n_sys; ++s) {
+        int64_t dbl = 0, ints = 0, finer = 0;
+        for (int l = l0; l < nlev; ++l) {
+            const Level &L = h->lev[l];
+            const int64_t N = L.sys_off[s + 1] - L.sys_off[s];
+            dbl += (l + 1 < nlev ? 3 : 2) * N * h->n * NC;
+            if (l + 1 < nlev) ints += 2 * ((N >> L.sell.lc) + 2) + N;
+            if (l > l0) ints += N + 1 + finer;
+            finer = N;
         }
-        nvec += nv * m;
+        most = std::max(most, dbl * 8 + ints * 4);
     }
-    const int64_t ints_off = (nvec * (int64_t)sizeof(T) + 15) / 16 * 16;
-    int64_t nints = 0;
-    int ncopy = 0;
-    auto add = [&](int k, int which, const int32_t *src, int64_t cnt) {
-        if (a) {
-            a->lv[k].ia[which] = (int32_t)nints;
-            if (cnt > 0) {
-                a->csrc[ncopy] = src;
-                a->cpre[ncopy] = (int32_t)nints;
-                ++ncopy;
-            }
-        }
-        nints += cnt;
-    };
-    for (int k = 0; k <= nl; ++k) {
-        const Level &L = h->lev[l0 + k];
-        const Level &F = h->lev[l0 + k - 1];
-        if (k < nl) {
-            add(k, IA_SOFF, L.sell.soff.get(), (int64_t)L.sell.nslices + 1);
-            add(k, IA_SW, L.sell.sw.get(), L.sell.nslices);
-            add(k, IA_SCOL, L.sell.scol.get(), L.sell.nent);
-            if (scaled(L)) {
-                add(k, IA_SOFFO, L.sod.soff.get(), (int64_t)L.sod.nslices + 1);
-                add(k, IA_SWO, L.sod.sw.get(), L.sod.nslices);
-                add(k, IA_SCOLO, L.sod.scol.get(), L.sod.nent);
-            }
-            add(k, IA_AGG, L.agg.get(), L.N);
-        }
-        add(k, IA_APTR, F.agg_ptr.get(), (int64_t)L.N + 1);
-        add(k, IA_AMEM, F.agg_mem.get(), F.N);
-    }
-    if (a) {
-        a->cpre[ncopy] = (int32_t)nints;
-        a->ncopy = ncopy;
-        a->nints = (int32_t)nints;
-        a->ints_off = (int32_t)ints_off;
-    }
-    return ints_off + nints * 4;
+    return most;
 }
 
-// dynamic LDS left for the tail: the device's per-workgroup limit (160 KB on
-// gfx950) less the kernel's static reduction arrays and a reserve
-int64_t tail_budget(const cbs_system *h, size_t tsize) {
-    return (int64_t)h->lds_max - 2 * kTailThreads * (int64_t)(tsize == sizeof(float) ? sizeof(float) : sizeof(double)) -
-           kTailLdsReserve;
+int64_t tail_lds_budget(const cbs_system *h) {
+    return (int64_t)h->lds_max - (int64_t)sizeof(TailRows) * kTailMax - kTailLdsReserve;
 }
 
-}  // namespace
-
-int tail_level_for(const cbs_system *h, size_t tsize) {
+// the first level (>= 1) that starts the tail, or -1
+int tail_level(const cbs_system *h) {
     const int nlev = (int)h->lev.size();
     if (nlev < 2 || h->opt.precond != CBS_PREC_AMG) return -1;
     const int32_t lim = h->opt.tail_rows == 0 ? kTailRowsDefault : h->opt.tail_rows;
     if (lim < 0) return -1;
     // a level whose cycle runs twice (W-cycle) keeps its per-step kernels
     for (int l = std::max(1, h->opt.w_levels + 1); l < nlev; ++l) {
-        if (h->lev[l].N > lim || nlev - l > kTailMax) continue;
-        bool dilu = false;                           // DILU and Gauss-Seidel levels keep their own kernels
-        for (int q = l; q + 1 < nlev; ++q) dilu = dilu || h->lev[q].dilu || h->lev[q].sgs;
-        if (dilu) continue;
-        // the forward layout is the larger one (scaled levels add a pattern and c)
-        const int64_t need = tsize == sizeof(float) ? tail_plan<float>(h, l, false, nullptr)
-                                                    : tail_plan<double>(h, l, false, nullptr);
-        if (need <= tail_budget(h, tsize)) return l;
+        if (nlev - l > kTailMax) continue;
+        const Level &L = h->lev[l];
+        int64_t rows = 0, vals = 0, m_max = 0;
+        for (int s = 0; s < h->n_sys; ++s) {
+            const int64_t N = L.sys_off[s + 1] - L.sys_off[s], m = N * h->n;
+            rows = std::max(rows, N);
+            m_max = std::max(m_max, m);
+            vals += m * tail_ld(m);
+        }
+        if (rows > lim || vals * 8 > kTailOpBytes || m_max * 8 > 64 * 1024) continue;
+        bool coloured = false;                       // DILU and Gauss-Seidel levels keep their own kernels
+        for (int q = l; q + 1 < nlev; ++q) coloured = coloured || h->lev[q].dilu || h->lev[q].sgs;
+        if (!coloured && tail_lds(h, l, 1) <= tail_lds_budget(h)) return l;
     }
     return -1;
 }
 
-template <typename T>
-void launch_tail(cbs_system *h, bool tr, int l0, const T *rfine) {
-    constexpr bool fp32 = sizeof(T) == sizeof(float);
-    const int n = h->n;
-    const int nlev = (int)h->lev.size();
-    const int nl = nlev - 1 - l0;
-    if (l0 < 1 || nl < 0 || nl + 1 > kTailMax) cbs_throw(CBS_ERR_ARG, "V-cycle tail: bad level range");
-    TailArgs<T> a{};
-    const int64_t lds = tail_plan<T>(h, l0, tr, &a);
-    if (lds > tail_budget(h, sizeof(T))) cbs_throw(CBS_ERR_ARG, "V-cycle tail: LDS budget exceeded");
-    for (int k = 0; k <= nl; ++k) {
-        Level &L = h->lev[l0 + k];
-        TailLvl<T> &d = a.lv[k];
-        d.N = L.N;
-        if (k == nl) break;                            // the coarsest needs no more
-        if constexpr (fp32) d.val = tr ? L.sell.v32T.get() : L.sell.v32.get();
-        else d.val = tr ? L.sell.v64T.get() : L.sell.v64.get();
-        d.Dinv = tr ? L.DinvT.get() : L.Dinv.get();
-        d.lc = L.sell.lc;
-        d.sp = tail_split(L.N, n);
-        d.scaled = fp32 && (tr ? L.scaledT : L.scaled);
-        if (d.scaled) {
-            d.sval = reinterpret_cast<const T *>(tr ? L.sod.v32T.get() : L.sod.v32.get());
-            d.lco = L.sod.lc;
-            d.spo = d.sp;
-        }
+template <int n, int NC>
+void operator_launch(const TailArgs &a, unsigned wgs, size_t lds, hipStream_t st) {
+    // more than 64 KB of dynamic LDS is requested explicitly
+    if (lds > 64 * 1024)
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tail_operator<n, NC>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL((k_tail_operator<n, NC>), dim3(wgs), dim3(kTailThreads), lds, st, a);
+    LAUNCHCHK();
+}
+
+template <int n>
+void operator_nc(int NC, const TailArgs &a, unsigned wgs, size_t lds, hipStream_t st) {
+    if (NC == 4) operator_launch<n, 4>(a, wgs, lds, st);
+    else if (NC == 2) operator_launch<n, 2>(a, wgs, lds, st);
+    else operator_launch<n, 1>(a, wgs, lds, st);
+}
+
+}  // namespace
+
+void tail_plan(cbs_system *h, bool kept) {
+    Tail &T = h->tail;
+    const int was = T.level;
+    T.level = tail_level(h);
+    if (T.level < 0 || (kept && T.level == was)) return;
+    T.max_m = 0;
+    const int nsys = h->n_sys, nlev = (int)h->lev.size(), nl = nlev - 1 - T.level;
+    std::vector<TailBlk> blk;
+    std::vector<int64_t> off(nsys + 1, 0);
+    std::vector<int32_t> roff;
+    for (int k = 0; k <= nl; ++k)
+        for (int64_t o : h->lev[T.level + k].sys_off) roff.push_back((int32_t)o);
+    for (int s = 0; s < nsys; ++s) {
+        const int32_t row0 = roff[s], m = (roff[s + 1] - row0) * h->n;
+        for (int32_t o = 0; o < m; o += kTailRowsPerWg) blk.push_back(TailBlk{row0, m, o, 0, off[s]});
+        off[s + 1] = off[s] + m * tail_ld(m);
+        T.max_m = std::max(T.max_m, m);
     }
-    Coarse &C = h->coarse;
-    a.rfine = rfine;
-    a.xout = vp<T>(h->lev[l0].vx);
-    a.cinv = tr ? C.invT.get() : C.inv.get();
-    a.coff = C.off.get();
-    a.cm = C.m.get();
-    a.croff = C.roff.get();
-    a.omega = level_omega(h->opt, l0);             // every tail level is below level 0
+    // columns per workgroup of k_tail_operator: as many as LDS holds, since
+    // they share the reads of the matrix, but no fewer workgroups than half
+    // the chip's CUs
+    std::vector<int32_t> wg(nsys + 1, 0);
+    for (T.ncols = 4;; T.ncols /= 2) {
+        for (int s = 0; s < nsys; ++s) wg[s + 1] = wg[s] + (int32_t)cdiv((int64_t)(roff[s + 1] - roff[s]) * h->n, T.ncols);
+        if (T.ncols == 1 || (wg[nsys] >= 128 && tail_lds(h, T.level, T.ncols) <= tail_lds_budget(h))) break;
+    }
+    T.wgs = wg[nsys];
+    roff.insert(roff.end(), wg.begin(), wg.end());
+    T.nblk = (int32_t)blk.size();
+    T.vals = off[nsys];
+    T.blk.ensure(blk.size());
+    T.off.ensure(off.size());
+    T.roff.ensure(roff.size());
+    hipStream_t st = h->stream;
+    HIPCHK(hipMemcpyAsync(T.blk.get(), blk.data(), sizeof(TailBlk) * blk.size(), hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(T.off.get(), off.data(), sizeof(int64_t) * off.size(), hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(T.roff.get(), roff.data(), sizeof(int32_t) * roff.size(), hipMemcpyHostToDevice, st));
+    HIPCHK(hipStreamSynchronize(st));                // the host arrays end here
+}
+
+void tail_form(cbs_system *h, bool tr) {
+    Tail &T = h->tail;
+    if (T.level < 0) return;
+    const int nlev = (int)h->lev.size(), nl = nlev - 1 - T.level, n = h->n;
+    DArr<double> &op = tr ? T.opT : T.op;
+    op.ensure(T.vals);
+    TailArgs a{};
+    for (int k = 0; k <= nl; ++k) {
+        Level &L = h->lev[T.level + k];
+        TailLvl &d = a.lv[k];
+        const Level &F = h->lev[T.level + k - 1];
+        d.aptr = F.agg_ptr.get();
+        d.amem = F.agg_mem.get();
+        if (k == nl) break;                          // the coarsest needs no more
+        d.val = tr ? L.sell.v64T.get() : L.sell.v64.get();
+        d.Dinv = tr ? L.DinvT.get() : L.Dinv.get();
+        d.soff = L.sell.soff.get();
+        d.sw = L.sell.sw.get();
+        d.scol = L.sell.scol.get();
+        d.lc = L.sell.lc;
+        d.agg = L.agg.get();
+    }
+    a.roff = T.roff.get();
+    a.cinv = tr ? h->coarse.invT.get() : h->coarse.inv.get();
+    a.coff = h->coarse.off.get();
+    a.cm = h->coarse.m.get();
+    a.opoff = T.off.get();
+    a.op = op.get();
+    a.omega = level_omega(h->opt, T.level);          // every tail level is below level 0
     a.nl = nl;
     a.nu1 = std::max(0, h->opt.pre_sweeps);
     a.nu2 = std::max(0, h->opt.post_sweeps);
     a.nsys = h->n_sys;
-    const dim3 g(1), b(kTailThreads);
-    const size_t shm = (size_t)lds;
-    // more than 64 KB of dynamic LDS is requested explicitly
-#define TAIL_N(NN)                                                                                       \
-    {                                                                                                    \
-        if (shm > 64 * 1024)                                                                             \
-            HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tail<NN, T>),                   \
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));           \
-        hipLaunchKernelGGL((k_tail<NN, T>), g, b, shm, h->stream, a);                                    \
-    }
+    a.wgoff = T.roff.get() + (size_t)(nl + 1) * (h->n_sys + 1);
+    const int NC = T.ncols;
+    const unsigned g = (unsigned)T.wgs;
+    const size_t lds = (size_t)tail_lds(h, T.level, NC);
     switch (n) {
+        case 1: operator_nc<1>(NC, a, g, lds, h->stream); break;
+        case 2: operator_nc<2>(NC, a, g, lds, h->stream); break;
+        case 3: operator_nc<3>(NC, a, g, lds, h->stream); break;
+        case 4: operator_nc<4>(NC, a, g, lds, h->stream); break;
+        case 5: operator_nc<5>(NC, a, g, lds, h->stream); break;
+        default: cbs_throw(CBS_ERR_ARG, "bdim must be 1..5");
+    }
+}
+
+template <typename T>
+void launch_tail(cbs_system *h, bool tr, const T *rfine, T *x) {
+    const Tail &Tl = h->tail;
+    if (Tl.level < 1) cbs_throw(CBS_ERR_ARG, "V-cycle tail: bad level");
+    const Level &F = h->lev[Tl.level - 1];
+    const dim3 g(Tl.nblk), b(kTailApplyThreads);
+    const size_t shm = sizeof(double) * (size_t)Tl.max_m;
+#define TAIL_N(NN)                                                                                              \
+    hipLaunchKernelGGL((k_tail_apply<NN, T>), g, b, shm, h->stream, Tl.blk.get(), tr ? Tl.opT.get() : Tl.op.get(), \
+                       F.agg_ptr.get(), F.agg_mem.get(), rfine, x)
+    switch (h->n) {
         case 1: TAIL_N(1); break;
         case 2: TAIL_N(2); break;
         case 3: TAIL_N(3); break;
@@ -500,5 +508,5 @@ void launch_tail(cbs_system *h, bool tr, int l0, const T *rfine) {
 #undef TAIL_N
     LAUNCHCHK();
 }
-template void launch_tail<float>(cbs_system *, bool, int, const float *);
-template void launch_tail<double>(cbs_system *, bool, int, const double *);
+template void launch_tail<float>(cbs_system *, bool, const float *, float *);
+template void launch_tail<double>(cbs_system *, bool, const double *, double *);
