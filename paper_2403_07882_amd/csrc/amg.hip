@@ -734,92 +734,139 @@ __global__ __launch_bounds__(256) void k_coarse_inverse(const int32_t *rp, const
     }
 }
 
-// The same Gauss-Jordan elimination with the augmented matrix [A | I] in LDS
-// (row r at r * W, W = 2m + 1: the odd stride keeps a column's entries in
-// different banks), for systems whose m fits.  One wavefront finds each
-// pivot: the largest |a_rk| over rows r >= k, the first such row on ties
-// (the serial scan's choice; NaN entries below the diagonal are passed over,
-// a NaN diagonal makes the matrix singular).  Columns of A left of the pivot
-// are dead once eliminated and are not updated, so each step is one pass
-// that swaps and scales the pivot row, then one that eliminates the other
-// rows; the inverse is the same as the global-memory kernel's.
-template <int n>
-__global__ __launch_bounds__(256) void k_coarse_inverse_lds(const int32_t *rp, const int32_t *col, const double *val,
-                                                            const int64_t *roff_blk, const int64_t *off,
-                                                            const int32_t *msz, double *inv, double *invT,
-                                                            int32_t *flag) {
+// The same elimination in place and in registers, for systems of up to
+// kInvRegMax unknowns: wavefront w of 16 holds rows w, w + 16, ... (RW of
+// them), lane c of it columns c and c + 64 (CW).  A row's multiplier is then
+// one lane of its own wavefront; only the pivot candidates, the scaled pivot
+// row and the row it changes places with pass through LDS, and a step costs
+// two barriers.  The serial chain of m steps bounds it: m = 80 took 422 us
+// with [A | I] in LDS and three barriers per step, and takes 218 us; m = 64
+// 106 -> 87 us.
+// The pivot is the largest |a_rk| over rows r >= k, the first such row on ties
+// (NaN entries below the diagonal are passed over, a NaN diagonal makes the
+// matrix singular).  In place, column k holds the inverse's column of the row
+// that pivoted; pi undoes the exchanges on the way out.  Every entry goes
+// through the operations that it would in [A | I].
+constexpr int kInvRegMax = 128;
+constexpr int kInvWaves = 16;
+
+__device__ inline double lane_value(double v, int lane) {      // lane: the same in the whole wavefront
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+template <int n, int RW, int CW>
+__global__ __launch_bounds__(64 * kInvWaves) void k_coarse_inverse_reg(const int32_t *rp, const int32_t *col,
+                                                                       const double *val, const int64_t *roff_blk,
+                                                                       const int64_t *off, const int32_t *msz,
+                                                                       double *inv, double *invT, int32_t *flag) {
+    constexpr int nn = n * n, C = 64 * CW;
     extern __shared__ double ci_lds[];
-    const int s = blockIdx.x;
-    const int m = msz[s], W = 2 * m + 1;
-    const int64_t r0 = roff_blk[s];
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    constexpr int nw = 4;                          // wavefronts of the workgroup
-    __shared__ int piv_row;
-    __shared__ double piv_abs, piv_d;
-    for (int e = t; e < m * W; e += blockDim.x) {
-        const int r = e / W, j = e - r * W;
-        ci_lds[e] = (j == m + r) ? 1.0 : 0.0;
-    }
+    __shared__ double prow[C], krow[C], cand_v[kInvWaves], diag_v;
+    __shared__ int cand_r[kInvWaves], pi[C];
+    const int s = blockIdx.x, m = msz[s];
+    const int64_t r0 = roff_blk[s];               // first block row of the system
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    for (int e = t; e < m * m; e += 64 * kInvWaves) ci_lds[e] = 0.0;
+    if (t < m) pi[t] = t;
     __syncthreads();
-    const int nb = m / n;
-    for (int bi = t; bi < nb; bi += blockDim.x) {
-        const int64_t i = r0 + bi;
-        for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-            const int bj = (int)(col[k] - r0);
-            for (int r = 0; r < n; ++r)
-                for (int c = 0; c < n; ++c)
-                    ci_lds[(bi * n + r) * W + bj * n + c] = val[(int64_t)k * n * n + r * n + c];
+    for (int bi = wv; bi < m / n; bi += kInvWaves) {
+        const int32_t k0 = rp[r0 + bi], cnt = (rp[r0 + bi + 1] - k0) * nn;
+        for (int q = lane; q < cnt; q += 64) {
+            const int32_t k = k0 + q / nn;
+            const int e = q % nn;
+            ci_lds[(bi * n + e / n) * m + (int)(col[k] - r0) * n + e % n] = val[(int64_t)k * nn + e];
         }
     }
     __syncthreads();
-    for (int k = 0; k < m; ++k) {
-        if (wv == 0) {
-            double bv = -1.0;
-            int br = m;
-            for (int r = k + lane; r < m; r += 64) {
-                const double v = fabs(ci_lds[r * W + k]);
-                if (v > bv) { bv = v; br = r; }     // NaN is never greater
-            }
+    double a[RW][CW];
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                const double ov = __shfl_xor(bv, o, 64);
-                const int orow = __shfl_xor(br, o, 64);
-                if (ov > bv || (ov == bv && orow < br)) { bv = ov; br = orow; }
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+            const int r = wv + kInvWaves * i, j = lane + 64 * c;
+            a[i][c] = r < m && j < m ? ci_lds[r * m + j] : 0.0;
+        }
+    for (int k = 0; k < m; ++k) {
+        // this wavefront's entries of column k, and its pivot candidate
+        double f[RW];
+        double bv = -1.0;
+        int br = m;
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int r = wv + kInvWaves * i;
+            f[i] = CW == 1 || k < 64 ? lane_value(a[i][0], k & 63) : lane_value(a[i][CW - 1], k & 63);
+            const double v = fabs(f[i]);
+            if (r >= k && r < m && v > bv) { bv = v; br = r; }     // NaN is never greater
+            if (r == k) {
+                if (lane == 0) diag_v = f[i];
+#pragma unroll
+                for (int c = 0; c < CW; ++c) krow[lane + 64 * c] = a[i][c];
             }
-            if (lane == 0) {
-                const double dk = ci_lds[k * W + k];
-                piv_abs = dk != dk ? dk : bv;
-                piv_row = br < m ? br : k;
-                piv_d = ci_lds[(br < m ? br : k) * W + k];
-            }
+        }
+        if (lane == 0) {
+            cand_v[wv] = bv;
+            cand_r[wv] = br;
         }
         __syncthreads();
-        const double pa = piv_abs;
-        if (!(pa > 0.0) || !isfinite(pa)) {        // the same value in every thread
+        bv = cand_v[0];
+        int p = cand_r[0];
+#pragma unroll
+        for (int w = 1; w < kInvWaves; ++w) {
+            const double ov = cand_v[w];
+            const int orow = cand_r[w];
+            if (ov > bv || (ov == bv && orow < p)) { bv = ov; p = orow; }
+        }
+        const double dk = diag_v;
+        if (!(bv > 0.0) || !isfinite(bv) || dk != dk) {            // the same in every thread
             if (t == 0) atomicOr(flag, 32);
             return;
         }
-        const int p = piv_row;
-        const double d = piv_d;
-        for (int j = k + t; j < 2 * m; j += blockDim.x) {
-            const double vp = ci_lds[p * W + j], vk = ci_lds[k * W + j];
-            ci_lds[k * W + j] = vp / d;
-            if (p != k) ci_lds[p * W + j] = vk;
+        p = __builtin_amdgcn_readfirstlane(p);
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+            if (wv + kInvWaves * i == p)                           // the pivot row, scaled
+#pragma unroll
+                for (int c = 0; c < CW; ++c)
+                    prow[lane + 64 * c] = (lane + 64 * c == k ? 1.0 : a[i][c]) / f[i];
+        if (t == 0) {
+            const int q = pi[k];
+            pi[k] = pi[p];
+            pi[p] = q;
         }
         __syncthreads();
-        for (int r = wv; r < m; r += nw) {
-            if (r == k) continue;
-            const double f = ci_lds[r * W + k];
-            for (int j = k + 1 + lane; j < 2 * m; j += 64) ci_lds[r * W + j] -= f * ci_lds[k * W + j];
+        double pr[CW];
+#pragma unroll
+        for (int c = 0; c < CW; ++c) pr[c] = prow[lane + 64 * c];
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int r = wv + kInvWaves * i;
+            if (r == k) {
+#pragma unroll
+                for (int c = 0; c < CW; ++c) a[i][c] = pr[c];
+            } else {
+                if (r == p) {                                      // takes the place of row k (p != k here)
+                    f[i] = krow[k];
+#pragma unroll
+                    for (int c = 0; c < CW; ++c) a[i][c] = krow[lane + 64 * c];
+                }
+#pragma unroll
+                for (int c = 0; c < CW; ++c) a[i][c] = (lane + 64 * c == k ? 0.0 : a[i][c]) - f[i] * pr[c];
+            }
         }
-        __syncthreads();
+        // krow is written again before the next barrier: wait for its reader
+        if (p != k) __syncthreads();
     }
-    for (int e = t; e < m * m; e += blockDim.x) {
-        const int r = e / m, c = e - r * m;
-        const double v = ci_lds[r * W + m + c];
-        inv[off[s] + e] = v;
-        invT[off[s] + (int64_t)c * m + r] = v;
-    }
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+            const int r = wv + kInvWaves * i, j = lane + 64 * c;
+            if (r < m && j < m) {
+                inv[off[s] + (int64_t)r * m + pi[j]] = a[i][c];
+                invT[off[s] + (int64_t)pi[j] * m + r] = a[i][c];
+            }
+        }
 }
 
 // ------------------------------------------------------------------ renumbering
@@ -1304,17 +1351,27 @@ void gather_blocks_n(int64_t nb, const int32_t *sk, const double *in, double *ou
     const int64_t tot = nb * (nn / V);
     if (tot > 0) hipLaunchKernelGGL(k_gather_blocks<n>, dim3(cdiv(tot, 256)), dim3(256), 0, st, nb, sk, in, out);
 }
-// lds > 0: the augmented matrices of every system fit in that much LDS
+// max_m: the largest system's unknowns
 template <int n>
 void coarse_inverse_n(int32_t n_sys, const int32_t *rp, const int32_t *col, const double *val, const int64_t *roffb,
                       const int64_t *off, const int32_t *msz, double *work, double *inv, double *invT, int32_t *flag,
-                      size_t lds, hipStream_t st) {
-    if (lds > 0) {
-        if (lds > 64 * 1024)
-            HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_coarse_inverse_lds<n>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(k_coarse_inverse_lds<n>, dim3(n_sys), dim3(256), lds, st, rp, col, val, roffb, off, msz,
-                           inv, invT, flag);
+                      int32_t max_m, hipStream_t st) {
+    if (max_m <= kInvRegMax) {
+        const size_t lds = sizeof(double) * (size_t)max_m * max_m;
+#define CI_REG(RW, CW)                                                                                              \
+    {                                                                                                               \
+        if (lds + 4096 > 64 * 1024)                                                                                 \
+            HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_coarse_inverse_reg<n, RW, CW>),            \
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));                      \
+        hipLaunchKernelGGL((k_coarse_inverse_reg<n, RW, CW>), dim3(n_sys), dim3(64 * kInvWaves), lds, st, rp, col, \
+                           val, roffb, off, msz, inv, invT, flag);                                                 \
+    }
+        // rows per wavefront and columns per lane that the largest system needs
+        if (max_m <= 32) CI_REG(2, 1)
+        else if (max_m <= 64) CI_REG(4, 1)
+        else if (max_m <= 80) CI_REG(5, 2)
+        else CI_REG(8, 2)
+#undef CI_REG
     } else {
         hipLaunchKernelGGL(k_coarse_inverse<n>, dim3(n_sys), dim3(256), 0, st, rp, col, val, roffb, off, msz, work,
                            inv, invT, flag);
@@ -1972,17 +2029,13 @@ void amg_setup(cbs_system *h) {
     C.invT.ensure(off[h->n_sys] > 0 ? off[h->n_sys] : 1);
     C.off.ensure(h->n_sys + 1); C.m.ensure(h->n_sys); C.roff.ensure(h->n_sys);
     DArr<int64_t> droffb(h->n_sys);
-    // [A | I] of the largest system in LDS (beside the kernel's few static
-    // words), else the elimination runs in global memory
-    const size_t ci_lds = sizeof(double) * (size_t)maxm * (2 * (size_t)maxm + 1);
-    const bool ci_in_lds = maxm > 0 && ci_lds + 1024 <= (size_t)h->lds_max;
-    DArr<double> work(ci_in_lds ? 1 : (off[h->n_sys] > 0 ? off[h->n_sys] : 1));
+    DArr<double> work(maxm <= kInvRegMax ? 1 : off[h->n_sys]);     // the general elimination's
     HIPCHK(hipMemcpyAsync(C.off.get(), off.data(), sizeof(int64_t) * (h->n_sys + 1), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(C.m.get(), msz.data(), sizeof(int32_t) * h->n_sys, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(C.roff.get(), roff.data(), sizeof(int64_t) * h->n_sys, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(droffb.get(), roffb.data(), sizeof(int64_t) * h->n_sys, hipMemcpyHostToDevice, st));
     NSWITCH(n, coarse_inverse_n, h->n_sys, Lc.rp, Lc.col, Lc.v64, droffb.get(), C.off.get(), C.m.get(), work.get(),
-            C.inv.get(), C.invT.get(), deferred, ci_in_lds ? ci_lds : 0, st);
+            C.inv.get(), C.invT.get(), deferred, maxm, st);
     LAUNCHCHK();
     // one read-back of every error the setup kernels recorded
     std::vector<int32_t> ev((size_t)nlev + 1);
