@@ -116,6 +116,20 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
         if (y64) y64[o] = (double)v;
         else y[o] = v;
     };
+    // the row's own b, x and D^{-1} do not wait for the sum: they are loaded
+    // with its first blocks (FP64 sweep of 35,805 rows: 9.6 -> 8.6 us)
+    const int64_t o = (int64_t)i * n + r;
+    constexpr bool SWEEP = MODE == 2 || MODE == 4;
+    TX bo = 0, xo = 0;
+    double di[n];
+    if (act) {
+        if (MODE != 0) bo = b[o];
+        if (SWEEP) {
+            xo = x[o];
+            if constexpr (PRO) xo = xo + pe[(int64_t)pagg[i] * n + r];
+        }
+        if (MODE == 2 || MODE == 3) load_row_nt<n, double, false>(Dinv + (int64_t)i * nn + r * n, di);
+    }
     A acc = 0;
     if (MODE != 3 && act) {
         const int32_t sl = p >> S.lc, ii = p - (sl << S.lc);
@@ -140,51 +154,53 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
                     for (int c = 0; c < n; ++c) acc += (A)bv[u][c] * (A)xv[u][c];
                 }
         }
-        for (; k < w; ++k) {
-            const int64_t e = base + ((int64_t)k << S.lc);
-            const int32_t j = S.scol[e];
-            if (j < 0) continue;
-            TV bv[n];
-            TX xv[n];
-            load_row_nt<n, TV, NT>(val + e * nn + r * n, bv);
-            load_xc<n, TX, PRO>(x, j, pagg, pe, xv);
+        // the last w % U blocks are loaded together too, not one after the
+        // other, each a chain of column and x (FP32 5x5 sweep of 8,000 rows:
+        // 6.3 -> 5.5 us; level 0 of 1M rows, where other wavefronts cover the
+        // wait, 1% faster)
+        if (U > 1 && k < w) {
+            int32_t j[U];
+            TV bv[U][n];
+            TX xv[U][n];
 #pragma unroll
-            for (int c = 0; c < n; ++c) acc += (A)bv[c] * (A)xv[c];
+            for (int u = 0; u < U - 1; ++u) j[u] = k + u < w ? S.scol[base + ((k + u) << S.lc)] : -1;
+#pragma unroll
+            for (int u = 0; u < U - 1; ++u) {
+                if (j[u] < 0) continue;
+                const int64_t e = base + ((int64_t)(k + u) << S.lc);
+                load_row_nt<n, TV, NT>(val + e * nn + r * n, bv[u]);
+                load_xc<n, TX, PRO>(x, j[u], pagg, pe, xv[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U - 1; ++u)
+                if (j[u] >= 0) {
+#pragma unroll
+                    for (int c = 0; c < n; ++c) acc += (A)bv[u][c] * (A)xv[u][c];
+                }
         }
     }
-    const int64_t o = (int64_t)i * n + r;
-    auto x_own = [&]() -> A {
-        TX v = x[o];
-        if constexpr (PRO) v = v + pe[(int64_t)pagg[i] * n + r];
-        return (A)v;
-    };
     if (MODE == 0) {
         if (act) y[o] = (TX)acc;
         return;
     }
     A res = 0;
-    if (act) res = (A)b[o] - acc;
+    if (act) res = (A)bo - acc;
     if (MODE == 1) {
         if (act) y[o] = (TX)res;
         return;
     }
     if (MODE == 4) {
-        if (act) {
-            const A xo = x_own();
-            put(o, (TX)(xo + (A)omega * (res - xo)));
-        }
+        if (act) put(o, (TX)((A)xo + (A)omega * (res - (A)xo)));
         return;
     }
     __shared__ A sres[64 * n];
     sres[t] = res;
     __syncthreads();
     if (act) {
-        const double *Di = Dinv + (int64_t)i * nn + r * n;
         double z = 0.0;
 #pragma unroll
-        for (int c = 0; c < n; ++c) z += Di[c] * (double)sres[lr * n + c];
-        const A xi = (MODE == 2) ? x_own() : (A)0;
-        put(o, (TX)(xi + (A)(omega * z)));
+        for (int c = 0; c < n; ++c) z += di[c] * (double)sres[lr * n + c];
+        put(o, (TX)((A)xo + (A)(omega * z)));
         if (MODE == 3 && aux) aux[o] = (TX)z;
     }
 }
@@ -193,7 +209,9 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
 // dependent loads (column, then x) along a row, not bandwidth, sets the time.
 // Here SP threads share each scalar row: thread kk takes blocks kk, kk + SP,
 // ...; the SP partial sums meet in LDS and are added in kk order.  A
-// workgroup covers 64 / SP block rows.
+// workgroup covers 64 / SP block rows.  U of a thread's blocks are in flight
+// at a time: one after the other, the sweeps of levels of 12,000 and 2,700
+// rows (SP = 2 and 4, FP32 4x4) took 7.3 and 5.8 us, now 5.3 and 3.9 us.
 template <int n, typename TV, typename TX, int MODE, int SP, bool PRO>
 __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__restrict__ val,
                                                        const TX *__restrict__ x, const TX *__restrict__ b,
@@ -202,7 +220,7 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
                                                        const int32_t *__restrict__ pagg,
                                                        const TX *__restrict__ pe, double *__restrict__ y64) {
     using A = typename Acc<TX>::type;
-    constexpr int nn = n * n, R = 64 / SP;
+    constexpr int nn = n * n, R = 64 / SP, U = 4;
     auto put = [&](int64_t o, TX v) {
         if (y64) y64[o] = (double)v;
         else y[o] = v;
@@ -213,32 +231,46 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
     const int32_t p = blockIdx.x * R + lr;
     const int32_t i = (S.prow && p < S.N) ? S.prow[p] : p;
     const bool act = p < S.N && i >= 0;
+    // own b and x: with the first blocks, as in k_rows (D^{-1}, which only one
+    // thread of SP needs, after the sum: 0.4 us less at SP = 2)
+    const int64_t o = (int64_t)i * n + r;
+    constexpr bool SWEEP = MODE == 2 || MODE == 4;
+    TX bo = 0, xo = 0;
+    int32_t ai = 0;
+    if (act && kk == 0) {
+        if (MODE != 0) bo = b[o];
+        if (SWEEP) xo = x[o];
+        if (PRO) ai = pagg[i];
+    }
     A acc = 0;
     if (act) {
         const int32_t sl = p >> S.lc, ii = p - (sl << S.lc);
         const int32_t base = S.soff[sl] + ii, w = S.sw[sl];
-        for (int32_t k = kk; k < w; k += SP) {
-            const int64_t e = base + ((int64_t)k << S.lc);
-            const int32_t j = S.scol[e];
-            if (j < 0) continue;
-            TV bv[n];
-            TX xv[n];
-            load_row_nt<n, TV, false>(val + e * nn + r * n, bv);
-            load_xc<n, TX, PRO>(x, j, pagg, pe, xv);
+        for (int32_t k = kk; k < w; k += SP * U) {
+            int32_t j[U];
+            TV bv[U][n];
+            TX xv[U][n];
 #pragma unroll
-            for (int c = 0; c < n; ++c) acc += (A)bv[c] * (A)xv[c];
+            for (int u = 0; u < U; ++u) j[u] = k + u * SP < w ? S.scol[base + ((k + u * SP) << S.lc)] : -1;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (j[u] < 0) continue;
+                const int64_t e = base + ((int64_t)(k + u * SP) << S.lc);
+                load_row_nt<n, TV, false>(val + e * nn + r * n, bv[u]);
+                load_xc<n, TX, PRO>(x, j[u], pagg, pe, xv[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (j[u] >= 0) {
+#pragma unroll
+                    for (int c = 0; c < n; ++c) acc += (A)bv[u][c] * (A)xv[u][c];
+                }
         }
     }
-    auto x_own = [&](int64_t o) -> A {
-        TX v = x[o];
-        if constexpr (PRO) v = v + pe[(int64_t)pagg[i] * n + r];
-        return (A)v;
-    };
     __shared__ A spart[64 * n];
     __shared__ A sres[R * n];
     spart[t] = acc;
     __syncthreads();
-    const int64_t o = (int64_t)i * n + r;
     if (kk == 0) {
         A sum = 0;
 #pragma unroll
@@ -246,14 +278,12 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
         if (MODE == 0) {
             if (act) y[o] = (TX)sum;
         } else {
-            const A res = act ? (A)b[o] - sum : (A)0;
+            if (PRO && act) xo = xo + pe[(int64_t)ai * n + r];
+            const A res = act ? (A)bo - sum : (A)0;
             if (MODE == 1) {
                 if (act) y[o] = (TX)res;
             } else if (MODE == 4) {
-                if (act) {
-                    const A xo = x_own(o);
-                    put(o, (TX)(xo + (A)omega * (res - xo)));
-                }
+                if (act) put(o, (TX)((A)xo + (A)omega * (res - (A)xo)));
             } else {
                 sres[lr * n + r] = res;
             }
@@ -266,7 +296,7 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
         double z = 0.0;
 #pragma unroll
         for (int c = 0; c < n; ++c) z += Di[c] * (double)sres[lr * n + c];
-        put(o, (TX)(x_own(o) + (A)(omega * z)));
+        put(o, (TX)((A)xo + (A)(omega * z)));
     }
 }
 
@@ -1014,9 +1044,22 @@ __global__ __launch_bounds__(64 * n) void k_restrict_sweep0(int32_t nc, const in
     const int t = threadIdx.x;
     const int lr = t / n, q = t - lr * n;
     const int32_t I = blockIdx.x * 64 + lr;
+    // D^{-1} with the members, which are summed in order, four in flight
+    constexpr int U = 4;
+    double di[n];
     A s = 0;
-    if (I < nc)
-        for (int32_t m = aptr[I]; m < aptr[I + 1]; ++m) s += (A)r[(int64_t)amem[m] * n + q];
+    if (I < nc) {
+        const int32_t m0 = aptr[I], m1 = aptr[I + 1];
+        load_row_nt<n, double, false>(Dinv + (int64_t)I * nn + q * n, di);
+        for (int32_t m = m0; m < m1; m += U) {
+            TX v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = r[(int64_t)amem[min(m + u, m1 - 1)] * n + q];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (m + u < m1) s += (A)v[u];
+        }
+    }
     const TX bv = (TX)s;
     const int64_t o = (int64_t)I * n + q;
     if (I < nc) b[o] = bv;
@@ -1024,10 +1067,9 @@ __global__ __launch_bounds__(64 * n) void k_restrict_sweep0(int32_t nc, const in
     sb[t] = (A)bv;
     __syncthreads();
     if (I < nc) {
-        const double *Di = Dinv + (int64_t)I * nn + q * n;
         double z = 0.0;
 #pragma unroll
-        for (int k = 0; k < n; ++k) z += Di[k] * (double)sb[lr * n + k];
+        for (int k = 0; k < n; ++k) z += di[k] * (double)sb[lr * n + k];
         x[o] = (TX)((A)0 + (A)(omega * z));
         if (c) c[o] = (TX)z;
     }
