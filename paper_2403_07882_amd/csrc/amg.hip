@@ -2221,34 +2221,55 @@ void permute_vec(cbs_system *h, const double *in, double *out, bool to_internal)
     LAUNCHCHK();
 }
 
-// cbs_spmv: caller-numbered A or A^T (sliced copy built on first use)
+// Products with the same values before cbs_spmv makes the sliced copy.  At
+// 389,000 cells 5x5 the copy costs 275 us (A^T: 550 us) and saves 16 us of a
+// 140 us product (A^T: 22 of 147 us, 47 of 188 us renumbered), so it pays
+// after some 17 products (A^T 12 to 25).  4x4 blocks are whole cache lines and
+// the block-CSR product is as fast as the sliced one (1M cells: 185 and 187
+// us; renumbered at random 254 and 249 us), so A keeps none there, except
+// below the rows from which the sliced product stops splitting its rows (at
+// some 10,000 rows 9.7 us against 12.6 us).
+constexpr int32_t kUserCopyAfter = 16;
+
+// cbs_spmv: caller-numbered A or A^T.  Options that name a kernel of the
+// sliced copy (schedule, row_split) use it from the first product on.
 void spmv_user(cbs_system *h, const double *x, double *y, bool transposed) {
     Sell &U = h->usell;
     const int n = h->n;
-    const size_t tot = 0;
-    (void)tot;
+    DArr<double> &copy = transposed ? U.v64T : U.v64;
+    int32_t &products = h->user_products[transposed ? 1 : 0];
+    if (!copy.get() && h->opt.schedule <= 0 && h->opt.row_split <= 0 &&
+        (products < kUserCopyAfter || (n == 4 && !transposed && h->N >= kSplitLevelRows))) {
+        products = std::min(products + 1, kUserCopyAfter);
+        launch_bcsr(n, h->N, h->rp.get(), h->col.get(), transposed ? h->mirror.get() : nullptr, h->vals.get(), x, y,
+                    h->stream);
+        return;
+    }
     if (!U.soff.get()) sell_build(h->N, h->rp.get(), h->col.get(), U, h->stream);
     const bool tune = !U.v64.get() && !U.v64T.get();
     const size_t nv = (size_t)U.nent * n * n;
-    if (!transposed) {
-        if (!U.v64.get()) {
-            U.v64.alloc(nv > 0 ? nv : 1);
-            sell_fill(n, U, h->vals.get(), U.v64.get(), h->stream);
+    if (!copy.get()) {
+        const double *vals = h->vals.get();
+        if (transposed) {
+            h->valsT.alloc((size_t)h->nnzb * n * n);
+            NSWITCH(n, transpose_n, h->nnzb, h->mirror.get(), h->vals.get(), h->valsT.get(), h->stream);
+            LAUNCHCHK();
+            vals = h->valsT.get();
         }
-        if (tune) {
-            U.sched64 = choose_sched(n, U, false, U.v64.get(), h->opt.schedule, h->stream);
-            U.sched64.split = row_split_for(U, h->nnzb, h->opt.row_split);
-        }
-        launch_rows<double, double>(0, n, U.view(), U.v64.get(), x, nullptr, y, nullptr, 0.0, h->stream);
-        return;
-    }
-    if (!U.v64T.get()) {
-        h->valsT.alloc((size_t)h->nnzb * n * n);
-        NSWITCH(n, transpose_n, h->nnzb, h->mirror.get(), h->vals.get(), h->valsT.get(), h->stream);
-        LAUNCHCHK();
-        U.v64T.alloc(nv > 0 ? nv : 1);
-        sell_fill(n, U, h->valsT.get(), U.v64T.get(), h->stream);
+        copy.alloc(nv > 0 ? nv : 1);
+        sell_fill(n, U, vals, copy.get(), h->stream);
         h->valsT.release();
     }
-    launch_rows<double, double>(0, n, U.view(), U.v64T.get(), x, nullptr, y, nullptr, 0.0, h->stream);
+    if (tune) {
+        U.sched64 = choose_sched(n, U, false, copy.get(), h->opt.schedule, h->stream);
+        U.sched64.split = row_split_for(U, h->nnzb, h->opt.row_split);
+    }
+    launch_rows<double, double>(0, n, U.view(), copy.get(), x, nullptr, y, nullptr, 0.0, h->stream);
+}
+
+void spmv_user_reset(cbs_system *h) {
+    h->valsT.release();
+    h->usell.v64.release();
+    h->usell.v64T.release();
+    h->user_products[0] = h->user_products[1] = 0;
 }

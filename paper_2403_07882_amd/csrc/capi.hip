@@ -318,9 +318,7 @@ int cbs_update_values(cbs_handle h, const double *diag, const double *upper, con
         h->t_convert_ms = elapsed_ms(h->ev0, h->ev1);
         h->values_changed = true;
         h->transposed_ready = false;
-        h->valsT.release();
-        h->usell.v64.release();
-        h->usell.v64T.release();
+        spmv_user_reset(h);
         invalidate_graphs(h);
         return CBS_OK;
     });
@@ -340,9 +338,7 @@ int cbs_assemble_luo(cbs_handle h, const double *Q, const double *Sf, const doub
         h->t_convert_ms = elapsed_ms(h->ev0, h->ev1);
         h->values_changed = true;
         h->transposed_ready = false;
-        h->valsT.release();
-        h->usell.v64.release();
-        h->usell.v64T.release();
+        spmv_user_reset(h);
         invalidate_graphs(h);
         return CBS_OK;
     });
@@ -362,9 +358,7 @@ int cbs_assemble_luo_noalloc(cbs_handle h, const double *Q, const double *Sf, co
         h->t_convert_ms = elapsed_ms(h->ev0, h->ev1);
         h->values_changed = true;
         h->transposed_ready = false;
-        h->valsT.release();
-        h->usell.v64.release();
-        h->usell.v64T.release();
+        spmv_user_reset(h);
         invalidate_graphs(h);
         return CBS_OK;
     });
@@ -384,9 +378,7 @@ int cbs_assemble_pu(cbs_handle h, const double *Sf, const double *fx, const doub
         h->t_convert_ms = elapsed_ms(h->ev0, h->ev1);
         h->values_changed = true;
         h->transposed_ready = false;
-        h->valsT.release();
-        h->usell.v64.release();
-        h->usell.v64T.release();
+        spmv_user_reset(h);
         invalidate_graphs(h);
         return CBS_OK;
     });

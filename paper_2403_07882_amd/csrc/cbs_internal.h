@@ -309,6 +309,7 @@ struct cbs_system {
     DArr<int32_t> perm_sk;                       // permuted level-0 slot -> caller-order slot
     DArr<double> valsT;                          // caller-order A^T values (cbs_spmv transpose)
     Sell usell;                                  // caller-order sliced copy (cbs_spmv)
+    int32_t user_products[2] = {0, 0};           // cbs_spmv calls with the present values, A and A^T
     // mixed precision escalated to FP64 (sticky until the next cbs_setup)
     bool precision_fallback = false;
     DArr<double> x0;                             // caller's initial guess, kept for a re-solve
@@ -387,6 +388,9 @@ void launch_cast_sweep0(int n, int32_t N, const double *b64, float *b, const dou
 template <typename TX>
 void launch_restrict_sweep0(int n, int32_t nc, const int32_t *agg_ptr, const int32_t *agg_mem, const TX *r, TX *b,
                             const double *Dinv, double omega, TX *x, TX *c, hipStream_t st);
+// y = A x straight from block CSR, or y = A^T x with the transpose slots
+void launch_bcsr(int n, int32_t N, const int32_t *rp, const int32_t *col, const int32_t *mirror, const double *val,
+                 const double *x, double *y, hipStream_t st);
 // time the schedules of the residual kernel on S (cached per shape)
 Sched autotune_rows(int n, const Sell &S, bool fp32, const void *val, hipStream_t st);
 // the schedule option: 0 = autotune_rows, 1..6 = a forced (unroll, non-temporal) pair
@@ -465,6 +469,8 @@ void level0_values_into(cbs_system *h, double *out);
 void refresh_level0_values(cbs_system *h);
 void permute_vec(cbs_system *h, const double *in, double *out, bool to_internal);
 void spmv_user(cbs_system *h, const double *x, double *y, bool transposed);
+// forget what cbs_spmv keeps of the old values
+void spmv_user_reset(cbs_system *h);
 // block-diagonal inverses of level l; with bad_slot the first singular block
 // row is left there for the caller to check, else it is checked here
 // (dslot: slots of the diagonal blocks in vals, default the level's own)
