@@ -255,9 +255,10 @@ struct Tail {
     int32_t ncols = 1, wgs = 0;          // columns per workgroup that forms the operators, and workgroups
     int64_t vals = 0;                    // values of all operators
     DArr<double> op, opT;
-    DArr<TailBlk> blk;
-    DArr<int64_t> off;                   // first value of each system's operator
-    DArr<int32_t> roff;                  // first row of every system on every tail level, then each
+    DArr<char> plan;                     // holds the next three
+    int64_t *off = nullptr;              // first value of each system's operator
+    TailBlk *blk = nullptr;
+    int32_t *roff = nullptr;             // first row of every system on every tail level, then each
                                          // system's first workgroup of the forming kernel
 };
 

@@ -22,6 +22,7 @@
 #include "cbs_internal.h"
 
 #include <algorithm>
+#include <cstring>
 
 namespace {
 
@@ -430,14 +431,18 @@ void tail_plan(cbs_system *h, bool kept) {
     roff.insert(roff.end(), wg.begin(), wg.end());
     T.nblk = (int32_t)blk.size();
     T.vals = off[nsys];
-    T.blk.ensure(blk.size());
-    T.off.ensure(off.size());
-    T.roff.ensure(roff.size());
-    hipStream_t st = h->stream;
-    HIPCHK(hipMemcpyAsync(T.blk.get(), blk.data(), sizeof(TailBlk) * blk.size(), hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(T.off.get(), off.data(), sizeof(int64_t) * off.size(), hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(T.roff.get(), roff.data(), sizeof(int32_t) * roff.size(), hipMemcpyHostToDevice, st));
-    HIPCHK(hipStreamSynchronize(st));                // the host arrays end here
+    // one array: the operators' offsets, the workgroups of the product, the rows
+    const size_t nb = sizeof(TailBlk) * blk.size(), no = sizeof(int64_t) * off.size(), nr = sizeof(int32_t) * roff.size();
+    std::vector<char> plan(no + nb + nr);
+    memcpy(plan.data(), off.data(), no);
+    memcpy(plan.data() + no, blk.data(), nb);
+    memcpy(plan.data() + no + nb, roff.data(), nr);
+    T.plan.ensure(plan.size());
+    T.off = reinterpret_cast<int64_t *>(T.plan.get());
+    T.blk = reinterpret_cast<TailBlk *>(T.plan.get() + no);
+    T.roff = reinterpret_cast<int32_t *>(T.plan.get() + no + nb);
+    HIPCHK(hipMemcpyAsync(T.plan.get(), plan.data(), plan.size(), hipMemcpyHostToDevice, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));         // the host array ends here
 }
 
 void tail_form(cbs_system *h, bool tr) {
@@ -462,18 +467,18 @@ void tail_form(cbs_system *h, bool tr) {
         d.lc = L.sell.lc;
         d.agg = L.agg.get();
     }
-    a.roff = T.roff.get();
+    a.roff = T.roff;
     a.cinv = tr ? h->coarse.invT.get() : h->coarse.inv.get();
     a.coff = h->coarse.off.get();
     a.cm = h->coarse.m.get();
-    a.opoff = T.off.get();
+    a.opoff = T.off;
     a.op = op.get();
     a.omega = level_omega(h->opt, T.level);          // every tail level is below level 0
     a.nl = nl;
     a.nu1 = std::max(0, h->opt.pre_sweeps);
     a.nu2 = std::max(0, h->opt.post_sweeps);
     a.nsys = h->n_sys;
-    a.wgoff = T.roff.get() + (size_t)(nl + 1) * (h->n_sys + 1);
+    a.wgoff = T.roff + (size_t)(nl + 1) * (h->n_sys + 1);
     const int NC = T.ncols;
     const unsigned g = (unsigned)T.wgs;
     const size_t lds = (size_t)tail_lds(h, T.level, NC);
@@ -495,7 +500,7 @@ void launch_tail(cbs_system *h, bool tr, const T *rfine, T *x) {
     const dim3 g(Tl.nblk), b(kTailApplyThreads);
     const size_t shm = sizeof(double) * (size_t)Tl.max_m;
 #define TAIL_N(NN)                                                                                              \
-    hipLaunchKernelGGL((k_tail_apply<NN, T>), g, b, shm, h->stream, Tl.blk.get(), tr ? Tl.opT.get() : Tl.op.get(), \
+    hipLaunchKernelGGL((k_tail_apply<NN, T>), g, b, shm, h->stream, Tl.blk, tr ? Tl.opT.get() : Tl.op.get(), \
                        F.agg_ptr.get(), F.agg_mem.get(), rfine, x)
     switch (h->n) {
         case 1: TAIL_N(1); break;
