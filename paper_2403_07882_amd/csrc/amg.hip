@@ -24,10 +24,6 @@ void build_row_sys(cbs_system *h, Level &L0);
 
 namespace {
 
-// wavefronts per workgroup of the Galerkin kernel: each takes a coarse row
-// of its own, and one per workgroup keeps the workgroup barriers from
-// making each wait for the slowest row (4 per workgroup was 10-20% slower)
-constexpr int kRapWaves = 1;
 constexpr int kRapCap = 4096;     // largest candidate list a coarse row may gather
 // Coarse rows with at most kRapSmall candidates (pairwise aggregates of short
 // rows) take a thread each instead of a wavefront: kRapSmallTpb threads per
@@ -393,35 +389,37 @@ __global__ void k_rap_maxc(int32_t nc, const int32_t *aptr, const int32_t *amem,
     atomicMax(maxc, c);
 }
 
-// LDS per wavefront: cap entries of column, slot and rank (cap = the
-// level's largest candidate count, rounded up), so light levels keep many
-// wavefronts resident.
+// LDS: four lists of cap entries (cap = the level's largest candidate count,
+// rounded up), so light levels keep many workgroups resident.  A candidate's
+// place in the list ordered by column (candidate order kept within a column)
+// is the number of candidates before it, counted over the whole list four at a
+// time: one pass of independent reads.  (Finding each column's first
+// candidate by a search that stops there, then its rank, then the place in
+// the grouped list were three passes, the first a chain of LDS reads: 8,000
+// cells 5x5 38 us per level, now 19 us; level 0 of 1M cells 4x4 612 us, now
+// 358 us, 3.4 TB/s of its blocks in and out.)
 template <int n, int PASS>
-__global__ __launch_bounds__(64 * kRapWaves) void k_rap(int32_t nc, int32_t cap, const int32_t *__restrict__ aptr,
-                                                        const int32_t *__restrict__ amem,
-                                                        const int32_t *__restrict__ rp,
-                                                        const int32_t *__restrict__ col,
-                                                        const double *__restrict__ val,
-                                                        const int32_t *__restrict__ agg, int32_t *cnt,
-                                                        const int32_t *__restrict__ rpc, int32_t *colc,
-                                                        double *valc, int32_t *flag) {
+__global__ __launch_bounds__(64) void k_rap(int32_t nc, int32_t cap, const int32_t *__restrict__ aptr,
+                                            const int32_t *__restrict__ amem, const int32_t *__restrict__ rp,
+                                            const int32_t *__restrict__ col, const double *__restrict__ val,
+                                            const int32_t *__restrict__ agg, int32_t *cnt,
+                                            const int32_t *__restrict__ rpc, int32_t *colc, double *valc,
+                                            int32_t *flag) {
     constexpr int nn = n * n;
-    constexpr uint32_t kFirst = 0x80000000u;
-    extern __shared__ int32_t rap_lds[];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int32_t *sJw = rap_lds + (size_t)w * 3 * cap;
-    uint32_t *sKw = reinterpret_cast<uint32_t *>(sJw + cap);
-    int32_t *sDw = sJw + 2 * cap;
-    const int32_t I = blockIdx.x * (int32_t)(blockDim.x >> 6) + w;
-    const bool active = I < nc;
+    typedef int32_t i4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) int32_t rap_lds[];
+    // columns and slots in candidate order, then ordered by column
+    int32_t *sJ = rap_lds, *sK = sJ + cap, *oJ = sK + cap, *oK = oJ + cap;
+    const int lane = threadIdx.x;
+    const int32_t I = blockIdx.x;                    // the grid has nc workgroups
     // the candidate list: the blocks of the members' rows, member by member.
     // Up to 64 members: one lane per member reads its row's extent, a scan
     // over the lanes gives each member's offset in the list, and every lane
     // then fills list entries of any member (found by binary search over the
     // offsets), so the dependent loads are not repeated per member.
-    __shared__ int32_t sMo[kRapWaves][65], sMk[kRapWaves][64];
+    __shared__ int32_t sMo[65], sMk[64];
     int32_t c = 0;
-    const int32_t m0 = active ? aptr[I] : 0, nm = active ? aptr[I + 1] - m0 : 0;
+    const int32_t m0 = aptr[I], nm = aptr[I + 1] - m0;
     const bool by_lane = nm <= 64;                   // the same for the whole wavefront
     if (by_lane) {
         int32_t kb = 0, len = 0;
@@ -437,8 +435,8 @@ __global__ __launch_bounds__(64 * kRapWaves) void k_rap(int32_t nc, int32_t cap,
             if (lane >= o) inc += v;
         }
         c = __shfl(inc, 63, 64);
-        if (lane < nm) { sMo[w][lane] = inc - len; sMk[w][lane] = kb; }
-        if (lane == 0) sMo[w][nm] = c;
+        if (lane < nm) { sMo[lane] = inc - len; sMk[lane] = kb; }
+        if (lane == 0) sMo[nm] = c;
     }
     __syncthreads();
     if (by_lane) {
@@ -447,12 +445,12 @@ __global__ __launch_bounds__(64 * kRapWaves) void k_rap(int32_t nc, int32_t cap,
             int32_t lo = 0, hi = nm - 1;             // last member whose offset is <= q
             while (lo < hi) {
                 const int32_t mid = (lo + hi + 1) >> 1;
-                if (sMo[w][mid] <= q) lo = mid;
+                if (sMo[mid] <= q) lo = mid;
                 else hi = mid - 1;
             }
-            const int32_t k = sMk[w][lo] + (q - sMo[w][lo]);
-            sJw[q] = agg[col[k]];
-            sKw[q] = (uint32_t)k;
+            const int32_t k = sMk[lo] + (q - sMo[lo]);
+            sJ[q] = agg[col[k]];
+            sK[q] = k;
         }
     } else {
         for (int32_t m = m0; m < m0 + nm; ++m) {
@@ -460,97 +458,74 @@ __global__ __launch_bounds__(64 * kRapWaves) void k_rap(int32_t nc, int32_t cap,
             const int32_t kb = rp[i], len = rp[i + 1] - kb;
             for (int32_t e = lane; e < len; e += 64) {
                 const int32_t q = c + e;
-                if (q < cap) { sJw[q] = agg[col[kb + e]]; sKw[q] = (uint32_t)(kb + e); }
+                if (q < cap) { sJ[q] = agg[col[kb + e]]; sK[q] = kb + e; }
             }
             c += len;
         }
     }
-    if (active && c > cap && lane == 0) atomicOr(flag, 8);
-    __syncthreads();
-    const int32_t cc = active ? min(c, cap) : 0;
-    for (int32_t q = lane; q < cc; q += 64) {
-        const int32_t J = sJw[q];
-        bool f = true;
-        for (int32_t p = 0; p < q; ++p)
-            if (sJw[p] == J) { f = false; break; }
-        if (f) sKw[q] |= kFirst;
-    }
+    if (c > cap && lane == 0) atomicOr(flag, 8);
+    const int32_t cc = min(c, cap), c4 = (cc + 3) & ~3;          // (cap is a multiple of 4)
+    if (cc + lane < c4) sJ[cc + lane] = INT32_MAX;               // after every column
     __syncthreads();
     if (PASS == 0) {
         int32_t d = 0;
-        for (int32_t q = lane; q < cc; q += 64) d += (sKw[q] & kFirst) ? 1 : 0;
+        for (int32_t q = lane; q < cc; q += 64) {
+            const int32_t J = sJ[q];
+            int32_t same = 0;                        // earlier candidates of the same column
+            for (int32_t p = 0; p < q; p += 4) {
+                const i4 v = *reinterpret_cast<const i4 *>(sJ + p);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) same += v[u] == J && p + u < q ? 1 : 0;
+            }
+            d += same == 0 ? 1 : 0;
+        }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) d += __shfl_xor(d, o, 64);
-        if (active && lane == 0) cnt[I] = d;
+        if (lane == 0) cnt[I] = d;
         return;
     }
-    const int32_t base = active ? rpc[I] : 0;
+    const int32_t base = rpc[I];
     for (int32_t q = lane; q < cc; q += 64) {
-        const int32_t J = sJw[q];
-        int32_t d = 0;
-        for (int32_t p = 0; p < cc; ++p) d += ((sKw[p] & kFirst) && sJw[p] < J) ? 1 : 0;
-        sDw[q] = d;
-        if (sKw[q] & kFirst) colc[base + d] = J;
-    }
-    __syncthreads();
-    // Candidates regrouped by output block, candidate order kept within a
-    // group: slot of q = (candidates of lower blocks) + (earlier candidates
-    // of its own block).  sJw (columns, no longer needed) takes the list.
-    for (int32_t q = lane; q < cc; q += 64) {
-        const int32_t d = sDw[q];
+        const int32_t J = sJ[q];
         int32_t pos = 0;
-        for (int32_t p = 0; p < cc; ++p) {
-            const int32_t dp = sDw[p];
-            pos += (dp < d || (dp == d && p < q)) ? 1 : 0;
+        for (int32_t p = 0; p < c4; p += 4) {
+            const i4 v = *reinterpret_cast<const i4 *>(sJ + p);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) pos += v[u] < J || (v[u] == J && p + u < q) ? 1 : 0;
         }
-        sJw[pos] = q;
+        oJ[pos] = J;
+        oK[pos] = sK[q];
     }
     __syncthreads();
-    // where each output block's group starts in the list (up to 64 blocks;
-    // sMo is free again), else found by binary search per output value
-    const int32_t nd = active ? rpc[I + 1] - base : 0;
-    const bool starts = nd <= 64;                    // the same for the whole wavefront
-    if (starts) {
-        for (int32_t q = lane; q < cc; q += 64) {
-            const int32_t dq = sDw[sJw[q]];
-            if (q == 0 || sDw[sJw[q - 1]] != dq) sMo[w][dq] = q;
+    // distinct columns in order: where each one's group starts (sJ, free now)
+    int32_t nd = 0;
+    for (int32_t q0 = 0; q0 < cc; q0 += 64) {
+        const int32_t q = q0 + lane;
+        const bool first = q < cc && (q == 0 || oJ[q] != oJ[q - 1]);
+        const uint64_t mask = __ballot(first);
+        if (first) {
+            const int32_t d = nd + (int32_t)__popcll(mask & ((1ull << lane) - 1));
+            sJ[d] = q;
+            colc[base + d] = oJ[q];
         }
-        if (lane == 0) sMo[w][nd] = cc;
+        nd += (int32_t)__popcll(mask);
     }
+    if (lane == 0) sJ[nd] = cc;                      // (nd = cap: the first slot, no longer needed)
     __syncthreads();
-    if (!active) return;
+    // each output value: its group's values, four loads in flight, added in
+    // candidate order
     for (int32_t t = lane; t < nd * nn; t += 64) {
         const int32_t d = t / nn, e = t - d * nn;
-        // the group of block d is [lo, end) of the list (ordered by block);
-        // its values are loaded four at a time and added in candidate order
-        int32_t lo, end;
-        if (starts) {
-            lo = sMo[w][d];
-            end = sMo[w][d + 1];
-        } else {
-            int32_t hi = cc;
-            lo = 0;
-            while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (sDw[sJw[mid]] < d) lo = mid + 1;
-                else hi = mid;
-            }
-            end = lo;
-            hi = cc;
-            while (end < hi) {
-                const int32_t mid = (end + hi) >> 1;
-                if (sDw[sJw[mid]] <= d) end = mid + 1;
-                else hi = mid;
-            }
-        }
-        auto src = [&](int32_t g) { return val[(int64_t)(sKw[sJw[g]] & ~kFirst) * nn + e]; };
+        const int32_t lo = sJ[d], end = sJ[d + 1];
         double acc = 0.0;
-        int32_t g = lo;
-        for (; g + 4 <= end; g += 4) {
-            const double v0 = src(g), v1 = src(g + 1), v2 = src(g + 2), v3 = src(g + 3);
-            acc += v0; acc += v1; acc += v2; acc += v3;
+        for (int32_t g = lo; g < end; g += 4) {
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = val[(int64_t)oK[min(g + u, end - 1)] * nn + e];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (g + u < end) acc += v[u];
         }
-        for (; g < end; ++g) acc += src(g);
         valc[(int64_t)(base + d) * nn + e] = acc;
     }
 }
@@ -1319,10 +1294,15 @@ template <int n>
 void rap_n(int pass, int32_t nc, int32_t cap, const int32_t *aptr, const int32_t *amem, const int32_t *rp,
            const int32_t *col, const double *val, const int32_t *agg, int32_t *cnt, const int32_t *rpc, int32_t *colc,
            double *valc, int32_t *flag, hipStream_t st) {
-    // at most 48 KB of LDS per workgroup: fewer wavefronts for long lists
-    const int waves = std::max(1, std::min(kRapWaves, (int)(49152 / (12 * (size_t)cap))));
-    const dim3 g(cdiv(nc, waves)), b(64 * waves);
-    const size_t lds = sizeof(int32_t) * 3 * (size_t)cap * waves;
+    const size_t lds = sizeof(int32_t) * 4 * (size_t)cap;
+    const dim3 g(nc), b(64);
+    if (lds > 48 * 1024) {
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rap<n, 0>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rap<n, 1>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    }
+    if (nc <= 0) return;
     if (pass == 0)
         hipLaunchKernelGGL((k_rap<n, 0>), g, b, lds, st, nc, cap, aptr, amem, rp, col, val, agg, cnt, rpc, colc, valc,
                            flag);
