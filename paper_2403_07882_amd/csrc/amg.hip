@@ -214,13 +214,6 @@ __global__ void k_diag_norm(int32_t N, const int32_t *dslot, const double *nrm, 
     if (i < N) df[i] = nrm[dslot[i]];
 }
 
-__global__ void k_zero_diag_w(int32_t N, const int32_t *rp, const int32_t *col, double *w) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    for (int32_t k = rp[i]; k < rp[i + 1]; ++k)
-        if (col[k] == i) w[k] = 0.0;
-}
-
 // ------------------------------------------------------------------ matching
 // partner: -1 unmatched, -2 excluded (frozen system), >= 0 matched partner
 __global__ void k_match_init(int32_t N, const int32_t *row_sys, const int32_t *sys_frozen, int32_t *partner) {
@@ -373,13 +366,12 @@ __global__ void k_sort_members(int32_t nc, const int32_t *aptr, int32_t *mem) {
 // ------------------------------------------------------------------ Galerkin RAP
 // pass 0: cnt[I] = number of distinct coarse columns of coarse row I
 // pass 1: colc / valc of coarse row I at rpc[I] (columns ascending)
-// One wavefront per coarse row: the candidate blocks (coarse column J of
-// every block of every member row) are gathered into LDS, duplicates are
-// marked (top bit of the slot), every candidate learns the rank d of its
-// column among the distinct ones, and the n*n sums of each distinct column
-// are spread over the lanes (coalesced block reads).  Each sum runs over
-// the candidates in gather order: members ascending, then row slots, the
-// order of the CPU reference.
+// One wavefront per coarse row (and workgroup, so that no row waits for
+// another's): the candidate blocks (coarse column J of every block of every
+// member row) are gathered into LDS and ordered by column, and the n*n sums
+// of each distinct column are spread over the lanes (coalesced block reads).
+// Each sum runs over the candidates in gather order: members ascending, then
+// row slots, the order of the CPU reference.
 // Candidate count of a coarse row: the blocks of all its member rows.
 __global__ void k_rap_maxc(int32_t nc, const int32_t *aptr, const int32_t *amem, const int32_t *rp, int32_t *maxc) {
     const int32_t I = blockIdx.x * blockDim.x + threadIdx.x;
@@ -855,22 +847,24 @@ __global__ void k_pos_counts(int32_t nc, const int32_t *aptr, const int32_t *pos
     if (I < nc) cnt[pos_c[I]] = aptr[I + 1] - aptr[I];
 }
 
+// ... and everything else that only moves with the rows: each position's row,
+// its length, aggregate, member list entry and system (one thread per
+// aggregate, whose rows are a short run)
 __global__ void k_pos_assign(int32_t nc, const int32_t *aptr, const int32_t *amem, const int32_t *pos_c,
-                             const int32_t *start, int32_t *pos_f) {
+                             const int32_t *start, const int32_t *rp, const int32_t *row_sys, PosArrays out) {
     const int32_t I = blockIdx.x * blockDim.x + threadIdx.x;
     if (I >= nc) return;
-    const int32_t s0 = start[pos_c[I]];
-    for (int32_t q = aptr[I]; q < aptr[I + 1]; ++q) pos_f[amem[q]] = s0 + (q - aptr[I]);
-}
-
-__global__ void k_invert(int32_t N, const int32_t *pos, int32_t *ip) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < N) ip[pos[i]] = i;
-}
-
-__global__ void k_perm_len(int32_t N, const int32_t *ip, const int32_t *rp, int32_t *len) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < N) len[i] = rp[ip[i] + 1] - rp[ip[i]];
+    const int32_t pc = pos_c[I];
+    int32_t p = start[pc];
+    for (int32_t q = aptr[I]; q < aptr[I + 1]; ++q, ++p) {
+        const int32_t i = amem[q];
+        out.pos[i] = p;
+        out.ip[p] = i;
+        out.rp[p] = rp[i + 1] - rp[i];
+        out.agg[p] = pc;
+        out.mem[p] = p;
+        out.row_sys[p] = row_sys[i];
+    }
 }
 
 // new row i' = old row ip[i'], columns renamed by pos and sorted; sk = old slot
@@ -942,14 +936,6 @@ __global__ void k_compose_slots(int64_t m, const int32_t *sk, int32_t *a) {
     if (e >= m) return;
     const int32_t v = a[e];
     if (v >= 0) a[e] = sk[v];
-}
-
-// out[i'] = map[ip[i']], renamed through pos_c when given
-__global__ void k_perm_map(int32_t N, const int32_t *ip, const int32_t *map, const int32_t *pos_c, int32_t *out) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    const int32_t v = map[ip[i]];
-    out[i] = pos_c ? pos_c[v] : v;
 }
 
 __global__ void k_iota(int32_t N, int32_t *a) {
@@ -1400,12 +1386,17 @@ void match_pass(cbs_system *h, const Graph &g, const int32_t *row_sys, const int
 // count comes back: past the last aggregate every aptr entry holds N.  The
 // largest candidate list of the Galerkin product over the graph rp (the
 // summed row lengths of an aggregate's members) goes to *maxc, which must
-// hold 0.
-void build_members(cbs_system *h, int32_t N, const int32_t *agg, DArr<int32_t> &aptr, DArr<int32_t> &amem,
-                   const int32_t *rp, int32_t *maxc) {
+// hold 0.  a2 (levels of up to kOneWgRows rows only): the map is first
+// composed with it.
+void build_members(cbs_system *h, int32_t N, int32_t *agg, const int32_t *a2, DArr<int32_t> &aptr,
+                   DArr<int32_t> &amem, const int32_t *rp, int32_t *maxc) {
     hipStream_t st = h->stream;
     aptr.alloc(N + 1);
     amem.alloc(N > 0 ? N : 1);
+    if (N <= kOneWgRows) {
+        one_wg_members(N, agg, a2, rp, aptr.get(), amem.get(), maxc, st);
+        return;
+    }
     DArr<int32_t> fill(N + 1), len(N + 1);
     hipLaunchKernelGGL(k_fill_int, dim3(cdiv(N + 1, 256)), dim3(256), 0, st, aptr.get(), (int64_t)N + 1, 0);
     hipLaunchKernelGGL(k_fill_int, dim3(cdiv(N + 1, 256)), dim3(256), 0, st, len.get(), (int64_t)N + 1, 0);
@@ -1549,17 +1540,30 @@ void aggregate_level(cbs_system *h, Level &L, const int32_t *sys_frozen, int32_t
     DArr<int32_t> aptr, amem;                      // members of the last pass's map on the current graph
     int32_t nc = 0, maxc = 0;
     for (int p = 0; p < passes; ++p) {
-        DArr<int32_t> a(p > 0 ? cur_N : 1);
-        int32_t *map = p == 0 ? L.agg.get() : a.get();
-        Graph g{cur_N, cur_rp, cur_col, cur_w, cur_lanes};
-        match_pass(h, g, cur_rowsys, sys_frozen, map, words.get() + 2 * p);
-        if (p > 0) hipLaunchKernelGGL(k_compose, dim3(cdiv(N, 256)), dim3(256), 0, st, N, map, L.agg.get());
-        LAUNCHCHK();
+        const bool more = p + 1 < passes;
+        DArr<int32_t> a(p > 0 ? cur_N : 1), nrs(more ? cur_N : 0);
+        int32_t *map = p == 0 ? L.agg.get() : a.get(), *nc_word = words.get() + 2 * p;
+        const bool one = cur_N <= kOneWgRows;
+        if (one) {
+            one_wg_match(cur_N, kMatchRounds, cur_rp, cur_col, cur_w, cur_rowsys, sys_frozen, map, nc_word, nrs.get(),
+                         st);
+        } else {
+            match_pass(h, Graph{cur_N, cur_rp, cur_col, cur_w, cur_lanes}, cur_rowsys, sys_frozen, map, nc_word);
+            if (more) {
+                hipLaunchKernelGGL(k_inherit_sys, dim3(cdiv(cur_N, 256)), dim3(256), 0, st, cur_N, map, cur_rowsys,
+                                   nrs.get());
+                LAUNCHCHK();
+            }
+        }
         // another pass works on this map's aggregate graph; after the last,
         // the level's Galerkin product on the composed map
-        const bool more = p + 1 < passes;
-        if (more) build_members(h, cur_N, map, aptr, amem, cur_rp, words.get() + 2 * p + 1);
-        else build_members(h, N, L.agg.get(), L.agg_ptr, L.agg_mem, L.rp, words.get() + 2 * p + 1);
+        if (p > 0 && (more || N > kOneWgRows)) {
+            hipLaunchKernelGGL(k_compose, dim3(cdiv(N, 256)), dim3(256), 0, st, N, map, L.agg.get());
+            LAUNCHCHK();
+        }
+        if (more) build_members(h, cur_N, map, nullptr, aptr, amem, cur_rp, words.get() + 2 * p + 1);
+        else build_members(h, N, L.agg.get(), p > 0 && N <= kOneWgRows ? map : nullptr, L.agg_ptr, L.agg_mem, L.rp,
+                           words.get() + 2 * p + 1);
         int32_t v[2];
         read_array(words.get() + 2 * p, 2, v, st);
         nc = v[0];
@@ -1567,22 +1571,18 @@ void aggregate_level(cbs_system *h, Level &L, const int32_t *sys_frozen, int32_t
         gmark(p == 0 ? "match1" : "match2");
         if (!more || nc <= 1) {
             if (more) {                            // stopped early: the level's members after all
-                build_members(h, N, L.agg.get(), L.agg_ptr, L.agg_mem, L.rp, words.get() + 2 * passes);
+                build_members(h, N, L.agg.get(), nullptr, L.agg_ptr, L.agg_mem, L.rp, words.get() + 2 * passes);
                 maxc = -1;                         // found again by the Galerkin product
             }
             break;
         }
-        DArr<int32_t> nrp, ncol, nrs;
+        // (its diagonal weights stay in: the matching passes over the diagonal)
+        DArr<int32_t> nrp, ncol;
         DArr<double> nw;
         const int64_t bound = L.nnzb;
         rap_build(h, 1, nc, aptr.get(), amem.get(), cur_rp, cur_col, cur_w, map, nrp, ncol, nw, true, maxc, bound,
                   deferred);
         gmark("wrap");
-        hipLaunchKernelGGL(k_zero_diag_w, dim3(cdiv(nc, 256)), dim3(256), 0, st, nc, nrp.get(), ncol.get(), nw.get());
-        nrs.alloc(nc);
-        hipLaunchKernelGGL(k_inherit_sys, dim3(cdiv(cur_N, 256)), dim3(256), 0, st, cur_N, map, cur_rowsys,
-                           nrs.get());
-        LAUNCHCHK();
         // the new graph becomes current (about twice the rows' degree)
         grp = std::move(nrp); gcol = std::move(ncol); gw = std::move(nw); cur_rs = std::move(nrs);
         cur_rp = grp.get(); cur_col = gcol.get(); cur_w = gw.get(); cur_rowsys = cur_rs.get();
@@ -1727,7 +1727,7 @@ void blockinv_level(cbs_system *h, int l, const double *vals, double *Dinv, int3
                     const int32_t *dslot) {
     Level &L = h->lev[l];
     int32_t *slot = bad_slot ? bad_slot : h->dflag.get();
-    HIPCHK(hipMemsetAsync(slot, 0x7f, sizeof(int32_t), h->stream));
+    if (!bad_slot) HIPCHK(hipMemsetAsync(slot, 0x7f, sizeof(int32_t), h->stream));
     NSWITCH(h->n, blockinv_n, L.N, dslot ? dslot : L.dslot, vals, Dinv, slot, h->stream);
     LAUNCHCHK();
     if (bad_slot) return;                        // the caller checks later
@@ -1800,7 +1800,7 @@ void amg_setup(cbs_system *h) {
     }
 
     DArr<int32_t> frozen(h->n_sys);
-    std::vector<int32_t> hfrozen(h->n_sys);
+    std::vector<int32_t> hfrozen(h->n_sys), dfrozen;           // (dfrozen: what the device holds)
     int l = 0;
     for (;; ++l) {
         Level &L = h->lev[l];
@@ -1813,7 +1813,12 @@ void amg_setup(cbs_system *h) {
         }
         bool last = all_small || l + 1 >= o.max_levels;
         if (!last && !(reuse && L.agg.get() && (int)h->lev.size() > l + 1)) {
-            HIPCHK(hipMemcpyAsync(frozen.get(), hfrozen.data(), sizeof(int32_t) * h->n_sys, hipMemcpyHostToDevice, st));
+            if (dfrozen != hfrozen) {
+                dfrozen = hfrozen;
+                HIPCHK(hipMemcpyAsync(frozen.get(), dfrozen.data(), sizeof(int32_t) * h->n_sys, hipMemcpyHostToDevice,
+                                      st));
+                HIPCHK(hipStreamSynchronize(st));
+            }
             aggregate_level(h, L, frozen.get(), deferred);
             pt.mark("agg" + std::to_string(l));
             // stall test over the systems still coarsening (frozen rows map 1:1)
@@ -1889,10 +1894,24 @@ void amg_setup(cbs_system *h) {
             if (mixed && o.scaled_sweeps && q + 1 < nlev && !level_uses_dilu(q) && !keep_sod)
                 todo.push_back({&L, &L.sod, true, false});
         }
-        for (auto &t : todo)
-            sell_pattern_begin(t.L->N, t.L->rp, t.L->col, *t.S, st, t.od, t.L == &h->lev[0] ? kSlice : kCoarseSlice,
-                               t.coloured ? t.L->rows_by_colour.get() : nullptr,
-                               t.coloured ? &t.L->colour_off : nullptr);
+        auto slice = [&](const Pending &t) { return t.L == &h->lev[0] ? kSlice : kCoarseSlice; };
+        SellJobs jobs;
+        int njobs = 0;
+        for (auto &t : todo) {
+            if (t.coloured || t.L->N > kOneWgRows || t.L->N < 1) {
+                sell_pattern_begin(t.L->N, t.L->rp, t.L->col, *t.S, st, t.od, slice(t),
+                                   t.coloured ? t.L->rows_by_colour.get() : nullptr,
+                                   t.coloured ? &t.L->colour_off : nullptr);
+                continue;
+            }
+            sell_pattern_shape(t.L->N, *t.S, slice(t));
+            jobs.j[njobs++] = SellJob{t.L->N, t.S->lc, t.od ? 1 : 0, t.L->rp, t.L->col, t.S->sw.get(), t.S->soff.get()};
+            if (njobs == kSellJobs) {
+                one_wg_sell_widths(jobs, njobs, st);
+                njobs = 0;
+            }
+        }
+        one_wg_sell_widths(jobs, njobs, st);
         for (size_t k0 = 0; k0 < todo.size(); k0 += kPinnedWords) {
             const size_t k1 = std::min(todo.size(), k0 + kPinnedWords);
             int32_t cnt[kPinnedWords];
@@ -2106,19 +2125,27 @@ void renumber_hierarchy(cbs_system *h, int32_t *deferred, bool lazy0) {
         pos[nlev - 1].alloc(C.N);
         hipLaunchKernelGGL(k_iota, dim3(cdiv(C.N, 256)), dim3(256), 0, st, C.N, pos[nlev - 1].get());
     }
-    std::vector<DArr<int32_t>> new_aptr(nlev);
+    // top-down: positions, and with them everything that moves with the rows
+    std::vector<DArr<int32_t>> new_aptr(nlev), ips(nlev), rpns(nlev), aggs(nlev), mems(nlev), rss(nlev);
     for (int l = nlev - 2; l >= 0; --l) {
         Level &F = h->lev[l];
-        const int32_t nc = F.nc;
+        const int32_t nc = F.nc, N = F.N;
         new_aptr[l].alloc(nc + 1);
+        pos[l].alloc(N); ips[l].alloc(N); rpns[l].alloc(N + 1); aggs[l].alloc(N); mems[l].alloc(N); rss[l].alloc(N);
+        const PosArrays out{pos[l].get(), ips[l].get(), rpns[l].get(), aggs[l].get(), mems[l].get(), rss[l].get()};
+        if (N <= kOneWgRows) {
+            one_wg_positions(N, nc, F.agg_ptr.get(), F.agg_mem.get(), pos[l + 1].get(), F.rp, F.row_sys.get(),
+                             new_aptr[l].get(), out, st);
+            continue;
+        }
         hipLaunchKernelGGL(k_pos_counts, dim3(cdiv(nc, 256)), dim3(256), 0, st, nc, F.agg_ptr.get(), pos[l + 1].get(),
                            new_aptr[l].get());
         LAUNCHCHK();
         scan_exclusive(new_aptr[l].get(), new_aptr[l].get(), nc, st);
-        pos[l].alloc(F.N);
         hipLaunchKernelGGL(k_pos_assign, dim3(cdiv(nc, 256)), dim3(256), 0, st, nc, F.agg_ptr.get(), F.agg_mem.get(),
-                           pos[l + 1].get(), new_aptr[l].get(), pos[l].get());
+                           pos[l + 1].get(), new_aptr[l].get(), F.rp, F.row_sys.get(), out);
         LAUNCHCHK();
+        scan_exclusive(rpns[l].get(), rpns[l].get(), N, st);
     }
     gmark("positions");
     for (int l = 0; l + 1 < nlev; ++l) {
@@ -2126,14 +2153,11 @@ void renumber_hierarchy(cbs_system *h, int32_t *deferred, bool lazy0) {
         const int32_t N = L.N;
         const int64_t nnz = L.nnzb;
         const dim3 G(cdiv(N, 256)), B(256);
-        DArr<int32_t> ip(N), rpn(N + 1), coln(nnz), sk(nnz), aggn(N), memn(N), rsn(N), mir(nnz), dsl(N);
+        DArr<int32_t> &ip = ips[l], &rpn = rpns[l];
+        DArr<int32_t> coln(nnz), sk(nnz), mir(nnz), dsl(N);
         if (l == 0) gmark("alloc0");
         const bool lazy = l == 0 && lazy0;
         DArr<double> vn(lazy ? 0 : (size_t)nnz * n * n);
-        hipLaunchKernelGGL(k_invert, G, B, 0, st, N, pos[l].get(), ip.get());
-        hipLaunchKernelGGL(k_perm_len, G, B, 0, st, N, ip.get(), L.rp, rpn.get());
-        LAUNCHCHK();
-        scan_exclusive(rpn.get(), rpn.get(), N, st);
         if (l == 0)        // level 0: short rows (face neighbours)
             hipLaunchKernelGGL(k_perm_rows<16>, G, B, 0, st, N, ip.get(), pos[l].get(), L.rp, L.col, rpn.get(),
                                coln.get(), sk.get());
@@ -2143,9 +2167,6 @@ void renumber_hierarchy(cbs_system *h, int32_t *deferred, bool lazy0) {
         if (!lazy) {
             NSWITCH(n, gather_blocks_n, nnz, sk.get(), L.v64, vn.get(), st);
         }
-        hipLaunchKernelGGL(k_perm_map, G, B, 0, st, N, ip.get(), L.agg.get(), pos[l + 1].get(), aggn.get());
-        hipLaunchKernelGGL(k_iota, G, B, 0, st, N, memn.get());
-        hipLaunchKernelGGL(k_perm_map, G, B, 0, st, N, ip.get(), L.row_sys.get(), nullptr, rsn.get());
         LANES_LAUNCH(k_mirror_search, lanes_for(N, nnz), N, N, rpn.get(), coln.get(), mir.get(), dsl.get(), deferred);
         LAUNCHCHK();
         L.lazy_vals = lazy;
@@ -2160,8 +2181,8 @@ void renumber_hierarchy(cbs_system *h, int32_t *deferred, bool lazy0) {
         L.o_mirror = std::move(mir); L.o_dslot = std::move(dsl);
         L.rp = L.o_rp.get(); L.col = L.o_col.get(); L.v64 = lazy ? nullptr : L.o_v64.get();
         L.mirror = L.o_mirror.get(); L.dslot = L.o_dslot.get();
-        L.agg = std::move(aggn); L.agg_ptr = std::move(new_aptr[l]); L.agg_mem = std::move(memn);
-        L.row_sys = std::move(rsn);
+        L.agg = std::move(aggs[l]); L.agg_ptr = std::move(new_aptr[l]); L.agg_mem = std::move(mems[l]);
+        L.row_sys = std::move(rss[l]);
         L.order = std::move(ip);
         if (l == 0) gmark("perm0");
     }

@@ -410,6 +410,8 @@ void sell_build(int32_t N, const int32_t *rp, const int32_t *col, Sell &S, hipSt
 void sell_pattern_begin(int32_t N, const int32_t *rp, const int32_t *col, Sell &S, hipStream_t st, bool offdiag,
                         int slice = kSlice, const int32_t *rows_by_colour = nullptr,
                         const std::vector<int32_t> *colour_off = nullptr);
+// only the sizes and the arrays for widths and offsets (one_wg_sell_widths fills them)
+void sell_pattern_shape(int32_t N, Sell &S, int slice);
 void sell_pattern_finish(const int32_t *rp, const int32_t *col, Sell &S, int64_t nent, hipStream_t st,
                          bool offdiag);
 // (with out32: also the FP32 rounding of every value, bit 64 of *flag set for
@@ -459,6 +461,34 @@ void launch_dilu_fwd(int n, const SellView &S, const T *val, const T *fval, cons
 template <typename T>
 void launch_dilu_bwd(int n, const SellView &S, const T *val, const int32_t *colour, int c, int32_t p0, int32_t cnt,
                      const double *Einv, T *yz, T *x, bool zero_guess, hipStream_t st);
+
+// Steps of the AMG setup in one workgroup, for levels of up to kOneWgRows
+// block rows (onewg.hip)
+constexpr int32_t kOneWgRows = 2048;
+// a level's arrays in the internal numbering, indexed by position (pos: by the
+// old row): the row held there (ip), row starts, aggregate, members (the
+// identity: an aggregate's rows are contiguous) and system
+struct PosArrays {
+    int32_t *pos, *ip, *rp, *agg, *mem, *row_sys;
+};
+struct SellJob {
+    int32_t N, lc, offdiag;
+    const int32_t *rp, *col;
+    int32_t *sw, *soff;
+};
+constexpr int kSellJobs = 32;
+struct SellJobs {
+    SellJob j[kSellJobs];
+};
+void one_wg_match(int32_t N, int rounds, const int32_t *rp, const int32_t *col, const double *w,
+                  const int32_t *row_sys, const int32_t *sys_frozen, int32_t *agg, int32_t *nc, int32_t *rs_c,
+                  hipStream_t st);
+void one_wg_members(int32_t N, int32_t *agg, const int32_t *a2, const int32_t *rp, int32_t *aptr, int32_t *amem,
+                    int32_t *maxc, hipStream_t st);
+void one_wg_positions(int32_t N, int32_t nc, const int32_t *aptr, const int32_t *amem, const int32_t *pos_c,
+                      const int32_t *rp, const int32_t *row_sys, int32_t *new_aptr, const PosArrays &out,
+                      hipStream_t st);
+void one_wg_sell_widths(const SellJobs &jobs, int count, hipStream_t st);
 
 // AMG setup (amg.hip)
 void amg_setup(cbs_system *h);

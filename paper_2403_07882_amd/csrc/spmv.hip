@@ -623,21 +623,26 @@ __global__ void k_sell_width(int32_t npos, int32_t ns, int32_t C, const int32_t 
     }
 }
 
-__global__ void k_sell_fill_idx(int32_t npos, int32_t C, const int32_t *rp, const int32_t *col, const int32_t *prow,
-                                const int32_t *soff, int32_t *scol, int32_t *ssrc, int offdiag) {
+// one thread per position, the padding past npos in the last slice included:
+// the row's entries, then -1 up to the slice width
+__global__ void k_sell_fill_idx(int32_t npos, int32_t ns, int32_t C, const int32_t *rp, const int32_t *col,
+                                const int32_t *prow, const int32_t *soff, const int32_t *sw, int32_t *scol,
+                                int32_t *ssrc, int offdiag) {
     const int32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= npos) return;
-    const int32_t i = prow ? prow[p] : p;
-    if (i < 0) return;
-    const int32_t sl = p / C, ii = p - sl * C;
+    if (p >= ns * C) return;
+    const int32_t i = p < npos ? (prow ? prow[p] : p) : -1;
+    const int32_t sl = p / C, ii = p - sl * C, w = sw[sl];
+    const int64_t e0 = soff[sl] + (int64_t)ii;
     int32_t q = 0;
-    for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-        if (offdiag && col[k] == i) continue;
-        const int64_t e = soff[sl] + (int64_t)q * C + ii;
-        scol[e] = col[k];
-        ssrc[e] = k;
-        ++q;
-    }
+    if (i >= 0)
+        for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
+            const int32_t j = col[k];
+            if (offdiag && j == i) continue;
+            scol[e0 + (int64_t)q * C] = j;
+            ssrc[e0 + (int64_t)q * C] = k;
+            ++q;
+        }
+    for (; q < w; ++q) scol[e0 + (int64_t)q * C] = ssrc[e0 + (int64_t)q * C] = -1;
 }
 
 __global__ void k_fill_i32(int64_t m, int32_t *a, int32_t v) {
@@ -1014,18 +1019,26 @@ void sell_pattern_begin(int32_t N, const int32_t *rp, const int32_t *col, Sell &
     scan_exclusive(S.soff.get(), S.soff.get(), ns, st);
 }
 
+void sell_pattern_shape(int32_t N, Sell &S, int slice) {
+    S.lc = 0;
+    while ((1 << S.lc) < slice) ++S.lc;
+    S.N = S.npos = N;
+    S.prow.release();
+    S.cpos.clear();
+    S.nslices = (N + slice - 1) / slice;
+    S.sw.alloc(S.nslices);
+    S.soff.alloc(S.nslices + 1);
+}
+
 void sell_pattern_finish(const int32_t *rp, const int32_t *col, Sell &S, int64_t nent, hipStream_t st,
                          bool offdiag) {
     S.nent = nent;
     S.scol.alloc(S.nent > 0 ? S.nent : 1);
     S.ssrc.alloc(S.nent > 0 ? S.nent : 1);
-    if (S.nent > 0) {
-        hipLaunchKernelGGL(k_fill_i32, dim3(cdiv(S.nent, 256)), dim3(256), 0, st, S.nent, S.scol.get(), -1);
-        hipLaunchKernelGGL(k_fill_i32, dim3(cdiv(S.nent, 256)), dim3(256), 0, st, S.nent, S.ssrc.get(), -1);
-    }
-    if (S.npos > 0)
-        hipLaunchKernelGGL(k_sell_fill_idx, dim3(cdiv(S.npos, 256)), dim3(256), 0, st, S.npos, 1 << S.lc, rp, col,
-                           S.prow.get(), S.soff.get(), S.scol.get(), S.ssrc.get(), offdiag ? 1 : 0);
+    if (S.nslices > 0)
+        hipLaunchKernelGGL(k_sell_fill_idx, dim3(cdiv((int64_t)S.nslices << S.lc, 256)), dim3(256), 0, st, S.npos,
+                           S.nslices, 1 << S.lc, rp, col, S.prow.get(), S.soff.get(), S.sw.get(), S.scol.get(),
+                           S.ssrc.get(), offdiag ? 1 : 0);
     LAUNCHCHK();
 }
 
