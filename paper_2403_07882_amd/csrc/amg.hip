@@ -19,6 +19,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 
 void build_row_sys(cbs_system *h, Level &L0);
 
@@ -298,8 +299,6 @@ __global__ void k_match_assign(int32_t N, const int32_t *rep, const int32_t *new
     if (i == 0) *nc = newid[N];
 }
 
-__global__ void k_copy_int(const int32_t *src, int32_t *dst) { *dst = *src; }
-
 __global__ void k_compose(int32_t N, const int32_t *a2, int32_t *agg) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
@@ -351,8 +350,10 @@ __global__ void k_fill_members(int32_t N, const int32_t *agg, int32_t *fill, int
     mem[atomicAdd(&fill[agg[i]], 1)] = i;
 }
 
-__global__ void k_sort_members(int32_t nc, const int32_t *aptr, int32_t *mem) {
+// (and the word found by the kernels before it goes out to the host)
+__global__ void k_sort_members(int32_t nc, const int32_t *aptr, int32_t *mem, const int32_t *word, int32_t *host) {
     const int32_t I = blockIdx.x * blockDim.x + threadIdx.x;
+    if (I == 0) *host = *word;
     if (I >= nc) return;
     const int32_t b = aptr[I], e = aptr[I + 1];
     for (int32_t a = b + 1; a < e; ++a) {
@@ -1385,11 +1386,11 @@ void match_pass(cbs_system *h, const Graph &g, const int32_t *row_sys, const int
 // N aggregates, sized for N so that they are built before the aggregate
 // count comes back: past the last aggregate every aptr entry holds N.  The
 // largest candidate list of the Galerkin product over the graph rp (the
-// summed row lengths of an aggregate's members) goes to *maxc, which must
-// hold 0.  a2 (levels of up to kOneWgRows rows only): the map is first
+// summed row lengths of an aggregate's members) goes to the host word *maxc
+// (word: device scratch).  a2 (levels of up to kOneWgRows rows only): the map is first
 // composed with it.
 void build_members(cbs_system *h, int32_t N, int32_t *agg, const int32_t *a2, DArr<int32_t> &aptr,
-                   DArr<int32_t> &amem, const int32_t *rp, int32_t *maxc) {
+                   DArr<int32_t> &amem, const int32_t *rp, int32_t *word, int32_t *maxc) {
     hipStream_t st = h->stream;
     aptr.alloc(N + 1);
     amem.alloc(N > 0 ? N : 1);
@@ -1400,14 +1401,15 @@ void build_members(cbs_system *h, int32_t N, int32_t *agg, const int32_t *a2, DA
     DArr<int32_t> fill(N + 1), len(N + 1);
     hipLaunchKernelGGL(k_fill_int, dim3(cdiv(N + 1, 256)), dim3(256), 0, st, aptr.get(), (int64_t)N + 1, 0);
     hipLaunchKernelGGL(k_fill_int, dim3(cdiv(N + 1, 256)), dim3(256), 0, st, len.get(), (int64_t)N + 1, 0);
+    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, word, (int64_t)1, 0);
     hipLaunchKernelGGL(k_count_members_len, dim3(cdiv(N, 256)), dim3(256), 0, st, N, agg, rp, aptr.get(), len.get());
     hipLaunchKernelGGL(k_max_into, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(N, 256), 256))), dim3(256), 0, st,
-                       (int64_t)N, len.get(), maxc);
+                       (int64_t)N, len.get(), word);
     LAUNCHCHK();
     scan_exclusive(aptr.get(), aptr.get(), N, st);
     HIPCHK(hipMemcpyAsync(fill.get(), aptr.get(), sizeof(int32_t) * (N + 1), hipMemcpyDeviceToDevice, st));
     hipLaunchKernelGGL(k_fill_members, dim3(cdiv(N, 256)), dim3(256), 0, st, N, agg, fill.get(), amem.get());
-    hipLaunchKernelGGL(k_sort_members, dim3(cdiv(N, 256)), dim3(256), 0, st, N, aptr.get(), amem.get());
+    hipLaunchKernelGGL(k_sort_members, dim3(cdiv(N, 256)), dim3(256), 0, st, N, aptr.get(), amem.get(), word, maxc);
     LAUNCHCHK();
 }
 
@@ -1472,11 +1474,9 @@ int32_t rap_build(cbs_system *h, int n_blk, int32_t nc, const int32_t *aptr, con
         if (late) {
             nz = (int32_t)nz_bound;
         } else {
-            // flag and count side by side: one copy back
-            hipLaunchKernelGGL(k_copy_int, dim3(1), dim3(1), 0, st, rpc.get() + nc, h->dflag.get() + 1);
-            LAUNCHCHK();
             int32_t v[2];
-            read_array(h->dflag.get(), 2, v, st);
+            const int32_t *src[2] = {h->dflag.get(), rpc.get() + nc};
+            read_words(src, 2, v, st);
             if (v[0] & 8) cbs_throw(CBS_ERR_ARG, "coarse row candidate overflow");
             nz = v[1];
         }
@@ -1520,11 +1520,10 @@ void aggregate_level(cbs_system *h, Level &L, const int32_t *sys_frozen, int32_t
     const int n = h->n;
     const int passes = std::max(1, h->opt.match_passes);
     DArr<double> df(N), w(L.nnzb > 0 ? L.nnzb : 1);
-    // device words: [2p] the count of pass p, [2p + 1] the candidate maximum
-    // after it, [2 passes] a spare
-    const int nw_ = 2 * passes + 1;
-    DArr<int32_t> words((size_t)nw_);
-    hipLaunchKernelGGL(k_fill_int, dim3(cdiv(nw_, 64)), dim3(64), 0, st, words.get(), (int64_t)nw_, 0);
+    // host words of the pass: aggregate count, candidate maximum (through
+    // device word 0 on large levels, whose workgroups combine it by atomics)
+    int32_t *hw = pinned_words();
+    DArr<int32_t> words(1);
     NSWITCH(n, strength_n, N, L.rp, L.col, L.mirror, L.dslot, L.v64, L.nnzb, df.get(), w.get(), st);
     LAUNCHCHK();
     gmark("strength");
@@ -1542,13 +1541,13 @@ void aggregate_level(cbs_system *h, Level &L, const int32_t *sys_frozen, int32_t
     for (int p = 0; p < passes; ++p) {
         const bool more = p + 1 < passes;
         DArr<int32_t> a(p > 0 ? cur_N : 1), nrs(more ? cur_N : 0);
-        int32_t *map = p == 0 ? L.agg.get() : a.get(), *nc_word = words.get() + 2 * p;
+        int32_t *map = p == 0 ? L.agg.get() : a.get();
         const bool one = cur_N <= kOneWgRows;
         if (one) {
-            one_wg_match(cur_N, kMatchRounds, cur_rp, cur_col, cur_w, cur_rowsys, sys_frozen, map, nc_word, nrs.get(),
+            one_wg_match(cur_N, kMatchRounds, cur_rp, cur_col, cur_w, cur_rowsys, sys_frozen, map, hw, nrs.get(),
                          st);
         } else {
-            match_pass(h, Graph{cur_N, cur_rp, cur_col, cur_w, cur_lanes}, cur_rowsys, sys_frozen, map, nc_word);
+            match_pass(h, Graph{cur_N, cur_rp, cur_col, cur_w, cur_lanes}, cur_rowsys, sys_frozen, map, hw);
             if (more) {
                 hipLaunchKernelGGL(k_inherit_sys, dim3(cdiv(cur_N, 256)), dim3(256), 0, st, cur_N, map, cur_rowsys,
                                    nrs.get());
@@ -1561,17 +1560,16 @@ void aggregate_level(cbs_system *h, Level &L, const int32_t *sys_frozen, int32_t
             hipLaunchKernelGGL(k_compose, dim3(cdiv(N, 256)), dim3(256), 0, st, N, map, L.agg.get());
             LAUNCHCHK();
         }
-        if (more) build_members(h, cur_N, map, nullptr, aptr, amem, cur_rp, words.get() + 2 * p + 1);
+        if (more) build_members(h, cur_N, map, nullptr, aptr, amem, cur_rp, words.get(), hw + 1);
         else build_members(h, N, L.agg.get(), p > 0 && N <= kOneWgRows ? map : nullptr, L.agg_ptr, L.agg_mem, L.rp,
-                           words.get() + 2 * p + 1);
-        int32_t v[2];
-        read_array(words.get() + 2 * p, 2, v, st);
-        nc = v[0];
-        maxc = v[1];
+                           words.get(), hw + 1);
+        HIPCHK(hipStreamSynchronize(st));
+        nc = hw[0];
+        maxc = hw[1];
         gmark(p == 0 ? "match1" : "match2");
         if (!more || nc <= 1) {
             if (more) {                            // stopped early: the level's members after all
-                build_members(h, N, L.agg.get(), nullptr, L.agg_ptr, L.agg_mem, L.rp, words.get() + 2 * passes);
+                build_members(h, N, L.agg.get(), nullptr, L.agg_ptr, L.agg_mem, L.rp, words.get(), hw + 1);
                 maxc = -1;                         // found again by the Galerkin product
             }
             break;
@@ -1915,14 +1913,9 @@ void amg_setup(cbs_system *h) {
         for (size_t k0 = 0; k0 < todo.size(); k0 += kPinnedWords) {
             const size_t k1 = std::min(todo.size(), k0 + kPinnedWords);
             int32_t cnt[kPinnedWords];
-            int32_t *w = pinned_words();
-            for (size_t k = k0; k < k1; ++k) {   // one synchronisation per 64 patterns
-                const Sell &S = *todo[k].S;
-                HIPCHK(hipMemcpyAsync(w + (k - k0), S.soff.get() + S.nslices, sizeof(int32_t), hipMemcpyDeviceToHost,
-                                      st));
-            }
-            HIPCHK(hipStreamSynchronize(st));
-            for (size_t k = k0; k < k1; ++k) cnt[k - k0] = w[k - k0];
+            const int32_t *src[kPinnedWords];    // one synchronisation per 64 patterns
+            for (size_t k = k0; k < k1; ++k) src[k - k0] = todo[k].S->soff.get() + todo[k].S->nslices;
+            read_words(src, (int)(k1 - k0), cnt, st);
             for (size_t k = k0; k < k1; ++k)
                 sell_pattern_finish(todo[k].L->rp, todo[k].L->col, *todo[k].S, cnt[k - k0], st, todo[k].od);
         }
@@ -1994,15 +1987,6 @@ void amg_setup(cbs_system *h) {
         }
         pt.mark("autotune");
     }
-    if (mixed) {
-        // FP32 level values that overflow (flagged while the FP32 copies and
-        // the row-scaled values were written): escalate the hierarchy to FP64
-        if (read_int(deferred, st) & 64) {
-            h->opt.precision = CBS_PRECISION_FP64;
-            h->precision_fallback = true;
-            for (int q = 0; q < nlev; ++q) alloc_level_vectors(h, h->lev[q], false);
-        }
-    }
     h->op_complexity = (double)nz_sum / (double)h->nnzb;
 
     // coarsest: dense inverse of each system
@@ -2026,20 +2010,34 @@ void amg_setup(cbs_system *h) {
     C.max_m = maxm;
     C.inv.ensure(off[h->n_sys] > 0 ? off[h->n_sys] : 1);
     C.invT.ensure(off[h->n_sys] > 0 ? off[h->n_sys] : 1);
-    C.off.ensure(h->n_sys + 1); C.m.ensure(h->n_sys); C.roff.ensure(h->n_sys);
-    DArr<int64_t> droffb(h->n_sys);
+    // one upload: offsets of the inverses, scalar and block rows, orders
+    const size_t ns = (size_t)h->n_sys, i8 = sizeof(int64_t);
+    std::vector<char> plan(i8 * (3 * ns + 1) + sizeof(int32_t) * ns);
+    memcpy(plan.data(), off.data(), i8 * (ns + 1));
+    memcpy(plan.data() + i8 * (ns + 1), roff.data(), i8 * ns);
+    memcpy(plan.data() + i8 * (2 * ns + 1), roffb.data(), i8 * ns);
+    memcpy(plan.data() + i8 * (3 * ns + 1), msz.data(), sizeof(int32_t) * ns);
+    C.plan.ensure(plan.size());
+    C.off = reinterpret_cast<int64_t *>(C.plan.get());
+    C.roff = C.off + ns + 1;
+    C.roffb = C.roff + ns;
+    C.m = reinterpret_cast<int32_t *>(C.roffb + ns);
     DArr<double> work(maxm <= kInvRegMax ? 1 : off[h->n_sys]);     // the general elimination's
-    HIPCHK(hipMemcpyAsync(C.off.get(), off.data(), sizeof(int64_t) * (h->n_sys + 1), hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(C.m.get(), msz.data(), sizeof(int32_t) * h->n_sys, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(C.roff.get(), roff.data(), sizeof(int64_t) * h->n_sys, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(droffb.get(), roffb.data(), sizeof(int64_t) * h->n_sys, hipMemcpyHostToDevice, st));
-    NSWITCH(n, coarse_inverse_n, h->n_sys, Lc.rp, Lc.col, Lc.v64, droffb.get(), C.off.get(), C.m.get(), work.get(),
+    HIPCHK(hipMemcpyAsync(C.plan.get(), plan.data(), plan.size(), hipMemcpyHostToDevice, st));
+    NSWITCH(n, coarse_inverse_n, h->n_sys, Lc.rp, Lc.col, Lc.v64, C.roffb, C.off, C.m, work.get(),
             C.inv.get(), C.invT.get(), deferred, maxm, st);
     LAUNCHCHK();
     // one read-back of every error the setup kernels recorded
     std::vector<int32_t> ev((size_t)nlev + 1);
     for (int32_t k0 = 0; k0 < nlev + 1; k0 += kPinnedWords)
         read_array(errs.get() + k0, std::min<int32_t>(kPinnedWords, nlev + 1 - k0), ev.data() + k0, st);
+    if (mixed && (ev[0] & 64)) {
+        // FP32 level values that overflow (flagged while the FP32 copies and
+        // the row-scaled values were written): escalate the hierarchy to FP64
+        h->opt.precision = CBS_PRECISION_FP64;
+        h->precision_fallback = true;
+        for (int q = 0; q < nlev; ++q) alloc_level_vectors(h, h->lev[q], false);
+    }
     if (ev[0] & 8) cbs_throw(CBS_ERR_ARG, "aggregate graph row candidate overflow");
     if (ev[0] & 16) cbs_throw(CBS_ERR_PATTERN, "coarse pattern is not symmetric");
     for (int q = 0; q + 1 < nlev; ++q)

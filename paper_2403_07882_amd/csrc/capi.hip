@@ -44,6 +44,22 @@ void require(bool cond, int code, const char *msg) {
     if (!cond) cbs_throw(code, msg);
 }
 
+// run `work` on two zeroed words that its kernels may set, timed into
+// t_convert_ms, and return the words once its stream is done
+template <typename F>
+int32_t *flagged(cbs_system *h, F &&work) {
+    int32_t *w = pinned_words();
+    w[0] = w[1] = 0;
+    HIPCHK(hipEventRecord(h->ev0, h->stream));
+    work(w);
+    HIPCHK(hipEventRecord(h->ev1, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    float ms = 0.f;
+    HIPCHK(hipEventElapsedTime(&ms, h->ev0, h->ev1));
+    h->t_convert_ms = ms;
+    return w;
+}
+
 double elapsed_ms(hipEvent_t a, hipEvent_t b) {
     float ms = 0.f;
     HIPCHK(hipEventSynchronize(b));
@@ -112,14 +128,13 @@ int create_common(cbs_handle *out, int32_t n_sys, const int64_t *cell_off, const
     h->flags.alloc((size_t)5 * n_sys);
     HIPCHK(hipMemsetAsync(h->flags.get(), 0, sizeof(int32_t) * 5 * n_sys, h->stream));
     build_items(h.get());
-    const auto t0 = std::chrono::steady_clock::now();
-    HIPCHK(hipEventRecord(h->ev0, h->stream));
-    globalize_faces(h.get(), la, ua);
-    convert_pattern(h.get());
-    convert_values(h.get(), diag, upper, lower);
-    HIPCHK(hipEventRecord(h->ev1, h->stream));
-    h->t_convert_ms = elapsed_ms(h->ev0, h->ev1);
-    (void)t0;
+    const int32_t *fl = flagged(h.get(), [&](int32_t *w) {
+        globalize_faces(h.get(), la, ua);
+        convert_pattern(h.get());
+        w[0] = w[1] = 0;                             // the pattern's read-backs went through the same words
+        convert_values(h.get(), diag, upper, lower, w);
+    });
+    require(!fl[0], CBS_ERR_NONFINITE, "non-finite matrix coefficient");
     *out = h.release();
     return CBS_OK;
 }
@@ -254,6 +269,8 @@ cbs_system::~cbs_system() {
     if (stream) (void)hipStreamSynchronize(stream);
     else (void)hipDeviceSynchronize();
     invalidate_graphs(this);
+    if (h_state) (void)hipHostFree(h_state);
+    if (h_scal) (void)hipHostFree(h_scal);
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
     if (ev0) (void)hipEventDestroy(ev0);
     if (ev1) (void)hipEventDestroy(ev1);
@@ -312,10 +329,8 @@ int cbs_update_values(cbs_handle h, const double *diag, const double *upper, con
         require(h != nullptr, CBS_ERR_ARG, "handle is NULL");
         set_alloc_handle(h);
         require(diag != nullptr && (h->F == 0 || (upper && lower)), CBS_ERR_ARG, "value arrays are NULL");
-        HIPCHK(hipEventRecord(h->ev0, h->stream));
-        convert_values(h, diag, upper, lower);
-        HIPCHK(hipEventRecord(h->ev1, h->stream));
-        h->t_convert_ms = elapsed_ms(h->ev0, h->ev1);
+        const int32_t *fl = flagged(h, [&](int32_t *w) { convert_values(h, diag, upper, lower, w); });
+        require(!fl[0], CBS_ERR_NONFINITE, "non-finite matrix coefficient");
         h->values_changed = true;
         h->transposed_ready = false;
         spmv_user_reset(h);
@@ -332,10 +347,7 @@ int cbs_assemble_luo(cbs_handle h, const double *Q, const double *Sf, const doub
         require(h->n == 5, CBS_ERR_ARG, "the density-based assembly needs 5 x 5 blocks");
         require(Q != nullptr && (h->F == 0 || Sf != nullptr), CBS_ERR_ARG, "state or face arrays are NULL");
         require(gamma > 1.0, CBS_ERR_ARG, "gamma must exceed 1");
-        HIPCHK(hipEventRecord(h->ev0, h->stream));
-        assemble_luo(h, Q, Sf, lam_visc, v_dt, gamma);
-        HIPCHK(hipEventRecord(h->ev1, h->stream));
-        h->t_convert_ms = elapsed_ms(h->ev0, h->ev1);
+        luo_flag_errors(flagged(h, [&](int32_t *w) { assemble_luo(h, Q, Sf, lam_visc, v_dt, gamma, w); }));
         h->values_changed = true;
         h->transposed_ready = false;
         spmv_user_reset(h);
@@ -372,10 +384,9 @@ int cbs_assemble_pu(cbs_handle h, const double *Sf, const double *fx, const doub
         require(h->n == 4, CBS_ERR_ARG, "the pressure-based assembly needs 4 x 4 blocks");
         require(vol != nullptr && (h->F == 0 || (Sf && fx && d && flux && nu_eff)), CBS_ERR_ARG,
                 "face or cell arrays are NULL");
-        HIPCHK(hipEventRecord(h->ev0, h->stream));
-        assemble_pu(h, Sf, fx, d, flux, nu_eff, vol, uu_add, pp_add);
-        HIPCHK(hipEventRecord(h->ev1, h->stream));
-        h->t_convert_ms = elapsed_ms(h->ev0, h->ev1);
+        const int32_t *fl = flagged(
+            h, [&](int32_t *w) { assemble_pu(h, Sf, fx, d, flux, nu_eff, vol, uu_add, pp_add, w); });
+        require(!fl[0], CBS_ERR_NONFINITE, "non-finite assembled coefficient (zero momentum diagonal or n . d = 0)");
         h->values_changed = true;
         h->transposed_ready = false;
         spmv_user_reset(h);
@@ -435,7 +446,7 @@ int cbs_setup(cbs_handle h, const cbs_options *opt) {
 static int solve_common(cbs_handle h, const double *b, double *x, cbs_stats *st, bool tr) {
     require(h->setup_done && !h->values_changed, CBS_ERR_STATE, "cbs_setup must follow create/update_values");
     const int64_t m = (int64_t)h->N * h->n;
-    check_finite(x, m, h->dflag.get(), h->stream);
+    check_finite(x, b, m, h->stream);
     const bool mixed = h->opt.precision == CBS_PRECISION_MIXED && h->opt.precond == CBS_PREC_AMG;
     if (mixed) {
         h->x0.ensure(m);

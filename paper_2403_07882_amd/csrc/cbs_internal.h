@@ -6,7 +6,6 @@
 #include <stdint.h>
 
 #include <string>
-#include <initializer_list>
 #include <vector>
 
 #include "cbs.h"
@@ -234,9 +233,11 @@ struct Level {
 struct Coarse {
     DArr<double> inv;                    // per-system dense inverses, concatenated
     DArr<double> invT;
-    DArr<int64_t> off;                   // element offset of each system's inverse
-    DArr<int32_t> m;                     // order of each system's matrix (rows * n)
-    DArr<int64_t> roff;                  // scalar-row offset of each system
+    DArr<char> plan;                     // holds the next four
+    int64_t *off = nullptr;              // element offset of each system's inverse
+    int64_t *roff = nullptr;             // scalar-row offset of each system
+    int64_t *roffb = nullptr;            // block-row offset of each system
+    int32_t *m = nullptr;                // order of each system's matrix (rows * n)
     int32_t max_m = 0;
 };
 
@@ -297,9 +298,10 @@ struct cbs_system {
     std::vector<int32_t> items_per_sys_off;      // host: first item of each system
     DArr<int32_t> item_off;                      // device copy of the above
     DArr<int32_t> dflag;                         // error flag scratch for checks
-    // pinned host mirrors for read-back
+    // pinned host mirrors that the scalar kernels write beside the device
+    // arrays: done | flags | iterations per system, and the scalars
+    int32_t *h_state = nullptr;
     double *h_scal = nullptr;
-    int32_t *h_done = nullptr;
     // captured iteration graphs (index: transposed solve), replayed on `stream`
     hipStream_t cap_stream = nullptr;
     // captured BiCGStab iteration: [whole, first half, second half][forward, transposed]
@@ -341,15 +343,18 @@ void scan_exclusive(const int32_t *in, int32_t *out, int64_t n, hipStream_t st);
 int32_t read_int(const int32_t *dptr, hipStream_t st);
 // several device int32 scalars / a short device array, one synchronisation
 constexpr int kPinnedWords = 64;
-int32_t *pinned_words();                 // kPinnedWords pinned host words of this thread
-void read_ints(std::initializer_list<const int32_t *> src, int32_t *out, hipStream_t st);
+int32_t *pinned_words();                 // kPinnedWords pinned host words of this thread, written by kernels
+void read_words(const int32_t *const *src, int count, int32_t *out, hipStream_t st);
 void read_array(const int32_t *dptr, int32_t count, int32_t *out, hipStream_t st);
 
 // conversion (convert.hip)
 void convert_pattern(cbs_system *h);
-void convert_values(cbs_system *h, const double *diag, const double *upper, const double *lower);
+// flag: two zeroed words that kernels can write, [0] set for a non-finite
+// coefficient, [1] for a bad cell state; the caller synchronises and reads them
+void convert_values(cbs_system *h, const double *diag, const double *upper, const double *lower, int32_t *flag);
 void assemble_luo(cbs_system *h, const double *Q, const double *Sf, const double *lam_visc, const double *v_dt,
-                  double gamma);
+                  double gamma, int32_t *flag);
+void luo_flag_errors(const int32_t *flag);
 // allocation-free variant of assemble_luo on the library's fixed scratch
 // (kNoAllocScratchBytes per device; larger systems are refused)
 constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;
@@ -357,8 +362,9 @@ size_t assemble_luo_scratch_bytes(int64_t N, int64_t F);
 void assemble_luo_noalloc(cbs_system *h, const double *Q, const double *Sf, const double *lam_visc,
                           const double *v_dt, double gamma);
 void assemble_pu(cbs_system *h, const double *Sf, const double *fx, const double *d, const double *flux,
-                 const double *nu, const double *vol, const double *uu_add, const double *pp_add);
-void check_finite(const double *a, int64_t count, int32_t *dflag, hipStream_t st);
+                 const double *nu, const double *vol, const double *uu_add, const double *pp_add, int32_t *flag);
+// CBS_ERR_NONFINITE unless both arrays of count values are finite
+void check_finite(const double *a, const double *b, int64_t count, hipStream_t st);
 void pack_fields(int32_t N, int32_t n, const double *soa, double *aos, hipStream_t st);
 void unpack_fields(int32_t N, int32_t n, const double *aos, double *soa, hipStream_t st);
 void gradient(cbs_system *h, const double *lam, const double *x, double *gd, double *gu, double *gl);

@@ -111,11 +111,30 @@ __device__ inline double sum_items(const double *partial, int32_t n_items, int q
 
 #define SC(slot) scal[(slot) * nsys + s]
 
+// Where the scalar kernels leave a system's state for the host (pinned memory;
+// see cbs_system::h_state): done, flags and iterations after every change,
+// the scalars when a true residual is formed.
+struct HostMirror {
+    int32_t *state;
+    double *scal;
+};
+
+__device__ inline void publish_state(const HostMirror &hm, int s, int nsys, const int32_t *done, const int32_t *flags,
+                                     const int32_t *iters) {
+    hm.state[s] = done[s];
+    hm.state[nsys + s] = flags[s];
+    hm.state[2 * nsys + s] = iters[s];
+}
+
+__device__ inline void publish_scal(const HostMirror &hm, int s, int nsys, const double *scal) {
+    for (int q = 0; q < S_NSCAL; ++q) hm.scal[q * nsys + s] = scal[q * nsys + s];
+}
+
 // Per-system scalar updates after a reduction.
 __global__ __launch_bounds__(kFinThreads) void k_fin(int phase, int32_t nsys, const int32_t *__restrict__ item_off,
                                                       int32_t n_items, const double *__restrict__ partial, double *scal,
                                                       int32_t *done, int32_t *flags, int32_t *iters, double tol2,
-                                                      const int32_t *restart_mask) {
+                                                      const int32_t *restart_mask, HostMirror hm) {
     const int s = blockIdx.x;
     const int32_t i0 = item_off[s], i1 = item_off[s + 1];
     // every phase needs at most two sums; compute them with the whole group
@@ -135,21 +154,18 @@ __global__ __launch_bounds__(kFinThreads) void k_fin(int phase, int32_t nsys, co
         done[s] = (bb == 0.0 || rr <= tol2 * bb) ? 1 : 0;
         flags[s] = 0;
         iters[s] = 0;
-        return;
-    }
-    if (phase == PH_TRUE) {                          // true residual of every system
+    } else if (phase == PH_TRUE) {                   // true residual of every system; the
+        SC(S_RREC) = SC(S_RR);                       // recurrence's is kept
         SC(S_RR) = q0;
+        publish_scal(hm, s, nsys, scal);
         return;
-    }
-    if (phase == PH_RESTART) {                       // rhat = r; p = v = 0 done by the caller
+    } else if (phase == PH_RESTART) {                // rhat = r; p = v = 0 done by the caller
         const double rr = q0;
         SC(S_RR) = rr; SC(S_RHO) = rr; SC(S_RHO0) = 1.0; SC(S_ALPHA) = 1.0; SC(S_OMEGA) = 1.0;
         SC(S_RRPREV) = 0.0;
         done[s] = (SC(S_BB) == 0.0 || rr <= tol2 * SC(S_BB)) ? 1 : 0;
         flags[s] = 0;
-        return;
-    }
-    if (phase == PH_ALPHA) {
+    } else if (phase == PH_ALPHA) {
         const double rv = q0;
         SC(S_RV) = rv;
         const double rho = SC(S_RHO);
@@ -179,6 +195,10 @@ __global__ __launch_bounds__(kFinThreads) void k_fin(int phase, int32_t nsys, co
         if (rrp > 0.0 && rr * (rr / rrp) <= 16.0 * tol2 * SC(S_BB)) flags[s] |= kFlagNear;
         SC(S_RRPREV) = rr;
     }
+    // the host looks after these, and at a breakdown, which ends the
+    // iteration's later phases (a state that stays as it is was published before)
+    if (phase == PH_INIT || phase == PH_RESTART || phase == PH_SNORM || phase == PH_END || (flags[s] & kFlagBreak))
+        publish_state(hm, s, nsys, done, flags, iters);
 }
 
 // p = r + beta (p - omega v),  beta = (rho / rho0) (alpha / omega)
@@ -417,11 +437,15 @@ __global__ __launch_bounds__(kVecThreads) void k_scale(const Item *__restrict__ 
 __global__ __launch_bounds__(kFinThreads) void k_gm_start(int32_t nsys, int m, const int32_t *__restrict__ item_off,
                                                            int32_t n_items, const double *__restrict__ partial,
                                                            double *scal, double *g, int32_t *done, int32_t *jlen,
-                                                           double tol2, int first) {
+                                                           double tol2, int first, const int32_t *flags,
+                                                           const int32_t *iters, HostMirror hm) {
     const int s = blockIdx.x;
     const double rr = sum_items(partial, n_items, 0, item_off[s], item_off[s + 1]);
     const double bbs = first ? sum_items(partial, n_items, 1, item_off[s], item_off[s + 1]) : 0.0;
     if (threadIdx.x != 0) return;
+    // the least-squares residual of the last cycle (first cycle: the initial
+    // true residual) before the restart replaces it
+    SC(S_RREC) = first ? rr : SC(S_RR);
     SC(S_RR) = rr;
     if (first) {
         const double bb = bbs;
@@ -435,6 +459,8 @@ __global__ __launch_bounds__(kFinThreads) void k_gm_start(int32_t nsys, int m, c
     gs[0] = beta;
     jlen[s] = 0;
     done[s] = (SC(S_BB) == 0.0 || rr <= tol2 * SC(S_BB)) ? 1 : 0;
+    publish_state(hm, s, nsys, done, flags, iters);
+    publish_scal(hm, s, nsys, scal);
 }
 
 // After the orthogonalisation of column j: H(j+1,j) = ||w|| (partials in slot
@@ -445,7 +471,8 @@ __global__ __launch_bounds__(kFinThreads) void k_gm_givens(int32_t nsys, int j, 
                                                             const int32_t *__restrict__ item_off, int32_t n_items,
                                                             const double *__restrict__ partial, int slot, double *scal,
                                                             double *H, double *cs, double *sn, double *g, int32_t *done,
-                                                            int32_t *jlen, int32_t *iters, double tol2, double *hn_out) {
+                                                            int32_t *jlen, int32_t *iters, double tol2, double *hn_out,
+                                                            const int32_t *flags, HostMirror hm) {
     __shared__ double sH[kMaxRestart + 1], sc[kMaxRestart + 1], ss[kMaxRestart + 1];
     const int s = blockIdx.x;
     if (done[s]) return;
@@ -479,6 +506,7 @@ __global__ __launch_bounds__(kFinThreads) void k_gm_givens(int32_t nsys, int j, 
         const double est = gn * gn;
         SC(S_RR) = est;
         if (est <= tol2 * SC(S_BB) || hn == 0.0) done[s] = 1;
+        publish_state(hm, s, nsys, done, flags, iters);
     }
     __syncthreads();
     for (int i = threadIdx.x; i <= j; i += kFinThreads) Hs[i * m + j] = sH[i];
@@ -541,7 +569,7 @@ void dots(cbs_system *h, int K, const double *a0, const double *b0, const double
 void fin(cbs_system *h, int phase, double tol2, const int32_t *restart_mask = nullptr) {
     hipLaunchKernelGGL(k_fin, dim3(h->n_sys), dim3(kFinThreads), 0, h->stream, phase, h->n_sys, h->item_off.get(),
                        h->n_items, h->partial.get(), h->scal.get(), h->done.get(), h->flags.get(),
-                       h->done.get() + 2 * h->n_sys, tol2, restart_mask);
+                       h->done.get() + 2 * h->n_sys, tol2, restart_mask, HostMirror{h->h_state, h->h_scal});
     LAUNCHCHK();
 }
 
@@ -852,27 +880,16 @@ struct HostView {
     std::vector<int32_t> state;     // done | flags | iters
 };
 
+// what the scalar kernels left in the pinned mirrors, copied: launches to come
+// write there again (the scalars are those of the last true residual)
 void read_state(cbs_system *h, HostView &hv, bool with_scal) {
-    hipStream_t st = h->stream;
-    hv.state.resize(3 * h->n_sys);
-    HIPCHK(hipMemcpyAsync(hv.state.data(), h->done.get(), sizeof(int32_t) * 3 * h->n_sys, hipMemcpyDeviceToHost, st));
-    if (with_scal) {
-        hv.scal.resize(S_NSCAL * h->n_sys);
-        HIPCHK(hipMemcpyAsync(hv.scal.data(), h->scal.get(), sizeof(double) * S_NSCAL * h->n_sys,
-                              hipMemcpyDeviceToHost, st));
-    }
-    HIPCHK(hipStreamSynchronize(st));
-}
-
-// keep the recurrence's ||r||^2 (S_RR) of every system in S_RREC before a
-// true residual overwrites it
-void save_recursive(cbs_system *h) {
-    const int nsys = h->n_sys;
-    HIPCHK(hipMemcpyAsync(h->scal.get() + (size_t)S_RREC * nsys, h->scal.get() + (size_t)S_RR * nsys,
-                          sizeof(double) * nsys, hipMemcpyDeviceToDevice, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    hv.state.assign(h->h_state, h->h_state + 3 * h->n_sys);
+    if (with_scal) hv.scal.assign(h->h_scal, h->h_scal + S_NSCAL * h->n_sys);
 }
 
 // true residual r = b - A x of every system -> S_RR
+// (the recurrence's goes to S_RREC)
 void true_residual(cbs_system *h, const double *b, const double *x, bool tr) {
     residual64(h, b, x, h->r.get(), tr);
     dots(h, 1, h->r.get(), h->r.get(), nullptr, nullptr, nullptr, nullptr, done_none(h));
@@ -1022,12 +1039,12 @@ int bicgstab(cbs_system *h, const double *b, double *x, bool tr, std::vector<int
                         int32_t one = 1;
                         HIPCHK(hipMemcpyAsync(h->done.get() + s, &one, sizeof(int32_t), hipMemcpyHostToDevice, st));
                         HIPCHK(hipStreamSynchronize(st));
+                        h->h_state[s] = 1;
                     }
                 continue;
             }
             if (all_done) {
                 // verify with the true residual; restart systems that fall short
-                save_recursive(h);
                 true_residual(h, b, x, tr);
                 read_state(h, hv, true);
                 std::vector<int32_t> mask(nsys, 0);
@@ -1038,7 +1055,7 @@ int bicgstab(cbs_system *h, const double *b, double *x, bool tr, std::vector<int
                     if (bb == 0.0 || rr <= tol2 * bb) status[s] = CBS_OK;
                     else if (it < o.max_iter && tr_restarts[s]++ < 50) { mask[s] = 1; any = true; }
                 }
-                if (!any) break;
+                if (!any) return it;             // S_RR holds the true residuals
                 HIPCHK(hipMemcpyAsync(rmask, mask.data(), sizeof(int32_t) * nsys, hipMemcpyHostToDevice, st));
                 hipLaunchKernelGGL(k_mask_copy, G, B, 0, st, items, rmask, 1, r, rh);
                 hipLaunchKernelGGL(k_mask_copy, G, B, 0, st, items, rmask, 1, nullptr, p);
@@ -1048,7 +1065,7 @@ int bicgstab(cbs_system *h, const double *b, double *x, bool tr, std::vector<int
                 continue;
             }
         }
-        if (it >= o.max_iter) { save_recursive(h); break; }
+        if (it >= o.max_iter) break;
         if (check) {
             // Near convergence (every unfinished system flagged by the end of
             // the last iteration) run the iteration in halves: if every
@@ -1076,6 +1093,7 @@ int bicgstab(cbs_system *h, const double *b, double *x, bool tr, std::vector<int
         }
         ++it;
     }
+    true_residual(h, b, x, tr);            // for the statistics
     return it;
 }
 
@@ -1105,19 +1123,15 @@ int fgmres(cbs_system *h, const double *b, double *x, bool tr, std::vector<int> 
     bool first = true;
     const int every = std::max(1, o.check_every);
     int32_t *iters = iters_ptr(h);
+    const HostMirror hm{h->h_state, h->h_scal};
     HIPCHK(hipMemsetAsync(iters, 0, sizeof(int32_t) * nsys, st));
     for (;;) {
-        // the least-squares residual of the last cycle (the first cycle: the
-        // initial true residual, saved below) before the restart replaces it
-        if (!first) save_recursive(h);
         residual64(h, b, x, r, tr);
         dots(h, 2, r, r, b, b, nullptr, nullptr, done_none(h));
         hipLaunchKernelGGL(k_gm_start, GS, BS, 0, st, nsys, m, h->item_off.get(), h->n_items, h->partial.get(),
-                           h->scal.get(), h->gvec.get(), h->done.get(), h->flags.get() + 3 * nsys, tol2, first ? 1 : 0);
-        if (first) {
-            hipLaunchKernelGGL(k_zero_if_bzero, G, B, 0, st, items, nsys, h->scal.get(), x);
-            save_recursive(h);
-        }
+                           h->scal.get(), h->gvec.get(), h->done.get(), h->flags.get() + 3 * nsys, tol2, first ? 1 : 0,
+                           h->flags.get(), iters, hm);
+        if (first) hipLaunchKernelGGL(k_zero_if_bzero, G, B, 0, st, items, nsys, h->scal.get(), x);
         first = false;
         read_state(h, hv, false);
         bool all_done = true;
@@ -1146,7 +1160,8 @@ int fgmres(cbs_system *h, const double *b, double *x, bool tr, std::vector<int> 
             }
             hipLaunchKernelGGL(k_gm_givens, GS, BS, 0, st, nsys, j, m, h->item_off.get(), h->n_items,
                                h->partial.get(), wslot, h->scal.get(), h->H.get(), h->cs.get(), h->sn.get(),
-                               h->gvec.get(), h->done.get(), h->flags.get() + 3 * nsys, iters, tol2, hn);
+                               h->gvec.get(), h->done.get(), h->flags.get() + 3 * nsys, iters, tol2, hn,
+                               h->flags.get(), hm);
             hipLaunchKernelGGL(k_scale, G, B, 0, st, items, h->done.get(), hn, m + 1, w, V + (j + 1) * ld);
             LAUNCHCHK();
             ++it;
@@ -1175,9 +1190,7 @@ int fgmres(cbs_system *h, const double *b, double *x, bool tr, std::vector<int> 
         // next cycle re-evaluates every system from its true residual
         HIPCHK(hipMemsetAsync(h->done.get(), 0, sizeof(int32_t) * nsys, st));
     }
-    // final true residual for the statistics
-    true_residual(h, b, x, tr);
-    return it;
+    return it;                                   // S_RR holds the true residuals: the last cycle's start
 }
 
 }  // namespace
@@ -1213,6 +1226,12 @@ void alloc_krylov(cbs_system *h) {
         h->sn.ensure((size_t)nsys * (mr + 1));
         h->yv.ensure((size_t)nsys * (mr + 1) * 3);
     }
+    if (!h->h_state) {
+        // written by the scalar kernels, read after a synchronisation
+        const unsigned how = hipHostMallocMapped | hipHostMallocCoherent | hipHostMallocPortable;
+        HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&h->h_state), sizeof(int32_t) * 3 * nsys, how));
+        HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&h->h_scal), sizeof(double) * S_NSCAL * nsys, how));
+    }
     const int K = std::max(3, h->opt.solver != CBS_SOLVER_BICGSTAB ? h->opt.restart + 2 : 3);
     h->partial.ensure((size_t)K * h->n_items);
 }
@@ -1221,10 +1240,10 @@ int krylov_solve(cbs_system *h, const double *b, double *x, cbs_stats *stv, bool
     hipStream_t st = h->stream;
     const int nsys = h->n_sys;
     if (tr) amg_build_transposed(h);
-    check_finite(b, (int64_t)h->N * h->n, h->dflag.get(), st);
     alloc_krylov(h);
     HIPCHK(hipMemsetAsync(h->flags.get(), 0, sizeof(int32_t) * 5 * nsys, st));
     HIPCHK(hipMemsetAsync(h->done.get(), 0, sizeof(int32_t) * 3 * nsys, st));
+    std::fill(h->h_state, h->h_state + 3 * nsys, 0);             // (the stream was synchronised by the last read)
     HIPCHK(hipEventRecord(h->ev0, st));
     std::vector<int> status;
     // the solvers run on work copies in the internal numbering (the captured
@@ -1245,18 +1264,7 @@ int krylov_solve(cbs_system *h, const double *b, double *x, cbs_stats *stv, bool
     if (h->renumbered) permute_vec(h, h->xw.get(), x, false);
     else launch_copy(m, h->xw.get(), x, st);
     HIPCHK(hipEventRecord(h->ev1, st));
-    // statistics: true residual per system (BiCGStab's last step may not have computed it)
-    std::vector<double> rr_rec(nsys), res0(nsys), bbv(nsys);
-    {
-        HostView hv;
-        read_state(h, hv, true);
-        for (int s = 0; s < nsys; ++s) {
-            rr_rec[s] = hv.scal[S_RREC * nsys + s];
-            res0[s] = hv.scal[S_RES0 * nsys + s];
-            bbv[s] = hv.scal[S_BB * nsys + s];
-        }
-    }
-    true_residual(h, bi, h->xw.get(), tr);
+    // statistics: both solvers leave the true residuals of x in S_RR
     HostView hv;
     read_state(h, hv, true);
     float ms = 0.f;
@@ -1264,7 +1272,7 @@ int krylov_solve(cbs_system *h, const double *b, double *x, cbs_stats *stv, bool
     int worst = CBS_OK;
     const double tol2 = h->opt.tol * h->opt.tol;
     for (int s = 0; s < nsys; ++s) {
-        const double bb = bbv[s], rr = hv.scal[S_RR * nsys + s];
+        const double bb = hv.scal[S_BB * nsys + s], rr = hv.scal[S_RR * nsys + s];
         int stt = status[s];
         if (stt != CBS_ERR_BREAKDOWN) stt = (bb == 0.0 || rr <= tol2 * bb) ? CBS_OK : CBS_NOT_CONVERGED;
         if (stt < 0) worst = std::min(worst, stt);
@@ -1276,8 +1284,8 @@ int krylov_solve(cbs_system *h, const double *b, double *x, cbs_stats *stv, bool
             S.levels = (int32_t)h->lev.size();
             S.precision_fallback = 0;
             S.rel_res_true = bb > 0.0 ? std::sqrt(rr / bb) : 0.0;
-            S.rel_res_recursive = bb > 0.0 ? std::sqrt(std::max(rr_rec[s], 0.0) / bb) : 0.0;
-            S.rel_res_initial = res0[s];
+            S.rel_res_recursive = bb > 0.0 ? std::sqrt(std::max(hv.scal[S_RREC * nsys + s], 0.0) / bb) : 0.0;
+            S.rel_res_initial = hv.scal[S_RES0 * nsys + s];
             S.t_convert_ms = h->t_convert_ms;
             S.t_setup_ms = h->t_setup_ms;
             S.t_solve_ms = ms;

@@ -1273,11 +1273,11 @@ void launch_coarse_solve(cbs_system *h, bool transposed, const void *b, void *x,
     const double *inv = transposed ? C.invT.get() : C.inv.get();
     const size_t shm = sizeof(double) * (size_t)C.max_m;
     if (fp32)
-        hipLaunchKernelGGL(k_coarse<float>, dim3(h->n_sys), dim3(256), shm, h->stream, inv, C.off.get(), C.m.get(),
-                           C.roff.get(), (const float *)b, (float *)x);
+        hipLaunchKernelGGL(k_coarse<float>, dim3(h->n_sys), dim3(256), shm, h->stream, inv, C.off, C.m,
+                           C.roff, (const float *)b, (float *)x);
     else
-        hipLaunchKernelGGL(k_coarse<double>, dim3(h->n_sys), dim3(256), shm, h->stream, inv, C.off.get(), C.m.get(),
-                           C.roff.get(), (const double *)b, (double *)x);
+        hipLaunchKernelGGL(k_coarse<double>, dim3(h->n_sys), dim3(256), shm, h->stream, inv, C.off, C.m,
+                           C.roff, (const double *)b, (double *)x);
     LAUNCHCHK();
 }
 

@@ -469,8 +469,8 @@ void tail_form(cbs_system *h, bool tr) {
     }
     a.roff = T.roff;
     a.cinv = tr ? h->coarse.invT.get() : h->coarse.inv.get();
-    a.coff = h->coarse.off.get();
-    a.cm = h->coarse.m.get();
+    a.coff = h->coarse.off;
+    a.cm = h->coarse.m;
     a.opoff = T.off;
     a.op = op.get();
     a.omega = level_omega(h->opt, T.level);          // every tail level is below level 0

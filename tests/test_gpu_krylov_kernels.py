@@ -66,3 +66,46 @@ def test_batched_gmres_systems_match_solo_iterates():
         xo, _ = O.gmres(O.from_system(sk), sk["b"], prec=O.PREC_BJACOBI, tol=1e-14, maxit=12, restart=9)
         xk = x[cat["cell_off"][k]:cat["cell_off"][k + 1]]
         assert np.linalg.norm(xk - xo) <= 1e-9 * np.linalg.norm(xo), k
+
+
+def test_breakdown_reaches_the_host():
+    """A block [[0, 1], [-1, 0]] makes (r, A r) vanish: BiCGStab without a
+    preconditioner breaks down, restarts once and gives up, alone and beside a
+    system that converges (its solution is still written)."""
+    D = np.array([[[0.0, 1.0], [-1.0, 0.0]], [[2.0, 1.0], [0.0, 3.0]]])
+    none = np.zeros((0, 2, 2))
+    no = np.zeros(0, np.int32)
+    with P.System(1, 2, no, no, D[:1], none, none) as s:
+        s.setup(precond=P.PREC_NONE)
+        with pytest.raises(P.CbsError) as e:
+            s.solve(np.array([[1.0, 0.0]]))
+        assert e.value.code == P.ERR_BREAKDOWN
+    with P.System(2, 2, no, no, D, none, none, cell_off=[0, 1, 2], face_off=[0, 0, 0]) as s:
+        s.setup(precond=P.PREC_NONE, tol=1e-12)
+        with pytest.raises(P.CbsError) as e:
+            s.solve_batch(np.array([[1.0, 0.0], [3.0, 3.0]]))
+        assert e.value.code == P.ERR_BREAKDOWN
+        # the handle still works
+        s.update_values(D[[1, 1]], none, none)
+        s.setup(precond=P.PREC_NONE, tol=1e-12)
+        x, st = s.solve_batch(np.array([[3.0, 3.0], [3.0, 3.0]]))
+        assert all(q["status"] == P.OK for q in st)
+        assert np.allclose(x.cpu().numpy(), 1.0, atol=1e-10)
+
+
+@pytest.mark.parametrize("solver", [P.SOLVER_BICGSTAB, P.SOLVER_FGMRES, P.SOLVER_GMRES])
+@pytest.mark.parametrize("max_iter,tol", [(0, 1e-8), (3, 1e-14), (500, 1e-10)])
+def test_reported_residuals_are_those_of_x(solver, max_iter, tol):
+    """The statistics' true residual against the oracle's on the returned x,
+    where the solve stops at once, at the cap and converged (relative error of
+    a residual formed in another order: eps |A||x| / |r|, under 1e-3 at 1e-10)."""
+    s = pressure_velocity(8, 7, 6, seed=76)
+    A = O.from_system(s)
+    x0 = np.random.default_rng(77).standard_normal((s["N"], 4))
+    with P.System.from_dict(s) as sysm:
+        sysm.setup(precond=P.PREC_AMG, solver=solver, restart=10, tol=tol, max_iter=max_iter)
+        x, st = sysm.solve(s["b"], x0)
+    assert abs(O.relres(A, s["b"], x.cpu().numpy()) - st["rel_res_true"]) <= 1e-3 * st["rel_res_true"]
+    assert abs(O.relres(A, s["b"], x0) - st["rel_res_initial"]) <= 1e-9 * st["rel_res_initial"]
+    assert abs(st["rel_res_recursive"] - st["rel_res_true"]) <= 0.1 * st["rel_res_true"] + 1e-13
+    assert st["status"] == (P.OK if max_iter == 500 else P.NOT_CONVERGED)
