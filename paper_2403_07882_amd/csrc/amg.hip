@@ -1899,7 +1899,8 @@ void amg_setup(cbs_system *h) {
             if (t.coloured || t.L->N > kOneWgRows || t.L->N < 1) {
                 sell_pattern_begin(t.L->N, t.L->rp, t.L->col, *t.S, st, t.od, slice(t),
                                    t.coloured ? t.L->rows_by_colour.get() : nullptr,
-                                   t.coloured ? &t.L->colour_off : nullptr);
+                                   t.coloured ? &t.L->colour_off : nullptr,
+                                   !t.coloured && t.L != &h->lev[0] && t.L->N >= kSplitLevelRows);
                 continue;
             }
             sell_pattern_shape(t.L->N, *t.S, slice(t));

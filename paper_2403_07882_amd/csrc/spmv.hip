@@ -104,12 +104,15 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
     constexpr int nn = n * n;
     const int t = threadIdx.x;
     const int lr = t / n, r = t - lr * n;
-    // position p in the sliced copy holds block row i (colour-ordered copies
+    // position p in the sliced copy holds block row h (colour-ordered copies
     // map positions to rows; the padding positions of their colour ranges
-    // hold none)
+    // hold none).  In a window-ordered copy the workgroup's 64 rows change
+    // places: their sums go back through LDS, and the thread finishes row p,
+    // so that the row vectors are read and written in order.
     const int32_t p = blockIdx.x * 64 + lr;
-    const int32_t i = (S.prow && p < S.N) ? S.prow[p] : p;
-    const bool act = p < S.N && i >= 0;
+    const int32_t h = (S.prow && p < S.N) ? S.prow[p] : p;
+    const bool act = p < S.N && h >= 0;
+    const int32_t i = S.win ? p : h;
     // sweep result: to y, or widened to FP64 into y64 (the last sweep of a
     // mixed-precision V-cycle hands its result straight to the FP64 loop)
     auto put = [&](int64_t o, TX v) {
@@ -145,7 +148,7 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
             for (int u = 0; u < U; ++u) {
                 const int64_t e = base + ((int64_t)(k + u) << S.lc);
                 load_row_nt<n, TV, NT>(val + e * nn + r * n, bv[u]);
-                load_xc<n, TX, PRO>(x, j[u] < 0 ? i : j[u], pagg, pe, xv[u]);
+                load_xc<n, TX, PRO>(x, j[u] < 0 ? h : j[u], pagg, pe, xv[u]);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -179,6 +182,12 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
                 }
         }
     }
+    __shared__ A sres[64 * n];
+    if (MODE != 3 && S.win) {
+        if (act) sres[(h - (int32_t)blockIdx.x * 64) * n + r] = acc;
+        __syncthreads();
+        acc = sres[t];
+    }
     if (MODE == 0) {
         if (act) y[o] = (TX)acc;
         return;
@@ -193,7 +202,7 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
         if (act) put(o, (TX)((A)xo + (A)omega * (res - (A)xo)));
         return;
     }
-    __shared__ A sres[64 * n];
+    if (S.win) __syncthreads();            // (the sums have been read)
     sres[t] = res;
     __syncthreads();
     if (act) {
@@ -359,6 +368,7 @@ void rows_launch(const SellView &S, const TV *val, const TX *x, const TX *b, TX 
                        aux, pagg, pe, y64)
     if (MODE == 3) { ROWS_V(1, false); return; }       // no matrix read
     const int sp = S.sched.split;
+    if (sp > 1 && S.win) cbs_throw(CBS_ERR_ARG, "a window-ordered copy keeps its rows whole");
     if (sp > 1) {
         const dim3 gs(cdiv((int64_t)S.N * sp, 64));
 #define ROWS_S(SS)                                                                                           \
@@ -650,6 +660,22 @@ __global__ void k_fill_i32(int64_t m, int32_t *a, int32_t v) {
     if (g < m) a[g] = v;
 }
 
+// Window order: the rows of each window by length, longest first, equal ones
+// in order (one wavefront per window).
+__global__ __launch_bounds__(kWindow) void k_window_order(int32_t N, const int32_t *rp, int32_t *prow) {
+    __shared__ int32_t len[kWindow];
+    const int t = threadIdx.x;
+    const int32_t i = blockIdx.x * kWindow + t;
+    const int32_t mine = i < N ? rp[i + 1] - rp[i] : -1;
+    len[t] = mine;
+    __syncthreads();
+    if (i >= N) return;
+    int rank = 0;
+#pragma unroll 8
+    for (int q = 0; q < kWindow; ++q) rank += len[q] > mine || (len[q] == mine && q < t) ? 1 : 0;
+    prow[blockIdx.x * kWindow + rank] = i;
+}
+
 // Colour-ordered positions: the t-th row of the (colour, row)-sorted list
 // goes to position cpos[c] + t - off[c] of its colour c.
 struct ColourRanges {
@@ -709,6 +735,7 @@ constexpr int kScaleU = 4;   // entries per row staged together in k_sell_scaled
 
 template <int n>
 __global__ __launch_bounds__(64 * n) void k_sell_scaled(int32_t N, int32_t nslices, int32_t lc,
+                                                        const int32_t *__restrict__ prow,
                                                         const int32_t *__restrict__ soff,
                                                         const int32_t *__restrict__ sw,
                                                         const int32_t *__restrict__ ssrc,
@@ -735,7 +762,7 @@ __global__ __launch_bounds__(64 * n) void k_sell_scaled(int32_t N, int32_t nslic
     if (r == 0 && w > 0) atomicMax(&wmax, w);
     double d[n];
 #pragma unroll
-    for (int q = 0; q < n; ++q) d[q] = (act && i < N) ? Dinv[i * nn + r * n + q] : 0.0;
+    for (int q = 0; q < n; ++q) d[q] = (act && i < N) ? Dinv[(prow ? prow[i] : i) * nn + r * n + q] : 0.0;
     __syncthreads();
     const int32_t W = wmax;
     bool bad = false;
@@ -787,6 +814,7 @@ __global__ __launch_bounds__(64 * n) void k_sell_scaled(int32_t N, int32_t nslic
 // row, r), kScaleU entries staged in LDS at a time.
 template <int n>
 __global__ __launch_bounds__(64 * n) void k_sell_fill_scaled(int32_t N, int32_t nslices, int32_t lc,
+                                                             const int32_t *__restrict__ prow,
                                                              const int32_t *__restrict__ fsoff,
                                                              const int32_t *__restrict__ fsw,
                                                              const int32_t *__restrict__ fscol,
@@ -812,9 +840,10 @@ __global__ __launch_bounds__(64 * n) void k_sell_fill_scaled(int32_t N, int32_t 
     if (t == 0) wmax = 0;
     __syncthreads();
     if (r == 0 && w > 0) atomicMax(&wmax, w);
+    const int32_t row = act && i < N ? (prow ? prow[i] : (int32_t)i) : -2;      // (-1: the padding's column)
     double d[n];
 #pragma unroll
-    for (int q = 0; q < n; ++q) d[q] = (act && i < N) ? Dinv[i * nn + r * n + q] : 0.0;
+    for (int q = 0; q < n; ++q) d[q] = (act && i < N) ? Dinv[(int64_t)row * nn + r * n + q] : 0.0;
     __syncthreads();
     const int32_t W = wmax;
     bool bad = false;
@@ -851,7 +880,7 @@ __global__ __launch_bounds__(64 * n) void k_sell_fill_scaled(int32_t N, int32_t 
                 f32[e * nn + r * n + c] = v;
                 bad = bad || !isfinite(v);
             }
-            const bool diag = cj[u] == (int32_t)i;
+            const bool diag = cj[u] == row;
             if (diag) { passed = 1; continue; }
             const int32_t jo = k0 + u - passed;
             if (jo >= wo) continue;
@@ -975,7 +1004,8 @@ void launch_bcsr(int n, int32_t N, const int32_t *rp, const int32_t *col, const 
 }
 
 void sell_pattern_begin(int32_t N, const int32_t *rp, const int32_t *col, Sell &S, hipStream_t st, bool offdiag,
-                        int slice, const int32_t *rows_by_colour, const std::vector<int32_t> *colour_off) {
+                        int slice, const int32_t *rows_by_colour, const std::vector<int32_t> *colour_off,
+                        bool window) {
     int lc = 0;
     while ((1 << lc) < slice) ++lc;
     if ((1 << lc) != slice || lc > 6) cbs_throw(CBS_ERR_ARG, "slice height must be a power of two up to 64");
@@ -1008,6 +1038,11 @@ void sell_pattern_begin(int32_t N, const int32_t *rp, const int32_t *col, Sell &
         S.cpos.clear();
         S.npos = N;
     }
+    S.win = window && !rows_by_colour && N > 0;
+    if (S.win) {
+        S.prow.alloc(N);
+        hipLaunchKernelGGL(k_window_order, dim3(cdiv(N, kWindow)), dim3(kWindow), 0, st, N, rp, S.prow.get());
+    }
     S.nslices = (S.npos + C - 1) / C;
     const int32_t ns = S.nslices;
     S.sw.alloc(ns > 0 ? ns : 1);
@@ -1024,6 +1059,7 @@ void sell_pattern_shape(int32_t N, Sell &S, int slice) {
     while ((1 << S.lc) < slice) ++S.lc;
     S.N = S.npos = N;
     S.prow.release();
+    S.win = false;
     S.cpos.clear();
     S.nslices = (N + slice - 1) / slice;
     S.sw.alloc(S.nslices);
@@ -1043,8 +1079,8 @@ void sell_pattern_finish(const int32_t *rp, const int32_t *col, Sell &S, int64_t
 }
 
 void sell_build(int32_t N, const int32_t *rp, const int32_t *col, Sell &S, hipStream_t st, bool offdiag, int slice,
-                const int32_t *rows_by_colour, const std::vector<int32_t> *colour_off) {
-    sell_pattern_begin(N, rp, col, S, st, offdiag, slice, rows_by_colour, colour_off);
+                const int32_t *rows_by_colour, const std::vector<int32_t> *colour_off, bool window) {
+    sell_pattern_begin(N, rp, col, S, st, offdiag, slice, rows_by_colour, colour_off, window);
     sell_pattern_finish(rp, col, S, read_int(S.soff.get() + S.nslices, st), st, offdiag);
 }
 
@@ -1074,12 +1110,14 @@ void sell_fill(int n, const Sell &S, const double *bcsr_vals, double *out, hipSt
 void sell_fill_scaled(int n, const Sell &F, const Sell &O, const double *bcsr_vals, const double *Dinv,
                       double *f64, float *f32, float *o32, int32_t *flag, hipStream_t st) {
     if (F.N <= 0) return;
-    if (F.lc != O.lc || F.nslices != O.nslices || F.prow.get() || O.prow.get())
+    // (window order depends on the row lengths alone, which the two patterns
+    // share but for the diagonal every row has)
+    if (F.lc != O.lc || F.nslices != O.nslices || F.win != O.win || (F.prow.get() && !F.win))
         cbs_throw(CBS_ERR_ARG, "sliced copies do not share their slices");
     const int64_t npos = (int64_t)F.nslices << F.lc;
     const dim3 g(cdiv(npos, 64));
 #define FS_N(NN)                                                                                               \
-    hipLaunchKernelGGL(k_sell_fill_scaled<NN>, g, dim3(64 * NN), 0, st, F.N, F.nslices, F.lc, F.soff.get(),     \
+    hipLaunchKernelGGL(k_sell_fill_scaled<NN>, g, dim3(64 * NN), 0, st, F.N, F.nslices, F.lc, F.prow.get(), F.soff.get(), \
                        F.sw.get(), F.scol.get(), F.ssrc.get(), O.soff.get(), O.sw.get(), bcsr_vals, Dinv, f64, \
                        f32, o32, flag)
     switch (n) {
@@ -1097,10 +1135,11 @@ void sell_scale(int n, const Sell &S, const double *bcsr_vals, const double *Din
                 hipStream_t st) {
     const int64_t npos = (int64_t)S.nslices << S.lc;
     if (S.N <= 0) return;
+    if (S.prow.get() && !S.win) cbs_throw(CBS_ERR_ARG, "row-scaled values of a coloured copy");
     const dim3 g(cdiv(npos, 64));
 #define SCALE_N(NN)                                                                                           \
-    hipLaunchKernelGGL(k_sell_scaled<NN>, g, dim3(64 * NN), 0, st, S.N, S.nslices, S.lc, S.soff.get(), S.sw.get(), \
-                       S.ssrc.get(), bcsr_vals, Dinv, out, flag)
+    hipLaunchKernelGGL(k_sell_scaled<NN>, g, dim3(64 * NN), 0, st, S.N, S.nslices, S.lc, S.prow.get(),          \
+                       S.soff.get(), S.sw.get(), S.ssrc.get(), bcsr_vals, Dinv, out, flag)
     switch (n) {
         case 1: SCALE_N(1); break;
         case 2: SCALE_N(2); break;
