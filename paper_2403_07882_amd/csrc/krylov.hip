@@ -341,26 +341,21 @@ __global__ void k_gm_add(const Item *__restrict__ items, const double *__restric
 // one item and kBasisGroup basis vectors at a time: the vector w is read once
 // per group instead of once per basis vector, the group's loads are in flight
 // together, and their sums are reduced in one pass.  59,319 cells, 5x5,
-// GMRES(30), mean of 15 vectors: one vector at a time with a reduction each
-// took 43 us for k_mdot and 28 us for k_maxpy, this form 8.1 us and 5.4 us (means over
-// both orthogonalisation passes, the second mostly masked).
+// GMRES(30), mean of 15 vectors and of both passes, the second mostly skipped:
+// one vector at a time with a reduction each took 43 us for k_mdot and 28 us
+// for k_maxpy, this form 8.1 us and 5.4 us.
 constexpr int kBasisGroup = 8;
 
-// partials of (V_i, w), i = 0..j, and with ww also (w, w) in slot j + 1;
-// blockIdx.y picks the group of basis vectors
-__global__ __launch_bounds__(kVecThreads) void k_mdot(const Item *__restrict__ items, int32_t n_items,
-                                                      const int32_t *__restrict__ done, int j, int64_t ld,
-                                                      const double *__restrict__ V, const double *__restrict__ w,
-                                                      double *__restrict__ partial, int ww) {
-    __shared__ double red[kBasisGroup * (kVecThreads / 64)];
-    const Item it = items[blockIdx.x];
-    if (done[it.sys]) return;                     // its partials are not read
-    const int K = j + 1 + (ww ? 1 : 0), i0 = (int)blockIdx.y * kBasisGroup;
+// One item's partials of (V_i, w) for the basis vectors i0 .. i0 + kBasisGroup - 1;
+// past the basis (i > j) the slot up to K - 1 takes (w, w)
+__device__ inline void item_dots(const Item &it, int item, int32_t n_items, int i0, int j, int K, int64_t ld,
+                                 const double *__restrict__ V, const double *w, double *__restrict__ partial,
+                                 double *red) {
     const double *vp[kBasisGroup];
     double acc[kBasisGroup];
 #pragma unroll
     for (int q = 0; q < kBasisGroup; ++q) {
-        vp[q] = i0 + q <= j ? V + (i0 + q) * ld : w;   // past the basis: (w, w), or unused
+        vp[q] = i0 + q <= j ? V + (i0 + q) * ld : w;
         acc[q] = 0.0;
     }
 #pragma unroll 2
@@ -373,49 +368,66 @@ __global__ __launch_bounds__(kVecThreads) void k_mdot(const Item *__restrict__ i
     if (threadIdx.x == 0)
 #pragma unroll
         for (int q = 0; q < kBasisGroup; ++q)
-            if (i0 + q < K) partial[(int64_t)(i0 + q) * n_items + blockIdx.x] = acc[q];
+            if (i0 + q < K) partial[(int64_t)(i0 + q) * n_items + item] = acc[q];
 }
 
-// h_i (per system) = sum of partials; accumulate into H(:, j); store in coef.
-// One wavefront per basis vector, so the sums of all of them run side by side
-// (one after the other by the whole workgroup: 7.9 us, now 3.2 us).
-// With skip (first pass, which also summed (w, w) in slot j + 1): a system
-// whose w keeps more than a tenth of its norm, ||w - sum h_i V_i||^2 =
-// ||w||^2 - sum h_i^2 > 0.01 ||w||^2, skips the second (re-orthogonalising)
-// pass: skip[s] = 1 (also for a finished system).
-constexpr int kMdotFinThreads = 1024;
-constexpr int kMaxRestart = 200;                  // cbs_setup refuses larger ones
+// partials of (V_i, w), i = 0..j, and (w, w) in slot j + 1; blockIdx.y picks
+// the group of basis vectors
+__global__ __launch_bounds__(kVecThreads) void k_mdot(const Item *__restrict__ items, int32_t n_items,
+                                                      const int32_t *__restrict__ done, int j, int64_t ld,
+                                                      const double *__restrict__ V, const double *__restrict__ w,
+                                                      double *__restrict__ partial) {
+    __shared__ double red[kBasisGroup * (kVecThreads / 64)];
+    const Item it = items[blockIdx.x];
+    if (done[it.sys]) return;                     // its partials are not read
+    item_dots(it, blockIdx.x, n_items, (int)blockIdx.y * kBasisGroup, j, j + 2, ld, V, w, partial, red);
+}
 
-__global__ __launch_bounds__(kMdotFinThreads) void k_mdot_fin(int j, int m, const int32_t *__restrict__ item_off,
-                                                               int32_t n_items, const double *__restrict__ partial,
-                                                               const int32_t *__restrict__ done, double *H,
-                                                               double *coef, int accumulate, int32_t *skip) {
-    __shared__ double sh[kMaxRestart + 2];
-    const int s = blockIdx.x;
-    if (done[s]) {
-        if (skip && threadIdx.x == 0) skip[s] = 1;
-        return;
-    }
-    const int32_t i0 = item_off[s], i1 = item_off[s + 1];
+// Sums over one system's items of K slots of partials -> out[0..K) (LDS), one
+// wavefront per slot, so that the slots' sums run side by side.  The caller
+// waits (a barrier) before it reads them.
+template <int THREADS>
+__device__ inline void slot_sums(const double *__restrict__ partial, int32_t n_items, int K, int32_t i0, int32_t i1,
+                                 double *out) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int K = j + 1 + (skip ? 1 : 0);
-    for (int i = wid; i < K; i += kMdotFinThreads / 64) {
+    for (int i = wid; i < K; i += THREADS / 64) {
         const double *pi = partial + (int64_t)i * n_items;
         double t = 0.0;
 #pragma unroll 4
         for (int32_t k = i0 + lane; k < i1; k += 64) t += pi[k];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-        if (lane == 0) sh[i] = t;
+        if (lane == 0) out[i] = t;
     }
+}
+
+// First pass: h_i (per system) = sum of partials, into H(:, j) and coef, one
+// wavefront per basis vector (one after the other by the whole workgroup:
+// 7.9 us, now 3.2 us).  A system whose w keeps more than a tenth of its norm,
+// ||w - sum h_i V_i||^2 = ||w||^2 - sum h_i^2 > 0.01 ||w||^2 ((w, w) in slot
+// j + 1), skips the second (re-orthogonalising) pass: skip[s] = 1 (also for a
+// finished system).
+constexpr int kMdotFinThreads = 1024;
+constexpr int kMaxRestart = 200;                  // cbs_setup refuses larger ones
+
+__global__ __launch_bounds__(kMdotFinThreads) void k_mdot_fin(int j, int m, const int32_t *__restrict__ item_off,
+                                                               int32_t n_items, const double *__restrict__ partial,
+                                                               const int32_t *__restrict__ done, double *H,
+                                                               double *coef, int32_t *skip) {
+    __shared__ double sh[kMaxRestart + 2];
+    const int s = blockIdx.x;
+    if (done[s]) {
+        if (threadIdx.x == 0) skip[s] = 1;
+        return;
+    }
+    slot_sums<kMdotFinThreads>(partial, n_items, j + 2, item_off[s], item_off[s + 1], sh);
     __syncthreads();
     if ((int)threadIdx.x <= j) {
         const int i = threadIdx.x;
-        double *h = H + (int64_t)s * (m + 1) * m + (int64_t)i * m + j;
-        *h = accumulate ? *h + sh[i] : sh[i];
+        H[(int64_t)s * (m + 1) * m + (int64_t)i * m + j] = sh[i];
         coef[(int64_t)s * (m + 1) + i] = sh[i];
     }
-    if (skip && threadIdx.x == 0) {
+    if (threadIdx.x == 0) {
         double hh = 0.0;
         for (int i = 0; i <= j; ++i) hh += sh[i] * sh[i];
         skip[s] = (sh[j + 1] - hh > 0.01 * sh[j + 1]) ? 1 : 0;
@@ -440,15 +452,9 @@ __device__ inline double basis_sum(double base, int K, const double *__restrict_
     return acc;
 }
 
-// w -= sum_i coef_i V_i, and the partials of the new (w, w) in slot `slot`
-__global__ __launch_bounds__(kVecThreads) void k_maxpy(const Item *__restrict__ items, int32_t n_items,
-                                                       const int32_t *__restrict__ done, int j, int m, int64_t ld,
-                                                       const double *__restrict__ V, const double *__restrict__ coef,
-                                                       double *__restrict__ w, double *__restrict__ partial, int slot) {
-    __shared__ double red[kVecThreads / 64];
-    const Item it = items[blockIdx.x];
-    if (done[it.sys]) return;
-    const double *c = coef + (int64_t)it.sys * (m + 1);
+// w -= sum_i c_i V_i over one item; returns this thread's part of the new (w, w)
+__device__ inline double item_axpy(const Item &it, int j, int64_t ld, const double *__restrict__ V, const double *c,
+                                   double *w) {
     double s0 = 0.0;
 #pragma unroll 2
     for (int64_t e = it.beg + threadIdx.x; e < it.end; e += kVecThreads) {
@@ -456,17 +462,60 @@ __global__ __launch_bounds__(kVecThreads) void k_maxpy(const Item *__restrict__ 
         w[e] = we;
         s0 += we * we;
     }
-    s0 = block_sum(s0, red);
+    return s0;
+}
+
+// End of the first pass: w -= sum_i coef_i V_i, and the partials of the new
+// (w, w) in slot `slot`.  For a system that takes the second pass, also that
+// pass's partials (V_i, w): a workgroup's item of w, just written by the
+// threads that read it again, is all they need.
+__global__ __launch_bounds__(kVecThreads) void k_maxpy(const Item *__restrict__ items, int32_t n_items,
+                                                       const int32_t *__restrict__ done,
+                                                       const int32_t *__restrict__ skip, int j, int m, int64_t ld,
+                                                       const double *__restrict__ V, const double *__restrict__ coef,
+                                                       double *w, double *__restrict__ partial, int slot) {
+    __shared__ double red[kBasisGroup * (kVecThreads / 64)];
+    const Item it = items[blockIdx.x];
+    if (done[it.sys]) return;
+    double s0 = block_sum(item_axpy(it, j, ld, V, coef + (int64_t)it.sys * (m + 1), w), red);
+    if (threadIdx.x == 0) partial[(int64_t)slot * n_items + blockIdx.x] = s0;
+    if (skip[it.sys]) return;
+    for (int i0 = 0; i0 <= j; i0 += kBasisGroup) {
+        item_dots(it, blockIdx.x, n_items, i0, j, j + 1, ld, V, w, partial, red);
+        __syncthreads();                          // red is used again
+    }
+}
+
+// The second pass, for the systems that take it: every workgroup sums the
+// partials for its coefficients, the system's first one adds them to H(:, j).
+// Most steps skip it, and a launch that does nothing costs 4 us: this is the
+// only one (with products, sums and V_{j+1} in launches of their own a step had
+// eight; 59,319 cells, 5x5, GMRES(30) of 86 steps: 10.93 -> 10.52 ms).
+__global__ __launch_bounds__(kVecThreads) void k_maxpy_again(const Item *__restrict__ items,
+                                                             const int32_t *__restrict__ item_off, int32_t n_items,
+                                                             const int32_t *__restrict__ skip, int j, int m,
+                                                             int64_t ld, const double *__restrict__ V, double *H,
+                                                             double *w, double *partial, int slot) {
+    __shared__ double c[kMaxRestart + 1], red[kVecThreads / 64];
+    const Item it = items[blockIdx.x];
+    const int s = it.sys;
+    if (skip[s]) return;
+    const int32_t i0 = item_off[s];
+    slot_sums<kVecThreads>(partial, n_items, j + 1, i0, item_off[s + 1], c);
+    __syncthreads();
+    if ((int32_t)blockIdx.x == i0)
+        for (int i = threadIdx.x; i <= j; i += kVecThreads) H[(int64_t)s * (m + 1) * m + (int64_t)i * m + j] += c[i];
+    const double s0 = block_sum(item_axpy(it, j, ld, V, c, w), red);
     if (threadIdx.x == 0) partial[(int64_t)slot * n_items + blockIdx.x] = s0;
 }
 
-// y = a * inv(scal) per system: V_{j+1} = w / hn ; V_0 = r / beta
+// V_0 = r / beta
 __global__ __launch_bounds__(kVecThreads) void k_scale(const Item *__restrict__ items, const int32_t *__restrict__ done,
-                                                       const double *__restrict__ nrm, int stride, const double *a,
-                                                       double *y) {
+                                                       const double *__restrict__ nrm, const double *__restrict__ a,
+                                                       double *__restrict__ y) {
     const Item it = items[blockIdx.x];
     if (done[it.sys]) return;
-    const double d = nrm[(int64_t)it.sys * stride];
+    const double d = nrm[it.sys];
     const double f = d > 0.0 ? 1.0 / d : 0.0;
     for (int64_t e = it.beg + threadIdx.x; e < it.end; e += kVecThreads) y[e] = a[e] * f;
 }
@@ -504,16 +553,31 @@ __global__ __launch_bounds__(kFinThreads) void k_gm_start(int32_t nsys, int m, c
 }
 
 // After the orthogonalisation of column j: H(j+1,j) = ||w|| (partials in slot
-// `slot`), apply the previous rotations, make rotation j, update g, and test
-// |g(j+1)|.  The column and the rotations pass through LDS: the rotations are
-// applied one after the other, which from memory cost a load each.
-__global__ __launch_bounds__(kFinThreads) void k_gm_givens(int32_t nsys, int j, int m,
+// `slot`), and in two kinds of workgroups side by side:
+// the first nsys, one per system, apply the previous rotations, make rotation
+// j, update g, and test |g(j+1)|.  The column and the rotations pass through
+// LDS: the rotations are applied one after the other, which from memory cost a
+// load each.
+// The others, one per item, form V_{j+1} = w / ||w|| (a system that finishes in
+// this step may leave its items undone: they are not read again).
+__global__ __launch_bounds__(kFinThreads) void k_gm_givens(int32_t nsys, int j, int m, const Item *__restrict__ items,
                                                             const int32_t *__restrict__ item_off, int32_t n_items,
                                                             const double *__restrict__ partial, int slot, double *scal,
                                                             double *H, double *cs, double *sn, double *g, int32_t *done,
-                                                            int32_t *jlen, int32_t *iters, double tol2, double *hn_out,
-                                                            const int32_t *flags, HostMirror hm) {
+                                                            int32_t *jlen, int32_t *iters, double tol2,
+                                                            const int32_t *flags, HostMirror hm,
+                                                            const double *__restrict__ w, double *__restrict__ vnext) {
     __shared__ double sH[kMaxRestart + 1], sc[kMaxRestart + 1], ss[kMaxRestart + 1];
+    __shared__ double sh[kFinThreads / 64];
+    double ww[1];
+    if ((int)blockIdx.x >= nsys) {
+        const Item it = items[blockIdx.x - nsys];
+        if (done[it.sys]) return;
+        sum_items<1>(partial, n_items, {slot}, item_off[it.sys], item_off[it.sys + 1], sh, ww);
+        const double d = sqrt(ww[0]), f = d > 0.0 ? 1.0 / d : 0.0;
+        for (int64_t e = it.beg + threadIdx.x; e < it.end; e += kVecThreads) vnext[e] = w[e] * f;
+        return;
+    }
     const int s = blockIdx.x;
     if (done[s]) return;
     double *Hs = H + (int64_t)s * (m + 1) * m;
@@ -523,12 +587,9 @@ __global__ __launch_bounds__(kFinThreads) void k_gm_givens(int32_t nsys, int j, 
         sc[i] = i < j ? c[i] : 0.0;
         ss[i] = i < j ? sv[i] : 0.0;
     }
-    __shared__ double sh[kFinThreads / 64];
-    double ww[1];
     sum_items<1>(partial, n_items, {slot}, item_off[s], item_off[s + 1], sh, ww);              // (a barrier inside)
     const double hn = sqrt(ww[0]);
     if (threadIdx.x == 0) {
-        hn_out[(int64_t)s * (m + 1)] = hn;
         double a = sH[0];
         for (int i = 0; i < j; ++i) {
             const double b = sH[i + 1];
@@ -1157,7 +1218,6 @@ int fgmres(cbs_system *h, const double *b, double *x, bool tr, std::vector<int> 
     const dim3 G(h->n_items), B(kVecThreads), GS(nsys), BS(kFinThreads);
     const int wslot = m + 1;                      // partials of (w, w) after the orthogonalisation
     double *coef = h->yv.get() + (int64_t)nsys * (m + 1);       // (m+1) per system
-    double *hn = coef + (int64_t)nsys * (m + 1);                // 1 per system (stride m+1)
     status.assign(nsys, CBS_NOT_CONVERGED);
     HostView hv;
     int it = 0;
@@ -1180,7 +1240,7 @@ int fgmres(cbs_system *h, const double *b, double *x, bool tr, std::vector<int> 
             if (hv.state[s]) status[s] = CBS_OK; else all_done = false;
         }
         if (all_done || it >= o.max_iter) break;
-        hipLaunchKernelGGL(k_scale, G, B, 0, st, items, h->done.get(), h->scal.get() + S_RHO * nsys, 1, r, V);
+        hipLaunchKernelGGL(k_scale, G, B, 0, st, items, h->done.get(), h->scal.get() + S_RHO * nsys, r, V);
         int j = 0;
         for (; j < m && it < o.max_iter; ++j) {
             double *vj = V + j * ld, *zj = flexible ? Z + j * ld : h->ph.get();
@@ -1189,21 +1249,18 @@ int fgmres(cbs_system *h, const double *b, double *x, bool tr, std::vector<int> 
             // classical Gram-Schmidt; a second pass re-orthogonalises the
             // systems whose w lost more than 90% of its norm in the first
             int32_t *skip = h->flags.get() + 4 * nsys;
-            for (int pass = 0; pass < 2; ++pass) {
-                const int32_t *mask = pass == 0 ? h->done.get() : skip;
-                const int ww = pass == 0 ? 1 : 0;
-                hipLaunchKernelGGL(k_mdot, dim3(h->n_items, cdiv(j + 1 + ww, kBasisGroup)), B, 0, st, items,
-                                   h->n_items, mask, j, ld, V, w, h->partial.get(), ww);
-                hipLaunchKernelGGL(k_mdot_fin, GS, dim3(kMdotFinThreads), 0, st, j, m, h->item_off.get(), h->n_items,
-                                   h->partial.get(), mask, h->H.get(), coef, pass, pass == 0 ? skip : nullptr);
-                hipLaunchKernelGGL(k_maxpy, G, B, 0, st, items, h->n_items, mask, j, m, ld, V, coef, w,
-                                   h->partial.get(), wslot);
-            }
-            hipLaunchKernelGGL(k_gm_givens, GS, BS, 0, st, nsys, j, m, h->item_off.get(), h->n_items,
-                               h->partial.get(), wslot, h->scal.get(), h->H.get(), h->cs.get(), h->sn.get(),
-                               h->gvec.get(), h->done.get(), h->flags.get() + 3 * nsys, iters, tol2, hn,
-                               h->flags.get(), hm);
-            hipLaunchKernelGGL(k_scale, G, B, 0, st, items, h->done.get(), hn, m + 1, w, V + (j + 1) * ld);
+            hipLaunchKernelGGL(k_mdot, dim3(h->n_items, cdiv(j + 2, kBasisGroup)), B, 0, st, items, h->n_items,
+                               h->done.get(), j, ld, V, w, h->partial.get());
+            hipLaunchKernelGGL(k_mdot_fin, GS, dim3(kMdotFinThreads), 0, st, j, m, h->item_off.get(), h->n_items,
+                               h->partial.get(), h->done.get(), h->H.get(), coef, skip);
+            hipLaunchKernelGGL(k_maxpy, G, B, 0, st, items, h->n_items, h->done.get(), skip, j, m, ld, V, coef, w,
+                               h->partial.get(), wslot);
+            hipLaunchKernelGGL(k_maxpy_again, G, B, 0, st, items, h->item_off.get(), h->n_items, skip, j, m, ld, V,
+                               h->H.get(), w, h->partial.get(), wslot);
+            hipLaunchKernelGGL(k_gm_givens, dim3(nsys + h->n_items), BS, 0, st, nsys, j, m, items, h->item_off.get(),
+                               h->n_items, h->partial.get(), wslot, h->scal.get(), h->H.get(), h->cs.get(),
+                               h->sn.get(), h->gvec.get(), h->done.get(), h->flags.get() + 3 * nsys, iters, tol2,
+                               h->flags.get(), hm, w, V + (j + 1) * ld);
             LAUNCHCHK();
             ++it;
             if ((it % every) == 0) {
@@ -1265,7 +1322,7 @@ void alloc_krylov(cbs_system *h) {
         h->gvec.ensure((size_t)nsys * (mr + 1));
         h->cs.ensure((size_t)nsys * (mr + 1));
         h->sn.ensure((size_t)nsys * (mr + 1));
-        h->yv.ensure((size_t)nsys * (mr + 1) * 3);
+        h->yv.ensure((size_t)nsys * (mr + 1) * 2);
     }
     if (!h->h_state) {
         // written by the scalar kernels, read after a synchronisation
