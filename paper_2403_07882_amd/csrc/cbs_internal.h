@@ -302,6 +302,7 @@ struct cbs_system {
     DArr<double> r, rh, p, v, ph, s, sh, t, w;
     DArr<double> V, Z, H, gvec, cs, sn, yv;      // FGMRES
     DArr<double> scal, partial;                  // per-system scalars, reduction partials
+    DArr<double> dpart;                          // partials that a product of the Krylov loop leaves (mode 5)
     DArr<int32_t> done, flags;                   // per-system converged / breakdown flags
     DArr<Item> items;                            // element ranges for level-0 vectors
     int32_t n_items = 0;
@@ -390,6 +391,9 @@ void gradient(cbs_system *h, const double *lam, const double *x, double *gd, dou
 // the first post-smoothing sweep.
 // Modes 2 and 4 with y64 != nullptr write the result widened to FP64 into y64
 // instead of y.
+// Mode 5 (FP64): A x with the workgroups' sums of b y and y y in y64, two rows
+// of rows_workgroups(S).
+int32_t rows_workgroups(const SellView &S);
 template <typename TV, typename TX>
 void launch_rows(int mode, int n, const SellView &S, const TV *val, const TX *x, const TX *b, TX *y,
                  const double *Dinv, double omega, hipStream_t st, TX *aux = nullptr,

@@ -84,6 +84,30 @@ __device__ inline void load_xc(const TX *__restrict__ x, int64_t j, const int32_
     }
 }
 
+// Sums of a and c over the workgroup (n wavefronts) -> out[blockIdx.x] and
+// out[gridDim.x + blockIdx.x], in a fixed order.
+template <int n>
+__device__ inline void wg_two_sums(double a, double c, double *__restrict__ out) {
+    __shared__ double sh[2 * n];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o, 64);
+        c += __shfl_xor(c, o, 64);
+    }
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    if (lane == 0) {
+        sh[2 * wid] = a;
+        sh[2 * wid + 1] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < n; ++w) v += sh[2 * w + threadIdx.x];
+        out[threadIdx.x * gridDim.x + blockIdx.x] = v;
+    }
+}
+
 // mode 0: y = A x; 1: y = b - A x; 2: y = x + w Dinv (b - A x); 3: y = w Dinv b
 // (and aux = Dinv b when aux is given); 4: y = x + w (b - x - A x), the sweep
 // of mode 2 on the row-scaled off-diagonal values Dinv_i A_ij (j != i; the
@@ -92,6 +116,9 @@ __device__ inline void load_xc(const TX *__restrict__ x, int64_t j, const int32_
 // (C = 16 on level 0, 8 on coarser levels) read C consecutive blocks; U steps
 // are loaded before they are summed, and the sums run in the row's column
 // order.
+// mode 5: y = A x as mode 0, and into y64 the workgroup's sums of b y and of
+// y y (gridDim.x of each): the two products that follow A x in the Krylov
+// loop, for which y would be read again.
 // Modes 2 and 4 with PRO: x is first corrected by the prolongated coarse
 // solution (x + P e, pagg = aggregate map, pe = e), see load_xc.
 template <int n, typename TV, typename TX, int MODE, int U, bool NT, bool PRO>
@@ -188,8 +215,9 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
         __syncthreads();
         acc = sres[t];
     }
-    if (MODE == 0) {
+    if (MODE == 0 || MODE == 5) {
         if (act) y[o] = (TX)acc;
+        if constexpr (MODE == 5) wg_two_sums<n>(act ? (double)bo * (double)acc : 0.0, act ? (double)acc * (double)acc : 0.0, y64);
         return;
     }
     A res = 0;
@@ -280,11 +308,11 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
     __shared__ A sres[R * n];
     spart[t] = acc;
     __syncthreads();
+    A sum = 0;
     if (kk == 0) {
-        A sum = 0;
 #pragma unroll
         for (int q = 0; q < SP; ++q) sum += spart[lr * n * SP + q * n + r];
-        if (MODE == 0) {
+        if (MODE == 0 || MODE == 5) {
             if (act) y[o] = (TX)sum;
         } else {
             if (PRO && act) xo = xo + pe[(int64_t)ai * n + r];
@@ -297,6 +325,10 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
                 sres[lr * n + r] = res;
             }
         }
+    }
+    if constexpr (MODE == 5) {
+        const bool on = act && kk == 0;
+        wg_two_sums<n>(on ? (double)bo * (double)sum : 0.0, on ? (double)sum * (double)sum : 0.0, y64);
     }
     if (MODE != 2) return;
     __syncthreads();
@@ -408,6 +440,9 @@ void rows_n(int mode, const SellView &S, const TV *val, const TX *x, const TX *b
         case 2: rows_nm<n, TV, TX, 2>(S, val, x, b, y, Dinv, omega, aux, pagg, pe, y64, st); break;
         case 3: rows_nm<n, TV, TX, 3>(S, val, x, b, y, Dinv, omega, aux, pagg, pe, y64, st); break;
         case 4: rows_nm<n, TV, TX, 4>(S, val, x, b, y, Dinv, omega, aux, pagg, pe, y64, st); break;
+        case 5:
+            if constexpr (sizeof(TX) == 8) rows_nm<n, TV, TX, 5>(S, val, x, b, y, Dinv, omega, aux, pagg, pe, y64, st);
+            break;
     }
 }
 
@@ -983,6 +1018,8 @@ __global__ void k_block_apply(int32_t N, const double *__restrict__ Dinv, const 
 }
 
 }  // namespace
+
+int32_t rows_workgroups(const SellView &S) { return (int32_t)cdiv((int64_t)S.N * std::max<int>(1, S.sched.split), 64); }
 
 template <typename TV, typename TX>
 void launch_rows(int mode, int n, const SellView &S, const TV *val, const TX *x, const TX *b, TX *y,
