@@ -80,7 +80,7 @@ int32_t item_elems(int64_t total) {
 
 void build_items(cbs_system *h) {
     std::vector<Item> items;
-    const int64_t len = item_elems((int64_t)h->N * h->n);
+    const int64_t len = item_elems((int64_t)h->N * h->n) / h->n * h->n;      // whole block rows
     h->items_per_sys_off.assign(h->n_sys + 1, 0);
     for (int s = 0; s < h->n_sys; ++s) {
         const int64_t b = h->cell_off[s] * h->n, e = h->cell_off[s + 1] * h->n;

@@ -535,5 +535,6 @@ void invalidate_graphs(cbs_system *h);
 void launch_copy(int64_t m, const double *a, double *b, hipStream_t st);
 template <typename T>
 void launch_fill(int64_t m, T *a, hipStream_t st);
-void precond_apply(cbs_system *h, const double *r, double *z, bool transposed);
+// begun: the zero-guess sweep on r has been made by the kernel that formed r
+void precond_apply(cbs_system *h, const double *r, double *z, bool transposed, bool begun = false);
 void spmv64(cbs_system *h, const double *x, double *y, bool transposed);

@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace {
 
@@ -192,7 +193,100 @@ __global__ __launch_bounds__(kFinThreads) void k_fin(int phase, int32_t nsys, co
     publish_state(hm, s, nsys, done, flags, iters);
 }
 
-// p = r + beta (p - omega v),  beta = (rho / rho0) (alpha / omega)
+// The preconditioner's zero-guess block-Jacobi sweep x = omega Dinv v, made by
+// the kernel that forms the vector v it starts from: one launch less per
+// application, and v is not read again.  b keeps v rounded to T (null in FP64,
+// where the cycle reads v itself), c = Dinv v if it is wanted; the roundings are
+// those of the sweep's own kernels.
+template <typename T>
+struct SweepOut {
+    T *b, *x, *c;
+    const double *Dinv;
+    double omega;
+};
+
+// Work items start at a block row, so a workgroup takes kVecThreads / n whole
+// rows at a time.
+template <int n> constexpr int kTile = kVecThreads / n * n;
+
+// One item of v and the sweep on it, kTiles tiles at a time so that their loads
+// are in flight together: load(e, raw) reads what element e is made of, form(e,
+// raw) makes it, stores it and returns it.  sb holds a step's values, others
+// from step to step, so that one barrier is enough.
+constexpr int kTiles = 2;
+template <int n, typename T> using TileLds = T[2][kTiles][kVecThreads];
+
+template <int n, typename T, typename Load, typename Form>
+__device__ inline void item_sweep0(const Item &it, const SweepOut<T> &z, TileLds<n, T> &sb, Load load, Form form) {
+    const int t = threadIdx.x;
+    int turn = 0;
+    for (int64_t base = it.beg; base < it.end; base += kTiles * kTile<n>, turn ^= 1) {
+        double raw[kTiles][3], di[kTiles][n];
+        bool act[kTiles];
+#pragma unroll
+        for (int u = 0; u < kTiles; ++u) {
+            const int64_t e = base + u * kTile<n> + t;
+            act[u] = t < kTile<n> && e < it.end;
+            if (!act[u]) continue;
+            load(e, raw[u]);
+            const double *d = z.Dinv + e * n;              // (element e is a row of a block: n values)
+#pragma unroll
+            for (int k = 0; k < n; ++k) di[u][k] = d[k];
+        }
+#pragma unroll
+        for (int u = 0; u < kTiles; ++u) {
+            if (!act[u]) continue;
+            const int64_t e = base + u * kTile<n> + t;
+            const T bv = (T)form(e, raw[u]);
+            sb[turn][u][t] = bv;
+            if (z.b) z.b[e] = bv;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kTiles; ++u) {
+            if (!act[u]) continue;
+            const int64_t e = base + u * kTile<n> + t;
+            const T *row = sb[turn][u] + t / n * n;
+            double s = 0.0;
+#pragma unroll
+            for (int k = 0; k < n; ++k) s += di[u][k] * (double)row[k];
+            z.x[e] = (T)((T)0 + (T)(z.omega * s));
+            if (z.c) z.c[e] = (T)s;
+        }
+    }
+}
+
+// p = r + beta (p - omega v),  beta = (rho / rho0) (alpha / omega), and the
+// zero-guess sweep on p (on the old p for a system that is through)
+template <int n, typename T>
+__global__ __launch_bounds__(kVecThreads) void k_p_update_sweep(const Item *__restrict__ items, int32_t nsys,
+                                                                const int32_t *__restrict__ done,
+                                                                const double *__restrict__ scal,
+                                                                const int32_t *__restrict__ flags,
+                                                                const double *__restrict__ r, double *__restrict__ p,
+                                                                const double *__restrict__ v, SweepOut<T> z) {
+    __shared__ TileLds<n, T> sb;
+    const Item it = items[blockIdx.x];
+    const int s = it.sys;
+    const bool on = !(done[s] || (flags[s] & kFlagBreak));
+    const double omega = SC(S_OMEGA);
+    const double beta = (SC(S_RHO) / SC(S_RHO0)) * (SC(S_ALPHA) / omega);
+    item_sweep0<n, T>(
+        it, z, sb,
+        [&](int64_t e, double (&raw)[3]) {
+            raw[0] = p[e];
+            raw[1] = r[e];
+            raw[2] = v[e];
+        },
+        [&](int64_t e, const double (&raw)[3]) {
+            if (!on) return raw[0];
+            const double pe = raw[1] + beta * (raw[0] - omega * raw[2]);
+            p[e] = pe;
+            return pe;
+        });
+}
+
+// p alone, for the other preconditioners
 __global__ __launch_bounds__(kVecThreads) void k_p_update(const Item *__restrict__ items, int32_t nsys,
                                                           const int32_t *__restrict__ done,
                                                           const double *__restrict__ scal,
@@ -225,36 +319,49 @@ struct DotSrc {
 // alpha = rho / (rhat, v);  s = r - alpha v, and partials of (s, s) for the
 // half-step test.  A breakdown ends the iteration's later parts, so it is
 // published here.
-__global__ __launch_bounds__(kVecThreads) void k_s_update(const Item *__restrict__ items,
-                                                          const int32_t *__restrict__ item_off, int32_t n_items,
-                                                          int32_t nsys, const int32_t *done, double *scal,
-                                                          int32_t *flags, int32_t *iters, const double *__restrict__ r,
+struct AlphaStep {
+    const int32_t *item_off, *done;
+    double *scal;
+    int32_t *flags, *iters;
+    DotSrc ds;
+    HostMirror hm;
+};
+
+// alpha of system s, or false at a breakdown (the whole workgroup); sh: 4 doubles
+__device__ inline bool alpha_step(const AlphaStep &a, int s, int nsys, double *sh, double &alpha) {
+    double *scal = a.scal;
+    const int32_t i0 = a.item_off[s];
+    const double rho = SC(S_RHO), rr = SC(S_RR);
+    double rv[1];
+    sum_items<1>(a.ds.p, a.ds.stride, {0}, a.ds.count ? 0 : i0, a.ds.count ? a.ds.count : a.item_off[s + 1], sh, rv);
+    const bool bad = rv[0] == 0.0 || !isfinite(rv[0]) || fabs(rv[0]) < 1e-300 * fmax(rr, 1e-300);
+    alpha = bad ? 0.0 : rho / rv[0];
+    if ((int32_t)blockIdx.x == i0 && threadIdx.x == 0) {
+        SC(S_RV) = rv[0];
+        SC(S_ALPHA) = alpha;
+        a.iters[s] += 1;
+        if (bad) {
+            a.flags[s] |= kFlagBreak;
+            publish_state(a.hm, s, nsys, a.done, a.flags, a.iters);
+        }
+    }
+    return !bad;
+}
+
+__global__ __launch_bounds__(kVecThreads) void k_s_update(const Item *__restrict__ items, int32_t n_items,
+                                                          int32_t nsys, AlphaStep a, const double *__restrict__ r,
                                                           const double *__restrict__ v, double *__restrict__ sv,
-                                                          double *partial, DotSrc ds, HostMirror hm) {
+                                                          double *__restrict__ partial) {
     __shared__ double red[kVecThreads / 64], sh[kFinThreads / 64];
     const Item it = items[blockIdx.x];
     const int s = it.sys;
     double s0 = 0.0;
-    if (!done[s] && !(flags[s] & kFlagBreak)) {
-        const int32_t i0 = item_off[s];
+    if (!a.done[s] && !(a.flags[s] & kFlagBreak)) {
         int64_t e = it.beg + threadIdx.x;
         const bool have = e < it.end;
         double re = have ? r[e] : 0.0, ve = have ? v[e] : 0.0;       // (with the partials)
-        const double rho = SC(S_RHO), rr = SC(S_RR);
-        double rv[1];
-        sum_items<1>(ds.p, ds.stride, {0}, ds.count ? 0 : i0, ds.count ? ds.count : item_off[s + 1], sh, rv);
-        const bool bad = rv[0] == 0.0 || !isfinite(rv[0]) || fabs(rv[0]) < 1e-300 * fmax(rr, 1e-300);
-        const double alpha = bad ? 0.0 : rho / rv[0];
-        if ((int32_t)blockIdx.x == i0 && threadIdx.x == 0) {
-            SC(S_RV) = rv[0];
-            SC(S_ALPHA) = alpha;
-            iters[s] += 1;
-            if (bad) {
-                flags[s] |= kFlagBreak;
-                publish_state(hm, s, nsys, done, flags, iters);
-            }
-        }
-        if (!bad && have)
+        double alpha;
+        if (alpha_step(a, s, nsys, sh, alpha) && have)
             for (;;) {
                 const double se = re - alpha * ve;
                 sv[e] = se;
@@ -265,6 +372,36 @@ __global__ __launch_bounds__(kVecThreads) void k_s_update(const Item *__restrict
                 ve = v[e];
             }
     }
+    s0 = block_sum(s0, red);
+    if (threadIdx.x == 0) partial[(int64_t)kSlotSS * n_items + blockIdx.x] = s0;
+}
+
+// the same and the zero-guess sweep on s
+template <int n, typename T>
+__global__ __launch_bounds__(kVecThreads) void k_s_update_sweep(const Item *__restrict__ items, int32_t n_items,
+                                                                int32_t nsys, AlphaStep a,
+                                                                const double *__restrict__ r,
+                                                                const double *__restrict__ v, double *__restrict__ sv,
+                                                                double *__restrict__ partial, SweepOut<T> z) {
+    __shared__ double red[kVecThreads / 64], sh[kFinThreads / 64];
+    __shared__ TileLds<n, T> sb;
+    const Item it = items[blockIdx.x];
+    const int s = it.sys;
+    double alpha = 0.0, s0 = 0.0;
+    const bool on = !a.done[s] && !(a.flags[s] & kFlagBreak) && alpha_step(a, s, nsys, sh, alpha);
+    item_sweep0<n, T>(
+        it, z, sb,
+        [&](int64_t e, double (&raw)[3]) {
+            raw[0] = on ? r[e] : sv[e];
+            raw[1] = v[e];
+        },
+        [&](int64_t e, const double (&raw)[3]) {
+            if (!on) return raw[0];
+            const double se = raw[0] - alpha * raw[1];
+            sv[e] = se;
+            s0 += se * se;
+            return se;
+        });
     s0 = block_sum(s0, red);
     if (threadIdx.x == 0) partial[(int64_t)kSlotSS * n_items + blockIdx.x] = s0;
 }
@@ -519,15 +656,18 @@ __global__ __launch_bounds__(kVecThreads) void k_maxpy_again(const Item *__restr
     if (threadIdx.x == 0) partial[(int64_t)slot * n_items + blockIdx.x] = s0;
 }
 
+// y = a / d over one item
+__device__ inline void item_scale(const Item &it, double d, const double *__restrict__ a, double *__restrict__ y) {
+    const double f = d > 0.0 ? 1.0 / d : 0.0;
+    for (int64_t e = it.beg + threadIdx.x; e < it.end; e += kVecThreads) y[e] = a[e] * f;
+}
+
 // V_0 = r / beta
 __global__ __launch_bounds__(kVecThreads) void k_scale(const Item *__restrict__ items, const int32_t *__restrict__ done,
                                                        const double *__restrict__ nrm, const double *__restrict__ a,
                                                        double *__restrict__ y) {
     const Item it = items[blockIdx.x];
-    if (done[it.sys]) return;
-    const double d = nrm[it.sys];
-    const double f = d > 0.0 ? 1.0 / d : 0.0;
-    for (int64_t e = it.beg + threadIdx.x; e < it.end; e += kVecThreads) y[e] = a[e] * f;
+    if (!done[it.sys]) item_scale(it, nrm[it.sys], a, y);
 }
 
 // Restart start: beta = ||r||, g = (beta, 0, ...), converged check.
@@ -584,8 +724,7 @@ __global__ __launch_bounds__(kFinThreads) void k_gm_givens(int32_t nsys, int j, 
         const Item it = items[blockIdx.x - nsys];
         if (done[it.sys]) return;
         sum_items<1>(partial, n_items, {slot}, item_off[it.sys], item_off[it.sys + 1], sh, ww);
-        const double d = sqrt(ww[0]), f = d > 0.0 ? 1.0 / d : 0.0;
-        for (int64_t e = it.beg + threadIdx.x; e < it.end; e += kVecThreads) vnext[e] = w[e] * f;
+        item_scale(it, sqrt(ww[0]), w, vnext);
         return;
     }
     const int s = blockIdx.x;
@@ -804,9 +943,30 @@ SellView position_range(SellView S, int32_t p0, int32_t p1) {
 // and b the level's right side, both left by an earlier cycle on this level,
 // whose zero-guess sweep also left c = D^{-1} b behind.  This is the second
 // run of a W-cycle's coarse correction.
+//
+// begun: the zero-guess sweep has been made (x of it in cycle_start, b and c =
+// D^{-1} b as this level keeps them), fused into the launch that formed b.
+template <typename T>
+T *cycle_start(cbs_system *h, int l, T *x) {
+    const int nu1 = std::max(0, h->opt.pre_sweeps), nu2 = std::max(0, h->opt.post_sweeps);
+    const int switches = (nu1 >= 1 ? nu1 - 1 : 0) + nu2;
+    return switches % 2 == 0 ? x : vptr<T>(h->lev[l].vt);
+}
+
+// a level that starts with a zero-guess block-Jacobi sweep
+bool starts_with_sweep0(const cbs_system *h, int l) {
+    const Level &L = h->lev[l];
+    return l < (int)h->lev.size() - 1 && !(l > 0 && l == h->tail.level) && !L.dilu && !L.sgs && h->opt.pre_sweeps >= 1;
+}
+
+// FP32 sweeps run on the row-scaled values Dinv A (D^{-T} A^T in the transposed
+// solve) against c = Dinv b, which the zero-guess sweep leaves behind
+template <typename T>
+bool scaled_sweeps(const Level &L, bool tr) { return sizeof(T) == sizeof(float) && (tr ? L.scaledT : L.scaled); }
+
 template <typename T>
 void vcycle(cbs_system *h, bool tr, int l, T *b, T *x, const T *rfine, const double *b64 = nullptr,
-            double *x64 = nullptr, bool zero = true) {
+            double *x64 = nullptr, bool zero = true, bool begun = false) {
     hipStream_t st = h->stream;
     const cbs_options &o = h->opt;
     const int n = h->n;
@@ -817,9 +977,9 @@ void vcycle(cbs_system *h, bool tr, int l, T *b, T *x, const T *rfine, const dou
     const double om = level_omega(o, l);
     constexpr bool fp32 = sizeof(T) == sizeof(float);
     const bool bj = l < nlev - 1 && !L.dilu && !L.sgs;
-    const bool fuse_in = fp32 && b64 && bj && nu1 >= 1;
+    const bool fuse_in = fp32 && b64 && bj && nu1 >= 1 && !begun;
     const bool fuse_out = fp32 && x64 && bj && nu2 >= 1;
-    if (b64 && !fuse_in) launch_cast<double, T>(m, b64, b, st);
+    if (b64 && !fuse_in && !begun) launch_cast<double, T>(m, b64, b, st);
     auto finish = [&] {
         if (x64 && !fuse_out) launch_cast<T, double>(m, x, x64, st);
     };
@@ -881,14 +1041,10 @@ void vcycle(cbs_system *h, bool tr, int l, T *b, T *x, const T *rfine, const dou
         finish();
         return;
     }
-    const int switches = zero ? (nu1 >= 1 ? nu1 - 1 : 0) + nu2 : nu1 + nu2;
-    T *cur = (switches % 2 == 0) ? x : tmp;
+    T *cur = zero ? cycle_start<T>(h, l, x) : (nu1 + nu2) % 2 == 0 ? x : tmp;
     T *oth = (cur == x) ? tmp : x;
     if (!zero && cur != x) launch_cast<T, T>(m, x, cur, st);
-    // FP32 sweeps run on the row-scaled values Dinv A (D^{-T} A^T in the
-    // transposed solve) against c = Dinv b, which the zero-guess sweep leaves
-    // behind
-    const bool scaled = fp32 && (tr ? L.scaledT : L.scaled);
+    const bool scaled = scaled_sweeps<T>(L, tr);
     const T *sval = scaled ? reinterpret_cast<const T *>(tr ? L.sod.v32T.get() : L.sod.v32.get()) : nullptr;
     T *c = scaled ? vptr<T>(L.vc) : nullptr;
     // pagg/pe: sweep from x + P e (the prolongation fused into the sweep);
@@ -906,7 +1062,8 @@ void vcycle(cbs_system *h, bool tr, int l, T *b, T *x, const T *rfine, const dou
             std::swap(cur, oth);
         }
     } else if (nu1 >= 1) {
-        if (fuse_in) {
+        if (begun) {
+        } else if (fuse_in) {
             if constexpr (fp32)
                 launch_cast_sweep0(n, L.N, b64, b, Dinv, om, cur, c, st);
         } else if (rfine) {
@@ -954,7 +1111,7 @@ static void residual64(cbs_system *h, const double *b, const double *x, double *
     launch_rows<double, double>(1, h->n, L0.sell.view(), val, x, b, r, nullptr, 0.0, h->stream);
 }
 
-void precond_apply(cbs_system *h, const double *r, double *z, bool tr) {
+void precond_apply(cbs_system *h, const double *r, double *z, bool tr, bool begun) {
     const int n = h->n;
     const int64_t m = (int64_t)h->N * n;
     hipStream_t st = h->stream;
@@ -982,10 +1139,49 @@ void precond_apply(cbs_system *h, const double *r, double *z, bool tr) {
     if (h->opt.precision == CBS_PRECISION_MIXED) {
         Level &L0 = h->lev[0];
         float *b32 = vptr<float>(L0.vb), *x32 = vptr<float>(L0.vx);
-        vcycle<float>(h, tr, 0, b32, x32, nullptr, r, z);
+        vcycle<float>(h, tr, 0, b32, x32, nullptr, r, z, true, begun);
     } else {
-        vcycle<double>(h, tr, 0, const_cast<double *>(r), z, nullptr);
+        vcycle<double>(h, tr, 0, const_cast<double *>(r), z, nullptr, nullptr, nullptr, true, begun);
     }
+}
+
+// The sweep with which precond_apply(., z) begins on T, for the kernel that
+// forms its argument; see SweepOut.
+template <typename T>
+static SweepOut<T> sweep_out(cbs_system *h, double *z, bool tr) {
+    Level &L0 = h->lev[0];
+    constexpr bool fp32 = sizeof(T) == sizeof(float);
+    T *x = fp32 ? vptr<T>(L0.vx) : reinterpret_cast<T *>(z);
+    return SweepOut<T>{fp32 ? vptr<T>(L0.vb) : nullptr, cycle_start<T>(h, 0, x),
+                       scaled_sweeps<T>(L0, tr) ? vptr<T>(L0.vc) : nullptr, tr ? L0.DinvT.get() : L0.Dinv.get(),
+                       level_omega(h->opt, 0)};
+}
+
+// f(n, SweepOut) with the block size as a constant where the preconditioner's
+// application to z begins with a zero-guess sweep; false where it does not, and
+// for vectors of kSweepUpdateElems values on, where the update in steps with a
+// barrier each falls behind by more than the launch.  960 rows: 2,440 -> 2,380
+// us a step, 8,000: 3,280 -> 3,240, 55k: 8,590 -> 8,535, 219k (1.1M values):
+// 11.97 -> 11.98 ms, 24 systems of 355k rows together (1.8M): 24.55 -> 24.18;
+// 1M rows (4M values) would go from 59.53 to 59.79.
+constexpr int64_t kSweepUpdateElems = 2 << 20;
+
+template <typename F>
+static bool with_sweep0(cbs_system *h, double *z, bool tr, F f) {
+    if (h->opt.precond != CBS_PREC_AMG || !starts_with_sweep0(h, 0) || (int64_t)h->N * h->n >= kSweepUpdateElems)
+        return false;
+    auto run = [&](auto out) {
+        switch (h->n) {
+            case 1: f(std::integral_constant<int, 1>(), out); break;
+            case 2: f(std::integral_constant<int, 2>(), out); break;
+            case 3: f(std::integral_constant<int, 3>(), out); break;
+            case 4: f(std::integral_constant<int, 4>(), out); break;
+            case 5: f(std::integral_constant<int, 5>(), out); break;
+        }
+    };
+    if (h->opt.precision == CBS_PRECISION_MIXED) run(sweep_out<float>(h, z, tr));
+    else run(sweep_out<double>(h, z, tr));
+    return true;
 }
 
 // ------------------------------------------------------------------ drivers
@@ -1047,11 +1243,20 @@ void bicg_half1(cbs_system *h, bool tr) {
     double *ph = h->ph.get(), *sv = h->s.get();
     const Item *items = h->items.get();
     const dim3 G(h->n_items), B(kVecThreads);
-    hipLaunchKernelGGL(k_p_update, G, B, 0, st, items, nsys, h->done.get(), h->scal.get(), h->flags.get(), r, p, v);
-    precond_apply(h, p, ph, tr);
+    const bool begun = with_sweep0(h, ph, tr, [&](auto nc, auto z) {
+        hipLaunchKernelGGL((k_p_update_sweep<nc, std::remove_pointer_t<decltype(z.x)>>), G, B, 0, st, items, nsys,
+                           h->done.get(), h->scal.get(), h->flags.get(), r, p, v, z);
+    });
+    if (!begun)
+        hipLaunchKernelGGL(k_p_update, G, B, 0, st, items, nsys, h->done.get(), h->scal.get(), h->flags.get(), r, p, v);
+    precond_apply(h, p, ph, tr, begun);
     const DotSrc ds = spmv_dots(h, ph, v, rh, nullptr, tr);
-    hipLaunchKernelGGL(k_s_update, G, B, 0, st, items, h->item_off.get(), h->n_items, nsys, h->done.get(),
-                       h->scal.get(), h->flags.get(), iters_ptr(h), r, v, sv, h->partial.get(), ds, mirror(h));
+    const AlphaStep a{h->item_off.get(), h->done.get(), h->scal.get(), h->flags.get(), iters_ptr(h), ds, mirror(h)};
+    if (!with_sweep0(h, h->sh.get(), tr, [&](auto nc, auto z) {
+            hipLaunchKernelGGL((k_s_update_sweep<nc, std::remove_pointer_t<decltype(z.x)>>), G, B, 0, st, items,
+                               h->n_items, nsys, a, r, v, sv, h->partial.get(), z);
+        }))
+        hipLaunchKernelGGL(k_s_update, G, B, 0, st, items, h->n_items, nsys, a, r, v, sv, h->partial.get());
     LAUNCHCHK();
 }
 
@@ -1069,7 +1274,8 @@ void bicg_finish(cbs_system *h, double *x, const DotSrc &ds) {
 
 void bicg_half2(cbs_system *h, double *x, bool tr) {
     double *sv = h->s.get(), *sh = h->sh.get(), *t = h->t.get();
-    precond_apply(h, sv, sh, tr);
+    // (the first half began it, and nothing has used the cycle's vectors since)
+    precond_apply(h, sv, sh, tr, with_sweep0(h, sh, tr, [](auto, auto) {}));
     bicg_finish(h, x, spmv_dots(h, sh, t, sv, t, tr));
 }
 
