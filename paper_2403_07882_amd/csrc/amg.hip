@@ -391,13 +391,17 @@ __global__ void k_rap_maxc(int32_t nc, const int32_t *aptr, const int32_t *amem,
 // the grouped list were three passes, the first a chain of LDS reads: 8,000
 // cells 5x5 38 us per level, now 19 us; level 0 of 1M cells 4x4 612 us, now
 // 358 us, 3.4 TB/s of its blocks in and out.)
+// slot: where in val the block of entry k is (null: at k); a level that keeps
+// no values of its own is read through it, in rows that are together there too
+// (219k rows 5x5: a copy in this order took 137 us before this
+// kernel, which takes 140 us through the slots and 129 without).
 template <int n, int PASS>
 __global__ __launch_bounds__(64) void k_rap(int32_t nc, int32_t cap, const int32_t *__restrict__ aptr,
                                             const int32_t *__restrict__ amem, const int32_t *__restrict__ rp,
                                             const int32_t *__restrict__ col, const double *__restrict__ val,
                                             const int32_t *__restrict__ agg, int32_t *cnt,
                                             const int32_t *__restrict__ rpc, int32_t *colc, double *valc,
-                                            int32_t *flag) {
+                                            int32_t *flag, const int32_t *__restrict__ slot) {
     constexpr int nn = n * n;
     typedef int32_t i4 __attribute__((ext_vector_type(4)));
     extern __shared__ __align__(16) int32_t rap_lds[];
@@ -443,7 +447,7 @@ __global__ __launch_bounds__(64) void k_rap(int32_t nc, int32_t cap, const int32
             }
             const int32_t k = sMk[lo] + (q - sMo[lo]);
             sJ[q] = agg[col[k]];
-            sK[q] = k;
+            sK[q] = slot ? slot[k] : k;
         }
     } else {
         for (int32_t m = m0; m < m0 + nm; ++m) {
@@ -451,7 +455,7 @@ __global__ __launch_bounds__(64) void k_rap(int32_t nc, int32_t cap, const int32
             const int32_t kb = rp[i], len = rp[i + 1] - kb;
             for (int32_t e = lane; e < len; e += 64) {
                 const int32_t q = c + e;
-                if (q < cap) { sJ[q] = agg[col[kb + e]]; sK[q] = kb + e; }
+                if (q < cap) { sJ[q] = agg[col[kb + e]]; sK[q] = slot ? slot[kb + e] : kb + e; }
             }
             c += len;
         }
@@ -1280,7 +1284,7 @@ void strength_n(int32_t N, const int32_t *rp, const int32_t *col, const int32_t 
 template <int n>
 void rap_n(int pass, int32_t nc, int32_t cap, const int32_t *aptr, const int32_t *amem, const int32_t *rp,
            const int32_t *col, const double *val, const int32_t *agg, int32_t *cnt, const int32_t *rpc, int32_t *colc,
-           double *valc, int32_t *flag, hipStream_t st) {
+           double *valc, int32_t *flag, const int32_t *slot, hipStream_t st) {
     const size_t lds = sizeof(int32_t) * 4 * (size_t)cap;
     const dim3 g(nc), b(64);
     if (lds > 48 * 1024) {
@@ -1292,10 +1296,10 @@ void rap_n(int pass, int32_t nc, int32_t cap, const int32_t *aptr, const int32_t
     if (nc <= 0) return;
     if (pass == 0)
         hipLaunchKernelGGL((k_rap<n, 0>), g, b, lds, st, nc, cap, aptr, amem, rp, col, val, agg, cnt, rpc, colc, valc,
-                           flag);
+                           flag, slot);
     else
         hipLaunchKernelGGL((k_rap<n, 1>), g, b, lds, st, nc, cap, aptr, amem, rp, col, val, agg, cnt, rpc, colc, valc,
-                           flag);
+                           flag, slot);
 }
 template <int n>
 void dilu_setup_n(const int32_t *rows, int32_t cnt, int c, const int32_t *rp, const int32_t *col, const int32_t *mirror,
@@ -1419,11 +1423,12 @@ void build_members(cbs_system *h, int32_t N, int32_t *agg, const int32_t *a2, DA
 // back here).  nz_bound >= 0: a bound on the coarse block count; the pattern
 // is then sized for it and its count not read back (nz_bound is returned),
 // and a candidate overflow sets bit 8 of *late_flag, which the caller reads
-// later.
+// later.  slot: as in k_rap; a scalar product (n_blk = 1) that builds its
+// pattern takes none.
 int32_t rap_build(cbs_system *h, int n_blk, int32_t nc, const int32_t *aptr, const int32_t *amem, const int32_t *rp,
                   const int32_t *col, const double *val, const int32_t *agg, DArr<int32_t> &rpc, DArr<int32_t> &colc,
                   DArr<double> &valc, bool pattern, int32_t maxc = -1, int64_t nz_bound = -1,
-                  int32_t *late_flag = nullptr) {
+                  int32_t *late_flag = nullptr, const int32_t *slot = nullptr) {
     hipStream_t st = h->stream;
     const bool late = nz_bound >= 0 && late_flag;
     int32_t *flag = late ? late_flag : h->dflag.get();
@@ -1468,7 +1473,7 @@ int32_t rap_build(cbs_system *h, int n_blk, int32_t nc, const int32_t *aptr, con
                                    nullptr, agg, rpc.get(), nullptr, nullptr, nullptr, longq.get(), nlong.get());
         } else
             NSWITCH(n_blk, rap_n, 0, nc, cap, aptr, amem, rp, col, val, agg, rpc.get(), nullptr, nullptr, nullptr,
-                    flag, st);
+                    flag, slot, st);
         LAUNCHCHK();
         scan_exclusive(rpc.get(), rpc.get(), nc, st);
         if (late) {
@@ -1498,7 +1503,7 @@ int32_t rap_build(cbs_system *h, int n_blk, int32_t nc, const int32_t *aptr, con
                                nullptr, rpc.get(), colc.get(), valc.get(), longq.get(), nlong_fill);
     } else
         NSWITCH(n_blk, rap_n, 1, nc, cap, aptr, amem, rp, col, val, agg, nullptr, rpc.get(), colc.get(), valc.get(),
-                flag, st);
+                flag, slot, st);
     LAUNCHCHK();
     return nz;
 }
@@ -1852,8 +1857,9 @@ void amg_setup(cbs_system *h) {
             // reuse: refresh the values of level l+1 with the kept pattern
             Level &C = h->lev[l + 1];
             Level &F = h->lev[l];
-            rap_build(h, n, C.N, F.agg_ptr.get(), F.agg_mem.get(), F.rp, F.col, F.v64, F.agg.get(), C.o_rp, C.o_col,
-                      C.o_v64, false, F.maxc > 0 ? F.maxc : -1);
+            rap_build(h, n, C.N, F.agg_ptr.get(), F.agg_mem.get(), F.rp, F.col, F.lazy_vals ? h->vals.get() : F.v64,
+                      F.agg.get(), C.o_rp, C.o_col, C.o_v64, false, F.maxc > 0 ? F.maxc : -1, -1, nullptr,
+                      F.lazy_vals ? h->perm_sk.get() : nullptr);
             continue;
         }
         // level l is the coarsest
@@ -2188,15 +2194,11 @@ void renumber_hierarchy(cbs_system *h, int32_t *deferred, bool lazy0) {
     h->renumbered = true;
 }
 
-// Level-0 values in the internal numbering after a coefficient update.
-// (a level 0 without its own copy gets one here: the Galerkin product of
-// level 1 in the re-setup reads the internal numbering)
+// Level-0 values in the internal numbering after a coefficient update, where
+// level 0 keeps them.
 void refresh_level0_values(cbs_system *h) {
     Level &L0 = h->lev[0];
-    if (L0.lazy_vals) {
-        L0.o_v64.ensure((size_t)h->nnzb * h->n * h->n);
-        L0.v64 = L0.o_v64.get();
-    }
+    if (L0.lazy_vals) return;
     NSWITCH(h->n, gather_blocks_n, h->nnzb, h->perm_sk.get(), h->vals.get(), L0.o_v64.get(), h->stream);
     LAUNCHCHK();
 }

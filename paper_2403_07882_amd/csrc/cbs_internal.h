@@ -223,11 +223,10 @@ struct Level {
     // internal renumbering: order[i'] = row of the original numbering
     DArr<int32_t> order;
     // level 0 without its own values in the internal numbering (a
-    // block-Jacobi level 0): its sliced copies and block inverses read the
-    // caller's block CSR (h->vals) through slot maps composed with the
-    // renumbering (the patterns' ssrc, and dslot_src for the diagonal
-    // blocks); v64 is then null, or after a values-only re-setup the
-    // internal copy the Galerkin product of level 1 reads
+    // block-Jacobi level 0): its sliced copies, block inverses and Galerkin
+    // product read the caller's block CSR (h->vals) through slot maps composed
+    // with the renumbering (the patterns' ssrc, dslot_src for the diagonal
+    // blocks, perm_sk); v64 is then null
     bool lazy_vals = false;
     DArr<int32_t> dslot_src;
     // transfer to the next level
