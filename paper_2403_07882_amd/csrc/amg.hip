@@ -711,9 +711,12 @@ __global__ __launch_bounds__(256) void k_coarse_inverse(const int32_t *rp, const
 // them), lane c of it columns c and c + 64 (CW).  A row's multiplier is then
 // one lane of its own wavefront; only the pivot candidates, the scaled pivot
 // row and the row it changes places with pass through LDS, and a step costs
-// two barriers.  The serial chain of m steps bounds it: m = 80 took 422 us
-// with [A | I] in LDS and three barriers per step, and takes 218 us; m = 64
-// 106 -> 87 us.
+// two barriers.  The serial chain of m steps bounds it, and in a step the
+// instructions of 16 wavefronts on one CU: the 16 candidates are compared in
+// the lanes of a row, four rotations, instead of one after the other by every
+// wavefront.  m = 80 took 422 us with [A | I] in LDS and three barriers per
+// step, 218 us with 15 comparisons each, and takes 181 us; m = 64 106, 87 and
+// 65 us.
 // The pivot is the largest |a_rk| over rows r >= k, the first such row on ties
 // (NaN entries below the diagonal are passed over, a NaN diagonal makes the
 // matrix singular).  In place, column k holds the inverse's column of the row
@@ -726,6 +729,18 @@ __device__ inline double lane_value(double v, int lane) {      // lane: the same
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
                             __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
+
+// (v, r) of the lane O further round its row of 16, if v is larger there, or
+// equal and r smaller
+template <int O>
+__device__ inline void better_of(double &v, int &r) {
+    constexpr int ror = 0x120 + O;                            // rotate within 16 lanes
+    const double ov = __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), ror, 0xf, 0xf, false),
+                                       __builtin_amdgcn_update_dpp(0, __double2loint(v), ror, 0xf, 0xf, false));
+    const int orow = __builtin_amdgcn_update_dpp(0, r, ror, 0xf, 0xf, false);
+    if (ov > v || (ov == v && orow < r)) { v = ov; r = orow; }
+}
+static_assert(kInvWaves == 16, "one candidate to a lane of a row of 16");
 
 template <int n, int RW, int CW>
 __global__ __launch_bounds__(64 * kInvWaves) void k_coarse_inverse_reg(const int32_t *rp, const int32_t *col,
@@ -781,14 +796,13 @@ __global__ __launch_bounds__(64 * kInvWaves) void k_coarse_inverse_reg(const int
             cand_r[wv] = br;
         }
         __syncthreads();
-        bv = cand_v[0];
-        int p = cand_r[0];
-#pragma unroll
-        for (int w = 1; w < kInvWaves; ++w) {
-            const double ov = cand_v[w];
-            const int orow = cand_r[w];
-            if (ov > bv || (ov == bv && orow < p)) { bv = ov; p = orow; }
-        }
+        bv = cand_v[lane & 15];
+        int p = cand_r[lane & 15];
+        better_of<8>(bv, p);
+        better_of<4>(bv, p);
+        better_of<2>(bv, p);
+        better_of<1>(bv, p);
+        bv = lane_value(bv, 0);
         const double dk = diag_v;
         if (!(bv > 0.0) || !isfinite(bv) || dk != dk) {            // the same in every thread
             if (t == 0) atomicOr(flag, 32);
