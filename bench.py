@@ -42,16 +42,17 @@ def seeded_normal(torch, count, dtype, dev, seed):
 # None where not measured for the current kernel code.  These counters count
 # requests from the L2 to the memory fabric, which the 256 MB Infinity Cache
 # (MALL) in front of HBM serves in part, so they bound HBM traffic from above.
-TRAFFIC_PU1M = {"sweep": 542250086, "sweep_l1": 228149376, "spmv_internal": 1128992973,
-                "spmv_caller": 1713110630}
+TRAFFIC_PU1M = {"sweep": 542268211, "sweep_l1": 201241396, "spmv_internal": 1138485862,
+                "spmv_caller": 1732405453}
 TRAFFIC_KIND = ("L2-to-memory-fabric bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated); the Infinity "
                 "Cache serves part of them, so HBM itself moves at most this much")
 # Average duration of the same kernels inside timed bench steps (rocprofv3
 # --kernel-trace of the default run: W-cycle on level 0, sweeps 1/2,
 # coarse damping 1.4,
 # profiles/bench_pu1M_kernel_stats.md); None where not measured for the
-# current kernel code.
-IN_STEP_US_PU1M = {"sweep": 84.32, "sweep_l1": 42.54, "spmv_internal": 182.65, "spmv_caller": None}
+# current kernel code (the steps' FP64 product is the sliced one, k_rows mode
+# 0, at 178.95 us; cbs_spmv reads the block CSR).
+IN_STEP_US_PU1M = {"sweep": 82.22, "sweep_l1": 37.03, "spmv_internal": None, "spmv_caller": None}
 IN_STEP_CYCLE = (1, 1.4, 1, 2)          # w_levels, coarse_omega, pre and post sweeps of that run
 
 
@@ -263,12 +264,17 @@ def level_sweep_call(P, torch, dev, sysm, n, level=0, op=None):
     return run, bool(f.value)
 
 
-def spmv_call(P, torch, dev, system, N, n):
+def spmv_call(P, torch, dev, system, N, n, warm=24):
     import ctypes as C
     L = P.lib()
     xv = seeded_normal(torch, N * n, torch.float64, dev, 103)
     yv = torch.empty_like(xv)
-    return lambda: L.cbs_spmv(system.h, C.c_void_p(xv.data_ptr()), C.c_void_p(yv.data_ptr()), 0)
+    run = lambda: L.cbs_spmv(system.h, C.c_void_p(xv.data_ptr()), C.c_void_p(yv.data_ptr()), 0)   # noqa: E731
+    # the library may make a sliced copy of the values after some products:
+    # what is timed is the product of a program that makes many
+    for _ in range(warm):
+        run()
+    return run
 
 
 def kernels_only(args, P, torch, dev, sysm, opt_mixed, N, n, nnzb, la, ua, diag, upper, lower):
@@ -281,7 +287,7 @@ def kernels_only(args, P, torch, dev, sysm, opt_mixed, N, n, nnzb, la, ua, diag,
     sys2 = internal_system(P, torch, dev, sysm, N, n, la, ua, diag, upper, lower)
     coarse = [level_sweep_call(P, torch, dev, sysm, n, level=l, op=op)[0]
               for l in (1, 2) for op in (P.LEVEL_SWEEP, P.LEVEL_RESIDUAL)]
-    for fn in (sweep, spmv_call(P, torch, dev, sysm, N, n), spmv_call(P, torch, dev, sys2, N, n), *coarse):
+    for fn in (sweep, spmv_call(P, torch, dev, sysm, N, n, 0), spmv_call(P, torch, dev, sys2, N, n, 0), *coarse):
         for _ in range(5):
             fn()
         torch.cuda.synchronize()
@@ -757,8 +763,8 @@ def main():
             (kobj("level-0 block-Jacobi sweep, %s (k_rows, internal numbering)" % sweep_desc, sweep_ms, sbytes,
                   "sweep") if args.w_levels >= 1 else
              kobj("level-1 block-Jacobi sweep, %s (k_rows)" % sweep_desc, sweep1_ms, sbytes1, "sweep_l1")),
-        "spmv_fp64": kobj("block SpMV FP64 (k_rows mode 0), internal numbering", spmv_ms, byts, "spmv_internal"),
-        "spmv_fp64_caller_numbering": kobj("block SpMV FP64 (k_rows mode 0), caller's random numbering",
+        "spmv_fp64": kobj("block SpMV FP64 (k_bcsr), internal numbering", spmv_ms, byts, "spmv_internal"),
+        "spmv_fp64_caller_numbering": kobj("block SpMV FP64 (k_bcsr), caller's random numbering",
                                            spmv_user_ms, byts, "spmv_caller"),
         "copy_peak": {"achieved": round(copy_gbs, 1), "unit": "GB/s", "kernel": "1 GiB device copy (torch copy_)"},
     }

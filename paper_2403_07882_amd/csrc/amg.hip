@@ -2244,7 +2244,9 @@ void permute_vec(cbs_system *h, const double *in, double *out, bool to_internal)
 // the block-CSR product is as fast as the sliced one (1M cells: 185 and 187
 // us; renumbered at random 254 and 249 us), so A keeps none there, except
 // below the rows from which the sliced product stops splitting its rows (at
-// some 10,000 rows 9.7 us against 12.6 us).
+// some 10,000 rows 9.7 us against 12.6 us).  The copy's schedule is the known
+// or the default one: timing the six takes as long as 72 products (5x5, 1M
+// rows: 25 ms, where the copy takes 1 ms and saves 40 us a product).
 constexpr int32_t kUserCopyAfter = 16;
 
 // cbs_spmv: caller-numbered A or A^T.  Options that name a kernel of the
@@ -2277,7 +2279,7 @@ void spmv_user(cbs_system *h, const double *x, double *y, bool transposed) {
         h->valsT.release();
     }
     if (tune) {
-        U.sched64 = choose_sched(n, U, false, copy.get(), h->opt.schedule, h->stream);
+        U.sched64 = known_sched(n, U, false, h->opt.schedule);
         U.sched64.split = row_split_for(U, h->nnzb, h->opt.row_split);
     }
     launch_rows<double, double>(0, n, U.view(), copy.get(), x, nullptr, y, nullptr, 0.0, h->stream);

@@ -415,6 +415,8 @@ void launch_bcsr(int n, int32_t N, const int32_t *rp, const int32_t *col, const 
 Sched autotune_rows(int n, const Sell &S, bool fp32, const void *val, hipStream_t st);
 // the schedule option: 0 = autotune_rows, 1..6 = a forced (unroll, non-temporal) pair
 Sched choose_sched(int n, const Sell &S, bool fp32, const void *val, int32_t forced, hipStream_t st);
+// the same without timing anything: what was found for these sizes before, or the default
+Sched known_sched(int n, const Sell &S, bool fp32, int32_t forced);
 // threads per scalar row of the block-row kernels on a level (row_split option)
 int8_t row_split_for(const Sell &S, int64_t nblocks, int32_t opt_split);
 // sliced-ELL pattern from BCSR (offdiag: without the diagonal blocks), and

@@ -1504,6 +1504,16 @@ int8_t row_split_for(const Sell &S, int64_t nblocks, int32_t opt_split) {
     return (int8_t)s;
 }
 
+Sched known_sched(int n, const Sell &S, bool fp32, int32_t forced) {
+    if (forced >= 1 && forced <= 6) return choose_sched(n, S, fp32, nullptr, forced, nullptr);
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    auto it = g_tune_cache.find(std::make_tuple(S.N, S.nent, n, fp32));
+    if (it != g_tune_cache.end()) return it->second;
+    // FP64 5x5: two blocks in flight leave room for more wavefronts (1M rows
+    // 281 us against 292, 8M 2,249 against 2,408)
+    return fp32 ? Sched{4, 1} : Sched{(int8_t)(n == 5 && S.N >= 65536 ? 2 : 4), 0};
+}
+
 Sched choose_sched(int n, const Sell &S, bool fp32, const void *val, int32_t forced, hipStream_t st) {
     if (forced >= 1 && forced <= 6) {
         static const int8_t unroll[3] = {1, 2, 4};
