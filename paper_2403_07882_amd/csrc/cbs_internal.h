@@ -453,7 +453,7 @@ template <typename TX>
 void launch_restrict(int n, int32_t nc, const int32_t *agg_ptr, const int32_t *agg_mem,
                      const TX *r, TX *bc, hipStream_t st);
 template <typename TX>
-void launch_prolong(int n, int32_t N, const int32_t *agg, const TX *e, TX *x, hipStream_t st);
+void launch_prolong(int n, int32_t N, const int32_t *agg, const TX *e, const TX *x, TX *to, hipStream_t st);
 template <typename TA, typename TB>
 void launch_cast(int64_t m, const TA *a, TB *b, hipStream_t st);
 void launch_coarse_solve(cbs_system *h, bool transposed, const void *b, void *x, bool fp32);

@@ -968,14 +968,15 @@ __global__ void k_restrict(int32_t nc, int n, const int32_t *__restrict__ aptr, 
     bc[g] = (TX)s;
 }
 
+// to = x + P e (to may be x)
 template <typename TX>
-__global__ void k_prolong(int32_t N, int n, const int32_t *__restrict__ agg, const TX *__restrict__ e,
-                          TX *__restrict__ x) {
+__global__ void k_prolong(int32_t N, int n, const int32_t *__restrict__ agg, const TX *__restrict__ e, const TX *x,
+                          TX *to) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= (int64_t)N * n) return;
     const int64_t i = g / n;
     const int q = (int)(g - i * n);
-    x[g] += e[(int64_t)agg[i] * n + q];
+    to[g] = x[g] + e[(int64_t)agg[i] * n + q];
 }
 
 template <typename TA, typename TB>
@@ -1325,13 +1326,14 @@ template void launch_restrict<double>(int, int32_t, const int32_t *, const int32
 template void launch_restrict<float>(int, int32_t, const int32_t *, const int32_t *, const float *, float *, hipStream_t);
 
 template <typename TX>
-void launch_prolong(int n, int32_t N, const int32_t *agg, const TX *e, TX *x, hipStream_t st) {
+void launch_prolong(int n, int32_t N, const int32_t *agg, const TX *e, const TX *x, TX *to, hipStream_t st) {
     const int64_t m = (int64_t)N * n;
-    if (m > 0) hipLaunchKernelGGL(k_prolong<TX>, dim3(cdiv(m, 256)), dim3(256), 0, st, N, n, agg, e, x);
+    if (m > 0) hipLaunchKernelGGL(k_prolong<TX>, dim3(cdiv(m, 256)), dim3(256), 0, st, N, n, agg, e, x, to);
     LAUNCHCHK();
 }
-template void launch_prolong<double>(int, int32_t, const int32_t *, const double *, double *, hipStream_t);
-template void launch_prolong<float>(int, int32_t, const int32_t *, const float *, float *, hipStream_t);
+template void launch_prolong<double>(int, int32_t, const int32_t *, const double *, const double *, double *,
+                                     hipStream_t);
+template void launch_prolong<float>(int, int32_t, const int32_t *, const float *, const float *, float *, hipStream_t);
 
 namespace {
 template <typename T>
