@@ -17,8 +17,8 @@
 //
 // MI355X, FP32 hierarchy of the 41x39x35-cell 4x4 system (tail of 107, 27 and
 // 6 rows): one workgroup 31.7 us per cycle, the operator 5.9 us, formed in
-// 99 us per setup; FP64, 960 cells (241, 62 and 16 rows): 34.9 ->
-// 6.6 us, formed in 108 us.
+// 67 us per setup; FP64, 960 cells (241, 62 and 16 rows): 34.9 ->
+// 6.6 us, formed in 71 us.
 #include "cbs_internal.h"
 
 #include <algorithm>
@@ -70,6 +70,15 @@ __device__ inline void tail_load_row(const double *__restrict__ p, double (&v)[n
     }
 }
 
+// Doubles that one block row of a vector takes in LDS.  The residual gathers
+// rows of x, the correction reads rows of r, in 16-byte pieces; at a distance of a multiple of 32 bytes the
+// pieces of a wavefront's 16 rows fall on few of the banks (n = 4, NC = 4: on
+// one eighth), at an odd multiple of 16 bytes on all of them: 960 cells 4x4 108
+// -> 71 us, 24 systems 5x5 328 -> 282 us.
+__host__ __device__ constexpr int tail_row(int n, int NC) {
+    return n * NC >= 8 && n * NC % 4 == 0 ? n * NC + 2 : n * NC;
+}
+
 // one system's rows of a level, and where its vectors (doubles, NC columns side
 // by side) and staged index lists (integers) start in LDS
 struct TailRows {
@@ -96,8 +105,8 @@ __device__ __forceinline__ void tail_residual(const TailLvl &L, const TailRows &
         double acc[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) acc[c] = 0.0;
+        const int32_t i = o / n, rr = o - i * n, gi = S.row0 + i;
         if (o < m) {
-            const int32_t i = o / n, rr = o - i * n, gi = S.row0 + i;
             const int32_t sl = gi >> L.lc, base = soff[sl - S.sl0] + (gi - (sl << L.lc)), w = sw[sl - S.sl0];
             for (int32_t k = kk; k < w; k += sp * U) {
                 int32_t j[U];
@@ -113,7 +122,7 @@ __device__ __forceinline__ void tail_residual(const TailLvl &L, const TailRows &
 #pragma unroll
                 for (int u = 0; u < U; ++u)
                     if (j[u] >= 0) {
-                        const double *xj = x + (j[u] - S.row0) * n * NC;
+                        const double *xj = x + (j[u] - S.row0) * tail_row(n, NC);
 #pragma unroll
                         for (int q = 0; q < n; ++q)
 #pragma unroll
@@ -126,7 +135,10 @@ __device__ __forceinline__ void tail_residual(const TailLvl &L, const TailRows &
             for (int c = 0; c < NC; ++c) acc[c] += __shfl_xor(acc[c], s, 64);
         if (o < m && kk == 0)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) r[o * NC + c] = b[o * NC + c] - acc[c];
+            for (int c = 0; c < NC; ++c) {
+                const int32_t e = i * tail_row(n, NC) + rr * NC + c;
+                r[e] = b[e] - acc[c];
+            }
     }
     __syncthreads();
 }
@@ -144,8 +156,9 @@ __device__ __forceinline__ void tail_correct(const TailLvl &L, const TailRows &S
         for (int c = 0; c < NC; ++c) {
             double z = 0.0;
 #pragma unroll
-            for (int q = 0; q < n; ++q) z += d[q] * v[(i * n + q) * NC + c];
-            x[o * NC + c] = (ZERO ? 0.0 : x[o * NC + c]) + omega * z;
+            for (int q = 0; q < n; ++q) z += d[q] * v[i * tail_row(n, NC) + q * NC + c];
+            double &xo = x[i * tail_row(n, NC) + rr * NC + c];
+            xo = (ZERO ? 0.0 : xo) + omega * z;
         }
     }
     __syncthreads();
@@ -154,7 +167,8 @@ __device__ __forceinline__ void tail_correct(const TailLvl &L, const TailRows &S
 // Columns q0 .. q0 + NC of one system's operator: the cycle of the tail on
 // unit right sides.  The level vectors and index lists of the system are in
 // LDS; matrix values and columns are read from L2, each block row once for
-// the NC columns.  Bound by those reads and by the barriers between steps.
+// the NC columns.  Bound by those reads, by the gathers from LDS (see tail_row)
+// and by the barriers between steps.
 template <int n, int NC>
 __global__ __launch_bounds__(kTailThreads) void k_tail_operator(const TailArgs a) {
     extern __shared__ __align__(16) char smem[];
@@ -172,7 +186,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_operator(const TailArgs a
     int32_t nv = 0;                                  // doubles of the vectors
     for (int k = 0; k <= nl; ++k) {
         const int32_t *ro = a.roff + k * (a.nsys + 1) + s;
-        nv += (k < nl ? 3 : 2) * (ro[1] - ro[0]) * n * NC;
+        nv += (k < nl ? 3 : 2) * (ro[1] - ro[0]) * tail_row(n, NC);
     }
     int32_t *is = reinterpret_cast<int32_t *>(vs + nv);
     if (t == 0) {
@@ -183,9 +197,9 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_operator(const TailArgs a
             S.row0 = ro[0];
             S.N = ro[1] - ro[0];
             S.sl0 = S.row0 >> a.lv[k].lc;
-            S.b = v; v += S.N * n * NC;
-            S.x = v; v += S.N * n * NC;
-            S.r = v; v += k < nl ? S.N * n * NC : 0;
+            S.b = v; v += S.N * tail_row(n, NC);
+            S.x = v; v += S.N * tail_row(n, NC);
+            S.r = v; v += k < nl ? S.N * tail_row(n, NC) : 0;
             if (k < nl) {
                 const int32_t ns = ((S.row0 + S.N - 1) >> a.lv[k].lc) - S.sl0 + 1;
                 S.soff = p; p += ns;
@@ -218,7 +232,8 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_operator(const TailArgs a
         }
     }
     const int32_t m = sS[0].N * n;
-    for (int32_t e = t; e < m * NC; e += kTailThreads) vs[sS[0].b + e] = e / NC == q0 + e % NC ? 1.0 : 0.0;
+    for (int32_t e = t; e < m * NC; e += kTailThreads)
+        vs[sS[0].b + e / (n * NC) * tail_row(n, NC) + e % (n * NC)] = e / NC == q0 + e % NC ? 1.0 : 0.0;
     __syncthreads();
     for (int k = 0; k < nl; ++k) {
         const TailRows S = sS[k], C = sS[k + 1];
@@ -231,7 +246,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_operator(const TailArgs a
             }
             tail_residual<n, NC>(L, S, vs, is);
         } else {
-            for (int32_t e = t; e < S.N * n * NC; e += kTailThreads) {
+            for (int32_t e = t; e < S.N * tail_row(n, NC); e += kTailThreads) {
                 vs[S.x + e] = 0.0;
                 vs[S.r + e] = vs[S.b + e];
             }
@@ -241,8 +256,9 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_operator(const TailArgs a
         for (int32_t e = t; e < C.N * n * NC; e += kTailThreads) {
             const int32_t I = e / (n * NC), q = e - I * n * NC;
             double v = 0.0;
-            for (int32_t p = is[C.aptr + I]; p < is[C.aptr + I + 1]; ++p) v += vs[S.r + is[C.amem + p] * n * NC + q];
-            vs[C.b + e] = v;
+            for (int32_t p = is[C.aptr + I]; p < is[C.aptr + I + 1]; ++p)
+                v += vs[S.r + is[C.amem + p] * tail_row(n, NC) + q];
+            vs[C.b + I * tail_row(n, NC) + q] = v;
         }
         __syncthreads();
     }
@@ -250,18 +266,26 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_operator(const TailArgs a
         const TailRows S = sS[nl];
         const int mc = a.cm[s];
         const double *M = a.cinv + a.coff[s];
-        for (int32_t o = t; o < mc; o += kTailThreads) {
+        // 16 adjacent lanes share a row, which they read in one run
+        for (int32_t o0 = 0; o0 < mc; o0 += kTailThreads / 16) {
+            const int32_t o = o0 + t / 16, kk = t & 15;
             double acc[NC];
 #pragma unroll
             for (int c = 0; c < NC; ++c) acc[c] = 0.0;
+            if (o < mc)
 #pragma unroll 4
-            for (int q = 0; q < mc; ++q) {
-                const double v = M[(int64_t)o * mc + q];
+                for (int q = kk; q < mc; q += 16) {
+                    const double v = M[(int64_t)o * mc + q];
 #pragma unroll
-                for (int c = 0; c < NC; ++c) acc[c] += v * vs[S.b + q * NC + c];
-            }
+                    for (int c = 0; c < NC; ++c) acc[c] += v * vs[S.b + q / n * tail_row(n, NC) + q % n * NC + c];
+                }
 #pragma unroll
-            for (int c = 0; c < NC; ++c) vs[S.x + o * NC + c] = acc[c];
+            for (int w = 8; w > 0; w >>= 1)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) acc[c] += __shfl_xor(acc[c], w, 64);
+            if (o < mc && kk == 0)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) vs[S.x + o / n * tail_row(n, NC) + o % n * NC + c] = acc[c];
         }
         __syncthreads();
     }
@@ -269,8 +293,8 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_operator(const TailArgs a
         const TailRows S = sS[k];
         const int32_t xc = sS[k + 1].x;
         for (int32_t e = t; e < S.N * n * NC; e += kTailThreads) {
-            const int32_t i = e / (n * NC);
-            vs[S.x + e] += vs[xc + is[S.agg + i] * n * NC + (e - i * n * NC)];
+            const int32_t i = e / (n * NC), q = e - i * n * NC;
+            vs[S.x + i * tail_row(n, NC) + q] += vs[xc + is[S.agg + i] * tail_row(n, NC) + q];
         }
         __syncthreads();
         for (int q = 0; q < a.nu2; ++q) {
@@ -283,7 +307,8 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_operator(const TailArgs a
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         if (q0 + c < m)
-            for (int32_t o = t; o < m; o += kTailThreads) op[(q0 + c) * ld + o] = vs[sS[0].x + o * NC + c];
+            for (int32_t o = t; o < m; o += kTailThreads)
+                op[(q0 + c) * ld + o] = vs[sS[0].x + o / n * tail_row(n, NC) + o % n * NC + c];
 }
 
 // kTailRowsPerWg scalar rows of one system's operator times the restricted
@@ -343,7 +368,7 @@ int64_t tail_lds(const cbs_system *h, int l0, int NC) {
         for (int l = l0; l < nlev; ++l) {
             const Level &L = h->lev[l];
             const int64_t N = L.sys_off[s + 1] - L.sys_off[s];
-            dbl += (l + 1 < nlev ? 3 : 2) * N * h->n * NC;
+            dbl += (l + 1 < nlev ? 3 : 2) * N * tail_row(h->n, NC);
             if (l + 1 < nlev) ints += 2 * ((N >> L.sell.lc) + 2) + N;
             if (l > l0) ints += N + 1 + finer;
             finer = N;
