@@ -121,8 +121,9 @@ typedef struct cbs_options {
                                 down to the coarsest and back, the cycle runs
                                 as one dense FP64 operator per system, formed
                                 at setup (one kernel instead of about five
-                                per level; at most 32 MB of operators, else
-                                it starts further down); 0 = 256, < 0 =
+                                per level; at most 32 MB of operators and no
+                                smoothed level of 32,768 rows of all systems,
+                                else it starts further down); 0 = 256, < 0 =
                                 never. Changes only the order of the row
                                 sums                                 [0] */
     int32_t schedule;        /* schedule of the block-row kernels (blocks

@@ -416,9 +416,14 @@ int tail_level(const cbs_system *h) {
             vals += m * tail_ld(m);
         }
         if (rows > lim || vals * 8 > kTailOpBytes || m_max * 8 > 64 * 1024) continue;
-        bool coloured = false;                       // DILU and Gauss-Seidel levels keep their own kernels
-        for (int q = l; q + 1 < nlev; ++q) coloured = coloured || h->lev[q].dilu || h->lev[q].sgs;
-        if (!coloured && tail_lds(h, l, 1) <= tail_lds_budget(h)) return l;
+        // DILU and Gauss-Seidel levels keep their own kernels, and so do levels
+        // whose copy is window-ordered (kSplitLevelRows rows and more of all
+        // systems together, which fill the chip): k_tail_operator takes a
+        // system's rows in order, and the rows of a window change places
+        // across systems
+        bool own = false;
+        for (int q = l; q + 1 < nlev; ++q) own = own || h->lev[q].dilu || h->lev[q].sgs || h->lev[q].sell.win;
+        if (!own && tail_lds(h, l, 1) <= tail_lds_budget(h)) return l;
     }
     return -1;
 }
@@ -500,6 +505,7 @@ void tail_form(cbs_system *h, bool tr) {
         d.aptr = F.agg_ptr.get();
         d.amem = F.agg_mem.get();
         if (k == nl) break;                          // the coarsest needs no more
+        if (L.sell.prow.get()) cbs_throw(CBS_ERR_ARG, "V-cycle tail: a level whose rows are not in order");
         d.val = tr ? L.sell.v64T.get() : L.sell.v64.get();
         d.Dinv = tr ? L.DinvT.get() : L.Dinv.get();
         d.soff = L.sell.soff.get();
