@@ -261,6 +261,7 @@ struct TailBlk {
 // (op: forward, opT: of the transposed hierarchy), column by column
 struct Tail {
     int level = -1;                      // first level, -1: none
+    int nlev = 0;                        // levels of the hierarchy that the plan is of
     int32_t nblk = 0, max_m = 0;
     int32_t ncols = 1, wgs = 0;          // columns per workgroup that forms the operators, and workgroups
     int64_t vals = 0;                    // values of all operators
@@ -459,8 +460,9 @@ void launch_cast(int64_t m, const TA *a, TB *b, hipStream_t st);
 void launch_coarse_solve(cbs_system *h, bool transposed, const void *b, void *x, bool fp32);
 void launch_block_apply(int n, int32_t N, const double *Dinv, const double *r, double *z, hipStream_t st);
 // V-cycle tail (tail.hip): tail_plan chooses the level it starts at (h->tail;
-// kept: the hierarchy's pattern is that of the last plan), tail_form forms its operators from the level matrices, and launch_tail runs
-// it on the residual of the level above (result: x of the first tail level)
+// kept: the levels of the last plan have their old patterns), tail_form forms
+// its operators from the level matrices, and launch_tail runs it on the
+// residual of the level above (result: x of the first tail level)
 void tail_plan(cbs_system *h, bool kept);
 void tail_form(cbs_system *h, bool tr);
 template <typename T>

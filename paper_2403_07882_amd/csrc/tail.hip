@@ -449,11 +449,14 @@ void operator_nc(int NC, const TailArgs &a, unsigned wgs, size_t lds, hipStream_
 
 void tail_plan(cbs_system *h, bool kept) {
     Tail &T = h->tail;
-    const int was = T.level;
+    const int was = T.level, nsys = h->n_sys, nlev = (int)h->lev.size();
     T.level = tail_level(h);
-    if (T.level < 0 || (kept && T.level == was)) return;
+    // a setup that keeps its aggregates appends levels all the same where the
+    // last one ended on a stalled level that the new values let go on
+    if (T.level < 0 || (kept && T.level == was && T.nlev == nlev)) return;
+    T.nlev = nlev;
     T.max_m = 0;
-    const int nsys = h->n_sys, nlev = (int)h->lev.size(), nl = nlev - 1 - T.level;
+    const int nl = nlev - 1 - T.level;
     std::vector<TailBlk> blk;
     std::vector<int64_t> off(nsys + 1, 0);
     std::vector<int32_t> roff;
