@@ -305,8 +305,7 @@ __global__ __launch_bounds__(kVecThreads) void k_p_update(const Item *__restrict
 // a launch that does nothing else (two of three such launches an iteration).
 // BiCGStab of 960 rows: the three took 177 us of 15 iterations, solve and setup
 // now 6.8% faster; 8,000 rows 6.3%, 55,000 rows 5.6%; 1M rows (977 partials)
-// 0.2%.  The first workgroup of a system leaves the scalars; another one that
-// sees its flags already decides as it would from the sums.
+// 0.2%.  The first workgroup of a system leaves the scalars.
 
 // Where the two products that follow A x are: partials of the work items in
 // the first slots (k_dots), or of the product's own workgroups (count of them,
@@ -327,16 +326,20 @@ struct AlphaStep {
     HostMirror hm;
 };
 
-// alpha of system s, or false at a breakdown (the whole workgroup); sh: 4 doubles
+// alpha of system s, or false at a breakdown (the whole workgroup); sh: 4 doubles.
+// The system's first workgroup may set the breakdown flag while others read it,
+// so the barriers of the sum lie before any branch on it: a wavefront that sees
+// the flag then decides as the others do from the sum.
 __device__ inline bool alpha_step(const AlphaStep &a, int s, int nsys, double *sh, double &alpha) {
     double *scal = a.scal;
     const int32_t i0 = a.item_off[s];
     const double rho = SC(S_RHO), rr = SC(S_RR);
     double rv[1];
     sum_items<1>(a.ds.p, a.ds.stride, {0}, a.ds.count ? 0 : i0, a.ds.count ? a.ds.count : a.item_off[s + 1], sh, rv);
+    const bool broken = a.flags[s] & kFlagBreak;
     const bool bad = rv[0] == 0.0 || !isfinite(rv[0]) || fabs(rv[0]) < 1e-300 * fmax(rr, 1e-300);
     alpha = bad ? 0.0 : rho / rv[0];
-    if ((int32_t)blockIdx.x == i0 && threadIdx.x == 0) {
+    if (!broken && (int32_t)blockIdx.x == i0 && threadIdx.x == 0) {
         SC(S_RV) = rv[0];
         SC(S_ALPHA) = alpha;
         a.iters[s] += 1;
@@ -345,7 +348,7 @@ __device__ inline bool alpha_step(const AlphaStep &a, int s, int nsys, double *s
             publish_state(a.hm, s, nsys, a.done, a.flags, a.iters);
         }
     }
-    return !bad;
+    return !bad && !broken;
 }
 
 __global__ __launch_bounds__(kVecThreads) void k_s_update(const Item *__restrict__ items, int32_t n_items,
@@ -356,7 +359,7 @@ __global__ __launch_bounds__(kVecThreads) void k_s_update(const Item *__restrict
     const Item it = items[blockIdx.x];
     const int s = it.sys;
     double s0 = 0.0;
-    if (!a.done[s] && !(a.flags[s] & kFlagBreak)) {
+    if (!a.done[s]) {
         int64_t e = it.beg + threadIdx.x;
         const bool have = e < it.end;
         double re = have ? r[e] : 0.0, ve = have ? v[e] : 0.0;       // (with the partials)
@@ -388,7 +391,7 @@ __global__ __launch_bounds__(kVecThreads) void k_s_update_sweep(const Item *__re
     const Item it = items[blockIdx.x];
     const int s = it.sys;
     double alpha = 0.0, s0 = 0.0;
-    const bool on = !a.done[s] && !(a.flags[s] & kFlagBreak) && alpha_step(a, s, nsys, sh, alpha);
+    const bool on = !a.done[s] && alpha_step(a, s, nsys, sh, alpha);
     item_sweep0<n, T>(
         it, z, sb,
         [&](int64_t e, double (&raw)[3]) {
