@@ -712,7 +712,8 @@ __global__ __launch_bounds__(kFinThreads) void k_gm_start(int32_t nsys, int m, c
 // LDS: the rotations are applied one after the other, which from memory cost a
 // load each.
 // The others, one per item, form V_{j+1} = w / ||w|| (a system that finishes in
-// this step may leave its items undone: they are not read again).
+// this step may leave its items undone: they are not read again; the sum, with
+// its barrier, comes before any look at `done`, which the first workgroups set).
 __global__ __launch_bounds__(kFinThreads) void k_gm_givens(int32_t nsys, int j, int m, const Item *__restrict__ items,
                                                             const int32_t *__restrict__ item_off, int32_t n_items,
                                                             const double *__restrict__ partial, int slot, double *scal,
@@ -725,9 +726,8 @@ __global__ __launch_bounds__(kFinThreads) void k_gm_givens(int32_t nsys, int j, 
     double ww[1];
     if ((int)blockIdx.x >= nsys) {
         const Item it = items[blockIdx.x - nsys];
-        if (done[it.sys]) return;
         sum_items<1>(partial, n_items, {slot}, item_off[it.sys], item_off[it.sys + 1], sh, ww);
-        item_scale(it, sqrt(ww[0]), w, vnext);
+        if (!done[it.sys]) item_scale(it, sqrt(ww[0]), w, vnext);
         return;
     }
     const int s = blockIdx.x;

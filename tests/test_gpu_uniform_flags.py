@@ -3,6 +3,9 @@ same flag: systems of many work items, alone and beside others."""
 import numpy as np
 import pytest
 
+import oracle as O
+from workloads import concat_systems, jacobian_box
+
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
@@ -32,3 +35,20 @@ def test_breakdown_of_many_workgroups(cells):
     assert st[0].iterations == st[2].iterations == 2
     assert (x[:cells] == 0.0).all() and (x[2 * cells:] == 0.0).all()
     assert np.abs(x[cells:2 * cells] - 1.0).max() <= 1e-11
+
+
+@pytest.mark.parametrize("solver", [P.SOLVER_GMRES, P.SOLVER_FGMRES])
+def test_gmres_systems_that_finish_in_different_steps(solver):
+    """A system of one step, others of many, several work items each."""
+    systems = [jacobian_box(*sh, n=5, seed=170 + k, vdt=v) for k, (sh, v) in
+               enumerate([((12, 11, 10), 1e9), ((13, 12, 11), 0.1), ((9, 9, 9), 10.0), ((14, 13, 12), 1e3)])]
+    cat = concat_systems(systems)
+    with P.System.from_dict(cat) as s:
+        s.setup(precond=P.PREC_BJACOBI, solver=solver, restart=12, tol=1e-10)
+        x, st = s.solve_batch(cat["b"])
+    x = x.cpu().numpy()
+    its = [q["iterations"] for q in st]
+    assert len(set(its)) > 2, its
+    for k, sk in enumerate(systems):
+        assert st[k]["status"] == P.OK
+        assert O.relres(O.from_system(sk), sk["b"], x[cat["cell_off"][k]:cat["cell_off"][k + 1]]) <= 1.01e-10
