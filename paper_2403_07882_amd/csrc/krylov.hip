@@ -183,7 +183,9 @@ __global__ __launch_bounds__(kFinThreads) void k_fin(int phase, int32_t nsys, co
         SC(S_RR) = rr;
         SC(S_RHO0) = SC(S_RHO);
         SC(S_RHO) = rhn;
-        if (rr <= tol2 * SC(S_BB)) done[s] = 1;
+        // after a half step r = s has met the tolerance whatever (r, r) rounds to:
+        // it may be summed in another order than (s, s) was
+        if (rr <= tol2 * SC(S_BB) || (flags[s] & kFlagHalf)) done[s] = 1;
         else if (SC(S_OMEGA) == 0.0 || rhn == 0.0 || !isfinite(rhn) || (flags[s] & kFlagBreak)) flags[s] |= kFlagBreak;
         flags[s] &= ~(kFlagHalf | kFlagNear);
         const double rrp = SC(S_RRPREV);
