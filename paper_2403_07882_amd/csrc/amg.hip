@@ -1810,7 +1810,7 @@ void amg_setup(cbs_system *h) {
                    sgs ? &L0.colour_off : nullptr);
         level_sell(h, L0, false, nullptr);
         L0.sell.sched64 = choose_sched(n, L0.sell, false, L0.sell.v64.get(), o.schedule, st);
-        L0.sell.sched64.split = row_split_for(L0.sell, L0.nnzb, o.row_split);
+        L0.sell.sched64.split = row_split_for(L0.sell.N, L0.nnzb, o.row_split);
         h->op_complexity = 1.0;
         h->tail.level = -1;
         return;
@@ -2003,8 +2003,8 @@ void amg_setup(cbs_system *h) {
         for (auto &L : h->lev) {
             L.sell.sched64 = L.sod.sched64 = s64;
             L.sell.sched32 = L.sod.sched32 = s32;
-            L.sell.sched64.split = L.sell.sched32.split = row_split_for(L.sell, L.nnzb, o.row_split);
-            L.sod.sched32.split = row_split_for(L.sod, L.nnzb - L.N, o.row_split);
+            L.sell.sched64.split = L.sell.sched32.split = row_split_for(L.sell.N, L.nnzb, o.row_split);
+            L.sod.sched32.split = row_split_for(L.sod.N, L.nnzb - L.N, o.row_split);
         }
         pt.mark("autotune");
     }
@@ -2242,12 +2242,18 @@ void permute_vec(cbs_system *h, const double *in, double *out, bool to_internal)
 // 140 us product (A^T: 22 of 147 us, 47 of 188 us renumbered), so it pays
 // after some 17 products (A^T 12 to 25).  4x4 blocks are whole cache lines and
 // the block-CSR product is as fast as the sliced one (1M cells: 185 and 187
-// us; renumbered at random 254 and 249 us), so A keeps none there, except
-// below the rows from which the sliced product stops splitting its rows (at
-// some 10,000 rows 9.7 us against 12.6 us).  The copy's schedule is the known
-// or the default one: timing the six takes as long as 72 products (5x5, 1M
+// us; renumbered at random 254 and 249 us), so A keeps none there from
+// kSplitLevelRows rows on.  The copy's schedule is the known or the default one: timing the six takes as long as 72 products (5x5, 1M
 // rows: 25 ms, where the copy takes 1 ms and saves 40 us a product).
 constexpr int32_t kUserCopyAfter = 16;
+
+// Both kernels split the rows of small systems over the same number of threads,
+// so that a product has the same bits in every call; from this many scalar rows
+// on they keep them whole.  5x5 first and sliced product, split and whole: 12,167
+// rows 5.1 and 5.2 us, 5.2 us; 24,389 rows 9.5 and 8.8 us, 9.7 and 8.0 us; 31,713
+// rows 13.0 and 10.2 us, 13.3 and 9.3 us.  4x4: 24,389 rows 4.9 and 5.2 us, 4.6
+// and 5.0 us; 31,713 rows 6.2 and 6.0 us, 6.0 and 5.4 us.
+constexpr int64_t kUserWholeRows = 98304;
 
 // cbs_spmv: caller-numbered A or A^T.  Options that name a kernel of the
 // sliced copy (schedule, row_split) use it from the first product on.
@@ -2256,11 +2262,13 @@ void spmv_user(cbs_system *h, const double *x, double *y, bool transposed) {
     const int n = h->n;
     DArr<double> &copy = transposed ? U.v64T : U.v64;
     int32_t &products = h->user_products[transposed ? 1 : 0];
+    const int8_t split = h->opt.row_split <= 0 && (int64_t)h->N * n >= kUserWholeRows
+                             ? 1 : row_split_for(h->N, h->nnzb, h->opt.row_split);
     if (!copy.get() && h->opt.schedule <= 0 && h->opt.row_split <= 0 &&
         (products < kUserCopyAfter || (n == 4 && !transposed && h->N >= kSplitLevelRows))) {
         products = std::min(products + 1, kUserCopyAfter);
         launch_bcsr(n, h->N, h->rp.get(), h->col.get(), transposed ? h->mirror.get() : nullptr, h->vals.get(), x, y,
-                    h->stream);
+                    split, h->stream);
         return;
     }
     if (!U.soff.get()) sell_build(h->N, h->rp.get(), h->col.get(), U, h->stream);
@@ -2280,7 +2288,7 @@ void spmv_user(cbs_system *h, const double *x, double *y, bool transposed) {
     }
     if (tune) {
         U.sched64 = known_sched(n, U, false, h->opt.schedule);
-        U.sched64.split = row_split_for(U, h->nnzb, h->opt.row_split);
+        U.sched64.split = split;
     }
     launch_rows<double, double>(0, n, U.view(), copy.get(), x, nullptr, y, nullptr, 0.0, h->stream);
 }

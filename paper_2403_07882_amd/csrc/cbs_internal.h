@@ -409,17 +409,18 @@ void launch_cast_sweep0(int n, int32_t N, const double *b64, float *b, const dou
 template <typename TX>
 void launch_restrict_sweep0(int n, int32_t nc, const int32_t *agg_ptr, const int32_t *agg_mem, const TX *r, TX *b,
                             const double *Dinv, double omega, TX *x, TX *c, hipStream_t st);
-// y = A x straight from block CSR, or y = A^T x with the transpose slots
+// y = A x straight from block CSR, or y = A^T x with the transpose slots, by
+// split threads per scalar row
 void launch_bcsr(int n, int32_t N, const int32_t *rp, const int32_t *col, const int32_t *mirror, const double *val,
-                 const double *x, double *y, hipStream_t st);
+                 const double *x, double *y, int split, hipStream_t st);
 // time the schedules of the residual kernel on S (cached per shape)
 Sched autotune_rows(int n, const Sell &S, bool fp32, const void *val, hipStream_t st);
 // the schedule option: 0 = autotune_rows, 1..6 = a forced (unroll, non-temporal) pair
 Sched choose_sched(int n, const Sell &S, bool fp32, const void *val, int32_t forced, hipStream_t st);
 // the same without timing anything: what was found for these sizes before, or the default
 Sched known_sched(int n, const Sell &S, bool fp32, int32_t forced);
-// threads per scalar row of the block-row kernels on a level (row_split option)
-int8_t row_split_for(const Sell &S, int64_t nblocks, int32_t opt_split);
+// threads per scalar row of the block-row kernels on a level of N rows (row_split option)
+int8_t row_split_for(int32_t N, int64_t nblocks, int32_t opt_split);
 // sliced-ELL pattern from BCSR (offdiag: without the diagonal blocks), and
 // values gathered from BCSR values
 void sell_build(int32_t N, const int32_t *rp, const int32_t *col, Sell &S, hipStream_t st, bool offdiag = false,

@@ -21,6 +21,12 @@ namespace {
 template <typename T> struct Acc { using type = double; };
 template <> struct Acc<float> { using type = float; };
 
+// One term of a row's sum is one fused operation wherever the sum is unrolled
+// (left to the compiler, some remainders became a product and an addition), so
+// that equal orders give equal bits.
+__device__ inline double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ inline float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 typedef float flt4 __attribute__((ext_vector_type(4)));
 
@@ -181,7 +187,7 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
             for (int u = 0; u < U; ++u)
                 if (j[u] >= 0) {
 #pragma unroll
-                    for (int c = 0; c < n; ++c) acc += (A)bv[u][c] * (A)xv[u][c];
+                    for (int c = 0; c < n; ++c) acc = mad((A)bv[u][c], (A)xv[u][c], acc);
                 }
         }
         // the last w % U blocks are loaded together too, not one after the
@@ -205,7 +211,7 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
             for (int u = 0; u < U - 1; ++u)
                 if (j[u] >= 0) {
 #pragma unroll
-                    for (int c = 0; c < n; ++c) acc += (A)bv[u][c] * (A)xv[u][c];
+                    for (int c = 0; c < n; ++c) acc = mad((A)bv[u][c], (A)xv[u][c], acc);
                 }
         }
     }
@@ -300,7 +306,7 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
             for (int u = 0; u < U; ++u)
                 if (j[u] >= 0) {
 #pragma unroll
-                    for (int c = 0; c < n; ++c) acc += (A)bv[u][c] * (A)xv[u][c];
+                    for (int c = 0; c < n; ++c) acc = mad((A)bv[u][c], (A)xv[u][c], acc);
                 }
         }
     }
@@ -342,30 +348,35 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
 }
 
 // y = A x, or with TR y = A^T x through the mirror slots, straight from block
-// CSR: thread (row i, r) as in k_rows, U blocks in flight.  For products with
-// values that have no sliced copy yet: the copy costs reading and writing the
-// matrix before its first use.  1M rows 4x4 in mesh order: copy 355 us +
-// product 187 us, this product 185 us (5.3 TB/s); transposed, copies 780 us +
-// product 186 us, this product 202 us.
-template <int n, bool TR>
+// CSR: thread (row i, r) as in k_rows, or SP threads per scalar row as in
+// k_rows_split, U blocks in flight.  For products with values that have no
+// sliced copy yet: the copy costs reading and writing the matrix before its
+// first use.  1M rows 4x4 in mesh order: copy 355 us + product 187 us, this
+// product 185 us (5.3 TB/s); transposed, copies 780 us + product 186 us, this
+// product 202 us.
+// A row's terms are added in the order of the sliced product with the same
+// number of threads per row, so y has the same bits from either.
+template <int n, bool TR, int SP>
 __global__ __launch_bounds__(64 * n) void k_bcsr(int32_t N, const int32_t *__restrict__ rp,
                                                  const int32_t *__restrict__ col,
                                                  const int32_t *__restrict__ mirror,
                                                  const double *__restrict__ val, const double *__restrict__ x,
                                                  double *__restrict__ y) {
     constexpr int nn = n * n, U = 4;
-    const int t = threadIdx.x, lr = t / n, r = t - lr * n;
-    const int32_t i = blockIdx.x * 64 + lr;
-    if (i >= N) return;
+    const int t = threadIdx.x, lr = t / (n * SP), kr = t - lr * (n * SP);
+    const int kk = kr / n, r = kr - kk * n;
+    const int32_t i = blockIdx.x * (64 / SP) + lr;
+    const bool act = i < N;
     double acc = 0.0;
-    const int32_t k1 = rp[i + 1];
-    for (int32_t k = rp[i]; k < k1; k += U) {
+    const int32_t k1 = act ? rp[i + 1] : 0;
+    for (int32_t k = act ? rp[i] + kk : 0; k < k1; k += SP * U) {
         int32_t j[U], m[U];
         double bv[U][n], xv[U][n];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            j[u] = k + u < k1 ? col[k + u] : -1;
-            m[u] = TR && k + u < k1 ? mirror[k + u] : k + u;
+            const int32_t q = k + u * SP;
+            j[u] = q < k1 ? col[q] : -1;
+            m[u] = TR && q < k1 ? mirror[q] : q;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -383,10 +394,22 @@ __global__ __launch_bounds__(64 * n) void k_bcsr(int32_t N, const int32_t *__res
         for (int u = 0; u < U; ++u)
             if (j[u] >= 0) {
 #pragma unroll
-                for (int c = 0; c < n; ++c) acc += bv[u][c] * xv[u][c];
+                for (int c = 0; c < n; ++c) acc = mad(bv[u][c], xv[u][c], acc);
             }
     }
-    y[(int64_t)i * n + r] = acc;
+    if constexpr (SP == 1) {
+        if (act) y[(int64_t)i * n + r] = acc;
+    } else {
+        __shared__ double spart[64 * n];
+        spart[t] = acc;
+        __syncthreads();
+        if (act && kk == 0) {
+            double sum = 0.0;
+#pragma unroll
+            for (int q = 0; q < SP; ++q) sum += spart[lr * n * SP + q * n + r];
+            y[(int64_t)i * n + r] = sum;
+        }
+    }
 }
 
 template <int n, typename TV, typename TX, int MODE, bool PRO>
@@ -1043,21 +1066,36 @@ template void launch_rows<float, float>(int, int, const SellView &, const float 
                                         float *, const double *, double, hipStream_t, float *, const int32_t *,
                                         const float *, double *);
 
-void launch_bcsr(int n, int32_t N, const int32_t *rp, const int32_t *col, const int32_t *mirror, const double *val,
+template <int n, int SP>
+void bcsr_launch(int32_t N, const int32_t *rp, const int32_t *col, const int32_t *mirror, const double *val,
                  const double *x, double *y, hipStream_t st) {
-    if (N <= 0) return;
-    const dim3 g(cdiv(N, 64)), b(64 * n);
-#define BCSR_N(NN)                                                                                          \
-    if (mirror) hipLaunchKernelGGL((k_bcsr<NN, true>), g, b, 0, st, N, rp, col, mirror, val, x, y);         \
-    else hipLaunchKernelGGL((k_bcsr<NN, false>), g, b, 0, st, N, rp, col, nullptr, val, x, y)
-    switch (n) {
-        case 1: BCSR_N(1); break;
-        case 2: BCSR_N(2); break;
-        case 3: BCSR_N(3); break;
-        case 4: BCSR_N(4); break;
-        case 5: BCSR_N(5); break;
+    const dim3 g(cdiv((int64_t)N * SP, 64)), b(64 * n);
+    if (mirror) hipLaunchKernelGGL((k_bcsr<n, true, SP>), g, b, 0, st, N, rp, col, mirror, val, x, y);
+    else hipLaunchKernelGGL((k_bcsr<n, false, SP>), g, b, 0, st, N, rp, col, nullptr, val, x, y);
+}
+
+template <int n>
+void bcsr_n(int split, int32_t N, const int32_t *rp, const int32_t *col, const int32_t *mirror, const double *val,
+            const double *x, double *y, hipStream_t st) {
+    switch (split) {
+        case 1: bcsr_launch<n, 1>(N, rp, col, mirror, val, x, y, st); break;
+        case 2: bcsr_launch<n, 2>(N, rp, col, mirror, val, x, y, st); break;
+        case 4: bcsr_launch<n, 4>(N, rp, col, mirror, val, x, y, st); break;
+        case 8: bcsr_launch<n, 8>(N, rp, col, mirror, val, x, y, st); break;
+        default: bcsr_launch<n, 16>(N, rp, col, mirror, val, x, y, st); break;
     }
-#undef BCSR_N
+}
+
+void launch_bcsr(int n, int32_t N, const int32_t *rp, const int32_t *col, const int32_t *mirror, const double *val,
+                 const double *x, double *y, int split, hipStream_t st) {
+    if (N <= 0) return;
+    switch (n) {
+        case 1: bcsr_n<1>(split, N, rp, col, mirror, val, x, y, st); break;
+        case 2: bcsr_n<2>(split, N, rp, col, mirror, val, x, y, st); break;
+        case 3: bcsr_n<3>(split, N, rp, col, mirror, val, x, y, st); break;
+        case 4: bcsr_n<4>(split, N, rp, col, mirror, val, x, y, st); break;
+        case 5: bcsr_n<5>(split, N, rp, col, mirror, val, x, y, st); break;
+    }
     LAUNCHCHK();
 }
 
@@ -1497,10 +1535,10 @@ std::map<std::tuple<int32_t, int64_t, int, bool>, Sched> g_tune_cache;
 // thread about three blocks.  (Level 2 of the 1M-cell p-U system, 47,807
 // rows, runs its sweep in 13.1 us with one thread per scalar row against
 // 14.1 us split four ways.)
-int8_t row_split_for(const Sell &S, int64_t nblocks, int32_t opt_split) {
-    if (S.N <= 0 || S.N >= kSplitLevelRows) return 1;
+int8_t row_split_for(int32_t N, int64_t nblocks, int32_t opt_split) {
+    if (N <= 0 || N >= kSplitLevelRows) return 1;
     if (opt_split > 0) return (int8_t)opt_split;
-    const double w = (double)nblocks / S.N;
+    const double w = (double)nblocks / N;
     int s = 1;
     while (s < 16 && 3.0 * (2 * s) <= w) s *= 2;
     return (int8_t)s;
