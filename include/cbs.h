@@ -327,7 +327,13 @@ int cbs_solve_transpose(cbs_handle h, const double *g, double *lambda, cbs_stats
 int cbs_gradient(cbs_handle h, const double *lambda, const double *x,
                  double *grad_diag, double *grad_upper, double *grad_lower);
 
-/* y = A x (transpose = 0) or y = A^T x (transpose = 1), FP64, block AoS. */
+/* y = A x (transpose = 0) or y = A^T x (transpose = 1), FP64, block AoS.
+ * Enqueued on the handle's stream.  The first product of each kind with new
+ * values may allocate, and the first one of the handle synchronise; later ones
+ * only launch, and give the same bits for the same x.  After a number of
+ * products with the same values one of them also copies the matrix into the
+ * layout that the products from then on read.  Under stream capture nothing is
+ * allocated or copied. */
 int cbs_spmv(cbs_handle h, const double *x, double *y, int32_t transpose);
 
 /* One application z = M^{-1} r of the preconditioner built by cbs_setup

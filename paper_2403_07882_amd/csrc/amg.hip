@@ -2237,10 +2237,10 @@ void permute_vec(cbs_system *h, const double *in, double *out, bool to_internal)
     LAUNCHCHK();
 }
 
-// Products with the same values before cbs_spmv makes the sliced copy.  At
-// 389,000 cells 5x5 the copy costs 275 us (A^T: 550 us) and saves 16 us of a
-// 140 us product (A^T: 22 of 147 us, 47 of 188 us renumbered), so it pays
-// after some 17 products (A^T 12 to 25).  4x4 blocks are whole cache lines and
+// Products with the same values before cbs_spmv fills the sliced copy.  At
+// 389,000 cells 5x5 the copy costs 285 us and saves 16 us of a 136 us product
+// (A^T: 24 of 143 us, 47 of 188 us renumbered), so it pays after some 18
+// products (A^T 6 to 12).  4x4 blocks are whole cache lines and
 // the block-CSR product is as fast as the sliced one (1M cells: 185 and 187
 // us; renumbered at random 254 and 249 us), so A keeps none there from
 // kSplitLevelRows rows on.  The copy's schedule is the known or the default one: timing the six takes as long as 72 products (5x5, 1M
@@ -2256,46 +2256,52 @@ constexpr int32_t kUserCopyAfter = 16;
 constexpr int64_t kUserWholeRows = 98304;
 
 // cbs_spmv: caller-numbered A or A^T.  Options that name a kernel of the
-// sliced copy (schedule, row_split) use it from the first product on.
+// sliced copy (schedule, row_split) use it from the first product on.  The
+// copy's pattern and memory come with the first product, whenever it is filled,
+// so that the others only launch; while the caller captures the stream nothing
+// is allocated, and no copy is filled by a launch that has yet to run.
 void spmv_user(cbs_system *h, const double *x, double *y, bool transposed) {
     Sell &U = h->usell;
-    const int n = h->n;
+    const int n = h->n, t = transposed ? 1 : 0;
     DArr<double> &copy = transposed ? U.v64T : U.v64;
-    int32_t &products = h->user_products[transposed ? 1 : 0];
-    const int8_t split = h->opt.row_split <= 0 && (int64_t)h->N * n >= kUserWholeRows
-                             ? 1 : row_split_for(h->N, h->nnzb, h->opt.row_split);
-    if (!copy.get() && h->opt.schedule <= 0 && h->opt.row_split <= 0 &&
-        (products < kUserCopyAfter || (n == 4 && !transposed && h->N >= kSplitLevelRows))) {
-        products = std::min(products + 1, kUserCopyAfter);
-        launch_bcsr(n, h->N, h->rp.get(), h->col.get(), transposed ? h->mirror.get() : nullptr, h->vals.get(), x, y,
-                    split, h->stream);
-        return;
-    }
-    if (!U.soff.get()) sell_build(h->N, h->rp.get(), h->col.get(), U, h->stream);
-    const bool tune = !U.v64.get() && !U.v64T.get();
-    const size_t nv = (size_t)U.nent * n * n;
-    if (!copy.get()) {
-        const double *vals = h->vals.get();
-        if (transposed) {
-            h->valsT.alloc((size_t)h->nnzb * n * n);
-            NSWITCH(n, transpose_n, h->nnzb, h->mirror.get(), h->vals.get(), h->valsT.get(), h->stream);
-            LAUNCHCHK();
-            vals = h->valsT.get();
+    if (!h->user_filled[t]) {
+        const bool named = h->opt.schedule > 0 || h->opt.row_split > 0;
+        const int8_t split = h->opt.row_split <= 0 && (int64_t)h->N * n >= kUserWholeRows
+                                 ? 1 : row_split_for(h->N, h->nnzb, h->opt.row_split);
+        const int32_t *mirror = transposed ? h->mirror.get() : nullptr;
+        bool bcsr = !named && n == 4 && !transposed && h->N >= kSplitLevelRows;
+        if (!bcsr) {
+            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(h->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+                (void)hipGetLastError();
+                bcsr = true;
+            } else {
+                if (!U.soff.get()) {
+                    Sell S;
+                    sell_build(h->N, h->rp.get(), h->col.get(), S, h->stream);
+                    U = std::move(S);
+                }
+                copy.ensure(U.nent > 0 ? (size_t)U.nent * n * n : 1);
+                bcsr = !named && ++h->user_products[t] <= kUserCopyAfter;
+            }
         }
-        copy.alloc(nv > 0 ? nv : 1);
-        sell_fill(n, U, vals, copy.get(), h->stream);
-        h->valsT.release();
-    }
-    if (tune) {
-        U.sched64 = known_sched(n, U, false, h->opt.schedule);
-        U.sched64.split = split;
+        if (bcsr) {
+            launch_bcsr(n, h->N, h->rp.get(), h->col.get(), mirror, h->vals.get(), x, y, split, h->stream);
+            return;
+        }
+        sell_fill(n, U, h->vals.get(), copy.get(), h->stream, nullptr, nullptr, mirror);
+        if (!h->user_filled[1 - t]) {
+            U.sched64 = known_sched(n, U, false, h->opt.schedule);
+            U.sched64.split = split;
+        }
+        h->user_filled[t] = true;
     }
     launch_rows<double, double>(0, n, U.view(), copy.get(), x, nullptr, y, nullptr, 0.0, h->stream);
 }
 
 void spmv_user_reset(cbs_system *h) {
-    h->valsT.release();
     h->usell.v64.release();
     h->usell.v64T.release();
     h->user_products[0] = h->user_products[1] = 0;
+    h->user_filled[0] = h->user_filled[1] = false;
 }

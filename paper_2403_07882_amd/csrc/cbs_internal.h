@@ -321,9 +321,9 @@ struct cbs_system {
     // internal renumbering of level 0 (AMG setup)
     bool renumbered = false;
     DArr<int32_t> perm_sk;                       // permuted level-0 slot -> caller-order slot
-    DArr<double> valsT;                          // caller-order A^T values (cbs_spmv transpose)
     Sell usell;                                  // caller-order sliced copy (cbs_spmv)
     int32_t user_products[2] = {0, 0};           // cbs_spmv calls with the present values, A and A^T
+    bool user_filled[2] = {false, false};        // usell holds the present values, A and A^T
     // mixed precision escalated to FP64 (sticky until the next cbs_setup)
     bool precision_fallback = false;
     DArr<double> x0;                             // caller's initial guess, kept for a re-solve
@@ -439,9 +439,9 @@ void sell_pattern_shape(int32_t N, Sell &S, int slice);
 void sell_pattern_finish(const int32_t *rp, const int32_t *col, Sell &S, int64_t nent, hipStream_t st,
                          bool offdiag);
 // (with out32: also the FP32 rounding of every value, bit 64 of *flag set for
-// values FP32 cannot hold)
+// values FP32 cannot hold; with mirror: the values of A^T)
 void sell_fill(int n, const Sell &S, const double *bcsr_vals, double *out, hipStream_t st, float *out32 = nullptr,
-               int32_t *flag = nullptr);
+               int32_t *flag = nullptr, const int32_t *mirror = nullptr);
 // out = FP32(Dinv_i A_ij) for every entry of the sliced pattern S, A_ij read
 // from the block-CSR values; an entry FP32 cannot hold sets bit 64 of *flag
 void sell_scale(int n, const Sell &S, const double *bcsr_vals, const double *Dinv, float *out, int32_t *flag,

@@ -352,7 +352,7 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
 // k_rows_split, U blocks in flight.  For products with values that have no
 // sliced copy yet: the copy costs reading and writing the matrix before its
 // first use.  1M rows 4x4 in mesh order: copy 355 us + product 187 us, this
-// product 185 us (5.3 TB/s); transposed, copies 780 us + product 186 us, this
+// product 185 us (5.3 TB/s); transposed, copy 370 us + product 186 us, this
 // product 202 us.
 // A row's terms are added in the order of the sliced product with the same
 // number of threads per row, so y has the same bits from either.
@@ -773,24 +773,27 @@ __global__ void k_colour_positions(int32_t N, ColourRanges cr, const int32_t *ro
 }
 
 // Values of a sliced copy gathered from block CSR (zeros in padding); with
-// out32, also their FP32 rounding, flagging (bit 64) values FP32 cannot hold.
+// out32, also their FP32 rounding, flagging (bit 64) values FP32 cannot hold;
+// with mirror, the values of A^T, each block the transpose of its mirror's.
 // Each thread moves kSellV(n) consecutive values of one block: 4 or 2 when
 // n*n allows, else one block row (odd n).
 __host__ __device__ constexpr int kSellV(int n) { return (n * n) % 4 == 0 ? 4 : ((n * n) % 2 == 0 ? 2 : n); }
 
-template <int n, bool F32>
-__global__ void k_sell_vals(int64_t nent, const int32_t *__restrict__ ssrc, const double *__restrict__ in,
-                            double *__restrict__ out, float *__restrict__ out32, int32_t *flag) {
+template <int n, bool F32, bool TR>
+__global__ void k_sell_vals(int64_t nent, const int32_t *__restrict__ ssrc, const int32_t *__restrict__ mirror,
+                            const double *__restrict__ in, double *__restrict__ out, float *__restrict__ out32,
+                            int32_t *flag) {
     constexpr int nn = n * n, V = kSellV(n);
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= nent * (nn / V)) return;
     const int64_t e = g / (nn / V);
     const int64_t o = e * nn + (g - e * (nn / V)) * V;     // first value of this thread
     const int32_t k = ssrc[e];
-    const double *src = in + (int64_t)(k < 0 ? 0 : k) * nn + (o - e * nn);
+    const int q = (int)(o - e * nn);
+    const double *src = in + (int64_t)(k < 0 ? 0 : (TR ? mirror[k] : k)) * nn;
     double v[V];
 #pragma unroll
-    for (int c = 0; c < V; ++c) v[c] = k >= 0 ? src[c] : 0.0;
+    for (int c = 0; c < V; ++c) v[c] = k >= 0 ? src[TR ? (q + c) % n * n + (q + c) / n : q + c] : 0.0;
     bool bad = false;
 #pragma unroll
     for (int c = 0; c < V; ++c) {
@@ -1181,17 +1184,18 @@ void sell_build(int32_t N, const int32_t *rp, const int32_t *col, Sell &S, hipSt
 }
 
 void sell_fill(int n, const Sell &S, const double *bcsr_vals, double *out, hipStream_t st, float *out32,
-               int32_t *flag) {
+               int32_t *flag, const int32_t *mirror) {
     const int64_t tot = S.nent * n * n;
     if (tot <= 0) return;
+    if (out32 && mirror) cbs_throw(CBS_ERR_ARG, "sliced FP32 copy of A^T through the mirror slots");
     const dim3 b(256);
+#define SV_K(NN, F32, TR)                                                                                       \
+    hipLaunchKernelGGL((k_sell_vals<NN, F32, TR>), dim3(cdiv(tot / kSellV(NN), 256)), b, 0, st, S.nent, S.ssrc.get(), \
+                       mirror, bcsr_vals, out, out32, flag)
 #define SV(NN)                                                                                                  \
-    if (out32)                                                                                                  \
-        hipLaunchKernelGGL((k_sell_vals<NN, true>), dim3(cdiv(tot / kSellV(NN), 256)), b, 0, st, S.nent,          \
-                           S.ssrc.get(), bcsr_vals, out, out32, flag);                                          \
-    else                                                                                                        \
-        hipLaunchKernelGGL((k_sell_vals<NN, false>), dim3(cdiv(tot / kSellV(NN), 256)), b, 0, st, S.nent,         \
-                           S.ssrc.get(), bcsr_vals, out, nullptr, nullptr)
+    if (out32) SV_K(NN, true, false);                                                                           \
+    else if (mirror) SV_K(NN, false, true);                                                                     \
+    else SV_K(NN, false, false)
     switch (n) {
         case 1: SV(1); break;
         case 2: SV(2); break;
@@ -1200,6 +1204,7 @@ void sell_fill(int n, const Sell &S, const double *bcsr_vals, double *out, hipSt
         case 5: SV(5); break;
     }
 #undef SV
+#undef SV_K
     LAUNCHCHK();
 }
 
