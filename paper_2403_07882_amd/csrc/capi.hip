@@ -86,6 +86,7 @@ void build_items(cbs_system *h) {
         const int64_t b = h->cell_off[s] * h->n, e = h->cell_off[s + 1] * h->n;
         for (int64_t q = b; q < e; q += len) items.push_back(Item{s, 0, q, std::min<int64_t>(e, q + len)});
         h->items_per_sys_off[s + 1] = (int32_t)items.size();
+        h->fold_sums = h->fold_sums || h->items_per_sys_off[s + 1] - h->items_per_sys_off[s] >= kFoldItems;
     }
     h->n_items = (int32_t)items.size();
     h->items.alloc(items.size());

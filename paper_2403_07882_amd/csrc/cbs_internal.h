@@ -80,6 +80,7 @@ struct Item {
 constexpr int kItemElems = 4096;      // most scalar elements per work item
 constexpr int kItemElemsMin = 512;    // least, on small systems (item_elems)
 constexpr int kVecThreads = 256;      // threads per element-wise workgroup
+constexpr int kFoldItems = 2048;      // items of a system whose partial sums get a launch of their own
 
 // per-system scalar slots of the Krylov loops: scal[slot * n_sys + s]
 enum {
@@ -306,6 +307,7 @@ struct cbs_system {
     DArr<int32_t> done, flags;                   // per-system converged / breakdown flags
     DArr<Item> items;                            // element ranges for level-0 vectors
     int32_t n_items = 0;
+    bool fold_sums = false;                      // a system has kFoldItems items or more (krylov.hip)
     std::vector<int32_t> items_per_sys_off;      // host: first item of each system
     DArr<int32_t> item_off;                      // device copy of the above
     DArr<int32_t> dflag;                         // error flag scratch for checks
