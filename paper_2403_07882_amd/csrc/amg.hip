@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <exception>
 
 void build_row_sys(cbs_system *h, Level &L0);
 
@@ -1760,6 +1761,12 @@ void amg_setup(cbs_system *h) {
     PhaseTimer pt(st, "setup");
     g_pt = &pt;
     struct Unset { ~Unset() { g_pt = nullptr; } } unset_;
+    // a setup that fails half way waits for the kernels it has enqueued: some
+    // write host words that the thread's next call takes for its own
+    struct Settle {
+        hipStream_t st;
+        ~Settle() { if (std::uncaught_exceptions() > 0) (void)hipStreamSynchronize(st); }
+    } settle_{st};
     const cbs_options &o = h->opt;
     const int n = h->n;
     const bool mixed = o.precision == CBS_PRECISION_MIXED;
