@@ -270,7 +270,6 @@ cbs_system::~cbs_system() {
     if (stream) (void)hipStreamSynchronize(stream);
     else (void)hipDeviceSynchronize();
     invalidate_graphs(this);
-    if (h_state) (void)hipHostFree(h_state);
     if (h_scal) (void)hipHostFree(h_scal);
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
     if (ev0) (void)hipEventDestroy(ev0);

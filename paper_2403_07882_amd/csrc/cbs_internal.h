@@ -312,9 +312,9 @@ struct cbs_system {
     DArr<int32_t> item_off;                      // device copy of the above
     DArr<int32_t> dflag;                         // error flag scratch for checks
     // pinned host mirrors that the scalar kernels write beside the device
-    // arrays: done | flags | iterations per system, and the scalars
-    int32_t *h_state = nullptr;
+    // arrays, one allocation: the scalars, then done | flags | iterations per system
     double *h_scal = nullptr;
+    int32_t *h_state = nullptr;
     // captured iteration graphs (index: transposed solve), replayed on `stream`
     hipStream_t cap_stream = nullptr;
     // captured BiCGStab iteration: [whole, first half, second half][forward, transposed]

@@ -1634,11 +1634,14 @@ void alloc_krylov(cbs_system *h) {
         h->sn.ensure((size_t)nsys * (mr + 1));
         h->yv.ensure((size_t)nsys * (mr + 1) * 2);
     }
-    if (!h->h_state) {
-        // written by the scalar kernels, read after a synchronisation
+    if (!h->h_scal) {
+        // written by the scalar kernels, read after a synchronisation; one
+        // allocation, so that both are there or neither
         const unsigned how = hipHostMallocMapped | hipHostMallocCoherent | hipHostMallocPortable;
-        HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&h->h_state), sizeof(int32_t) * 3 * nsys, how));
-        HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&h->h_scal), sizeof(double) * S_NSCAL * nsys, how));
+        void *p = nullptr;
+        HIPCHK(hipHostMalloc(&p, (sizeof(double) * S_NSCAL + sizeof(int32_t) * 3) * nsys, how));
+        h->h_scal = static_cast<double *>(p);
+        h->h_state = reinterpret_cast<int32_t *>(h->h_scal + (size_t)S_NSCAL * nsys);
     }
     const int K = std::max(kSlots, h->opt.solver != CBS_SOLVER_BICGSTAB ? h->opt.restart + 2 : 0);
     h->partial.ensure((size_t)K * h->n_items);
