@@ -458,9 +458,11 @@ static int solve_common(cbs_handle h, const double *b, double *x, cbs_stats *st,
         o.precision = CBS_PRECISION_FP64;
         o.reuse_aggregates = 1;
         h->opt = o;
+        h->setup_done = false;                   // until the FP64 hierarchy is whole
         invalidate_graphs(h);
         amg_setup(h);
         alloc_krylov(h);
+        h->setup_done = true;
         h->precision_fallback = true;
         launch_copy(m, h->x0.get(), x, h->stream);
         rc = krylov_solve(h, b, x, st, tr);

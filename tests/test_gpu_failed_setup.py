@@ -60,3 +60,32 @@ def test_calls_after_a_setup_without_memory(shape):
         refused += 1
     assert refused > 40
     good.close()
+
+
+def test_solve_whose_fallback_runs_out_of_memory():
+    """The FP64 hierarchy of a mixed solve that did not converge finds no memory:
+    the handle has no preconditioner until the next setup, and works after it."""
+    s = jacobian_box(12, 11, 10, n=5, seed=252)
+    refuse = [False]
+
+    def alloc(ctx, nbytes, stream):
+        return None if refuse[0] else torch.cuda.caching_allocator_alloc(int(nbytes), None, int(stream or 0))
+
+    hook = P.Allocator(B._ALLOC_FN(alloc), B._FREE_FN(lambda ctx, p, q: torch.cuda.caching_allocator_delete(int(p))), None)
+    with P.System.from_dict(s) as sysm:
+        assert P.lib().cbs_set_allocator(sysm.h, C.byref(hook)) == P.OK
+        kw = dict(precond=P.PREC_AMG, precision=P.PRECISION_MIXED)
+        sysm.setup(**kw)
+        sysm.solve(s["b"])
+        sysm.setup(max_iter=1, tol=1e-14, reuse_aggregates=1, **kw)
+        refuse[0] = True
+        with pytest.raises(P.CbsError) as e:
+            sysm.solve(s["b"])
+        assert e.value.code == P.ERR_OOM
+        refuse[0] = False
+        for call in (sysm.solve, sysm.apply_precond):
+            with pytest.raises(P.CbsError) as e:
+                call(s["b"])
+            assert e.value.code == P.ERR_STATE
+        sysm.setup(**kw)
+        assert sysm.solve(s["b"])[1]["status"] == P.OK
