@@ -318,11 +318,6 @@ __global__ void k_fill_int(int32_t *a, int64_t n, int32_t v) {
     if (i < n) a[i] = v;
 }
 
-__global__ void k_count_members(int32_t N, const int32_t *agg, int32_t *cnt) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < N) atomicAdd(&cnt[agg[i]], 1);
-}
-
 // members per aggregate, and the summed row lengths (over the graph rp) of
 // each aggregate's members: its Galerkin candidate count
 __global__ void k_count_members_len(int32_t N, const int32_t *agg, const int32_t *rp, int32_t *cnt, int32_t *len) {
