@@ -1,0 +1,55 @@
+"""Batches of hundreds of small systems, on both sides of the counts from which
+their kernels change."""
+import itertools
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2403_07882_amd as P  # noqa: E402
+
+
+def _full(cells, n, rng):
+    """A matrix in which every pair of cells shares a face."""
+    la, ua = np.array(list(itertools.combinations(range(cells), 2)), dtype=np.int32).reshape(-1, 2).T
+    d, u, lo = (rng.standard_normal((k, n, n)) for k in (cells, la.size, la.size))
+    A = np.zeros((cells, n, cells, n))
+    A[np.arange(cells), :, np.arange(cells)] = d
+    A[la, :, ua], A[ua, :, la] = u, lo
+    return la, ua, d, u, lo, A.reshape(cells * n, cells * n)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("most", [48, 49])
+@pytest.mark.parametrize("count", [768, 769])
+def test_dense_inverses_of_many_systems(count, most, n):
+    """Full random matrices of up to 48 unknowns and of up to 49 (or the block
+    size's next).  Gauss-Jordan with partial pivoting: 20 m eps cond(A)."""
+    print("many inverses", count, most, n, flush=True)
+    rng = np.random.default_rng(260 + n)
+    big = most // n if most == 48 else 48 // n + 1
+    kinds = [_full(c, n, rng) for c in (1, 2, 3, max(1, big // 2), big)]
+    pick = [kinds[(i * i + i // 5) % 5] for i in range(count - 1)] + [kinds[4]]
+    cat = [np.concatenate([p[k] for p in pick]) for k in range(5)]
+    co = np.cumsum([0] + [p[2].shape[0] for p in pick])
+    fo = np.cumsum([0] + [p[0].size for p in pick])
+    r = rng.standard_normal((co[-1], n))
+    with P.System(int(co[-1]), n, *cat, cell_off=co, face_off=fo) as s:
+        s.setup(precond=P.PREC_AMG, coarse_max=64)
+        assert s.info()["levels"] == 1
+        z = [s.apply_precond(r, transpose=t).cpu().numpy() for t in (False, True)]
+        cat[2][co[-2]:] = 1.0                          # the last system is singular
+        cat[3][fo[-2]:] = 1.0
+        cat[4][fo[-2]:] = 1.0
+        if pick[-1][5].shape[0] > 1:
+            s.update_values(*cat[2:])
+            with pytest.raises(P.CbsError) as e:
+                s.setup(precond=P.PREC_AMG, coarse_max=64)
+            assert e.value.code == P.ERR_SINGULAR
+    for k, p in enumerate(pick):
+        for got, M in ((z[0], p[5]), (z[1], p[5].T)):
+            ref = np.linalg.solve(M, r[co[k]:co[k + 1]].ravel())
+            bar = 20 * M.shape[0] * 2.3e-16 * np.linalg.cond(M)
+            assert np.linalg.norm(got[co[k]:co[k + 1]].ravel() - ref) <= bar * np.linalg.norm(ref), k
