@@ -31,6 +31,13 @@ constexpr int kTailRowsPerWg = 16;         // scalar rows per workgroup of the p
                                            // line of a column of the operator
 constexpr int kTailApplyThreads = 512;
 constexpr int64_t kTailLdsReserve = 1024;
+// A tail of the coarsest level alone saves one launch of two, and only up to this
+// many workgroups is that more than its operators cost.  5x5, product against
+// restriction and dense solve, and the forming: 64 systems of 20 unknowns 4.0,
+// 6.0 and 10 us, 128 systems 4.0, 6.1 and 16 us (256 workgroups); 256 systems of
+// 35 unknowns 7.1, 6.9 and 47 us, 512 of 20 6.9, 6.6 and 50 us, 2,048 of 20 36,
+// 13 and 353 us.
+constexpr int64_t kTailCoarseBlocks = 256;
 
 // one level of the tail
 struct TailLvl {
@@ -408,13 +415,15 @@ int tail_level(const cbs_system *h) {
     for (int l = std::max(1, h->opt.w_levels + 1); l < nlev; ++l) {
         if (nlev - l > kTailMax) continue;
         const Level &L = h->lev[l];
-        int64_t rows = 0, vals = 0, m_max = 0;
+        int64_t rows = 0, vals = 0, m_max = 0, blocks = 0;
         for (int s = 0; s < h->n_sys; ++s) {
             const int64_t N = L.sys_off[s + 1] - L.sys_off[s], m = N * h->n;
             rows = std::max(rows, N);
             m_max = std::max(m_max, m);
             vals += m * tail_ld(m);
+            blocks += cdiv(m, kTailRowsPerWg);
         }
+        if (l + 1 == nlev && blocks > kTailCoarseBlocks) continue;
         if (rows > lim || vals * 8 > kTailOpBytes || m_max * 8 > 64 * 1024) continue;
         // DILU and Gauss-Seidel levels keep their own kernels, and so do levels
         // whose copy is window-ordered (kSplitLevelRows rows and more of all

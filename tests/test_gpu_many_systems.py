@@ -53,3 +53,30 @@ def test_dense_inverses_of_many_systems(count, most, n):
             ref = np.linalg.solve(M, r[co[k]:co[k + 1]].ravel())
             bar = 20 * M.shape[0] * 2.3e-16 * np.linalg.cond(M)
             assert np.linalg.norm(got[co[k]:co[k + 1]].ravel() - ref) <= bar * np.linalg.norm(ref), k
+
+
+@pytest.mark.parametrize("precision", [P.PRECISION_FP64, P.PRECISION_MIXED])
+@pytest.mark.parametrize("count", [128, 129])
+def test_tail_of_the_coarsest_level_alone(count, precision):
+    """Chains of 20 cells, 5x5, whose level 1 is the coarsest: two workgroups to a
+    system of the tail's product, up to 256 of them, else the level's own launches.
+    Against the cycle without a tail: 1e-11, FP32 1e-5."""
+    rng = np.random.default_rng(270)
+    N, n = 20, 5
+    la = np.arange(N - 1, dtype=np.int32)
+    off = rng.uniform(0.2, 1.0, (count, N - 1))[:, :, None, None] * (np.eye(n) + 0.2 * rng.standard_normal((count, N - 1, n, n)))
+    diag = np.tile(0.2 * np.eye(n), (count, N, 1, 1))
+    diag[:, :-1] += off
+    diag[:, 1:] += off
+    flat = lambda a: a.reshape(-1, n, n)        # noqa: E731
+    f = rng.standard_normal((count * N, n))
+    z = {}
+    with P.System(count * N, n, np.tile(la, count), np.tile(la + 1, count), flat(diag), flat(-off), flat(-off),
+                  cell_off=N * np.arange(count + 1), face_off=(N - 1) * np.arange(count + 1)) as s:
+        for tail in (-1, 0):
+            s.setup(precond=P.PREC_AMG, precision=precision, tail_rows=tail)
+            assert s.info()["levels"] == 2
+            z[tail] = [s.apply_precond(f, transpose=t).cpu().numpy() for t in (False, True)]
+            assert all(st["status"] == P.OK for st in s.solve_batch(f)[1])
+    for a, b in zip(z[0], z[-1]):
+        assert np.abs(a - b).max() <= (1e-5 if precision == P.PRECISION_MIXED else 1e-11) * np.abs(b).max()
