@@ -325,7 +325,8 @@ struct DotSrc {
 };
 
 // the items of every system; folded: the place of a system's first item in a
-// slot of partials holds their sum
+// slot of partials holds their sum (after k_fold_sums, or because it is the only
+// one: no reductions in 20,000 workgroups of a system each)
 struct ItemRange {
     const int32_t *off;
     bool folded;
@@ -870,7 +871,9 @@ void dots(cbs_system *h, int K, const double *a0, const double *b0, const double
     LAUNCHCHK();
 }
 
-ItemRange item_range(const cbs_system *h) { return ItemRange{h->item_off.get(), h->fold_sums}; }
+ItemRange item_range(const cbs_system *h) {
+    return ItemRange{h->item_off.get(), h->fold_sums || h->n_items == h->n_sys};
+}
 
 // K slots of partials from slot0 on, ready for kernels whose workgroups all sum them
 void fold(cbs_system *h, int slot0, int K) {
