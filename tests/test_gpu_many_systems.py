@@ -80,3 +80,38 @@ def test_tail_of_the_coarsest_level_alone(count, precision):
             assert all(st["status"] == P.OK for st in s.solve_batch(f)[1])
     for a, b in zip(z[0], z[-1]):
         assert np.abs(a - b).max() <= (1e-5 if precision == P.PRECISION_MIXED else 1e-11) * np.abs(b).max()
+
+
+@pytest.mark.parametrize("solver", [P.SOLVER_BICGSTAB, P.SOLVER_GMRES, P.SOLVER_FGMRES])
+@pytest.mark.parametrize("count", [1023, 1024])
+def test_state_of_many_systems_reaches_the_host(count, solver):
+    """Systems that are solved, have a zero right side, start converged or (with
+    BiCGStab) break down, each with its own statistics, as on their own."""
+    print("many states", count, solver, flush=True)
+    kinds = {"solved": (np.array([[2.0, 1.0], [0.0, 3.0]]), [3.0, 3.0]), "zero": (np.eye(2), [0.0, 0.0]),
+             "broken": (np.array([[0.0, 1.0], [-1.0, 0.0]]), [1.0, 0.0]), "started": (4.0 * np.eye(2), [4.0, 4.0])}
+    bicg = solver == P.SOLVER_BICGSTAB
+    pick = [list(kinds)[(i * 7 + i // 4) % 4] for i in range(count)]
+    if not bicg:
+        pick = [k if k != "broken" else "solved" for k in pick]
+    D, b = np.array([kinds[k][0] for k in pick]), np.array([kinds[k][1] for k in pick])
+    x0 = np.array([[1.0, 1.0] if k == "started" else [0.0, 0.0] for k in pick])
+    none, no = np.zeros((0, 2, 2)), np.zeros(0, np.int32)
+    kw = dict(precond=P.PREC_NONE, solver=solver, tol=1e-12, restart=5)
+
+    def solve(sel):
+        m = len(sel)
+        with P.System(m, 2, no, no, D[sel], none, none, cell_off=np.arange(m + 1), face_off=np.zeros(m + 1)) as s:
+            s.setup(**kw)
+            bd, x = (torch.tensor(a[sel], device="cuda") for a in (b, x0))
+            st = (P.Stats * m)()
+            rc = P.lib().cbs_solve_batch(s.h, bd.data_ptr(), x.data_ptr(), st)
+        assert rc == min(q.status for q in st)
+        return x.cpu().numpy(), [(q.status, q.iterations, q.rel_res_true, q.rel_res_recursive, q.rel_res_initial) for q in st]
+
+    x, st = solve(list(range(count)))
+    own = {k: solve([pick.index(k)]) for k in set(pick)}
+    for i, k in enumerate(pick):
+        assert st[i] == own[k][1][0], (i, k)
+        assert np.array_equal(x[i], own[k][0][0]), (i, k)
+    assert {own[k][1][0][0] for k in own} == ({P.OK, P.ERR_BREAKDOWN} if bicg else {P.OK})
