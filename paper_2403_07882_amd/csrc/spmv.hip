@@ -789,11 +789,17 @@ __global__ void k_sell_vals(int64_t nent, const int32_t *__restrict__ ssrc, cons
     const int64_t e = g / (nn / V);
     const int64_t o = e * nn + (g - e * (nn / V)) * V;     // first value of this thread
     const int32_t k = ssrc[e];
-    const int q = (int)(o - e * nn);
-    const double *src = in + (int64_t)(k < 0 ? 0 : (TR ? mirror[k] : k)) * nn;
     double v[V];
+    if constexpr (TR) {
+        const int q = (int)(o - e * nn);
+        const double *src = in + (int64_t)(k < 0 ? 0 : mirror[k]) * nn;
 #pragma unroll
-    for (int c = 0; c < V; ++c) v[c] = k >= 0 ? src[TR ? (q + c) % n * n + (q + c) / n : q + c] : 0.0;
+        for (int c = 0; c < V; ++c) v[c] = k >= 0 ? src[(q + c) % n * n + (q + c) / n] : 0.0;
+    } else {
+        const double *src = in + (int64_t)(k < 0 ? 0 : k) * nn + (o - e * nn);
+#pragma unroll
+        for (int c = 0; c < V; ++c) v[c] = k >= 0 ? src[c] : 0.0;
+    }
     bool bad = false;
 #pragma unroll
     for (int c = 0; c < V; ++c) {
