@@ -2397,7 +2397,7 @@ void spmv_user(cbs_system *h, const double *x, double *y, bool transposed) {
         }
         h->user_filled[t] = true;
     }
-    launch_rows<double, double>(0, n, U.view(), copy.get(), x, nullptr, y, nullptr, 0.0, h->stream);
+    launch_rows<double, double>(6, n, U.view(), copy.get(), x, nullptr, y, nullptr, 0.0, h->stream);
 }
 
 void spmv_user_reset(cbs_system *h) {

@@ -394,7 +394,7 @@ void gradient(cbs_system *h, const double *lam, const double *x, double *gd, dou
 // Modes 2 and 4 with y64 != nullptr write the result widened to FP64 into y64
 // instead of y.
 // Mode 5 (FP64): A x with the workgroups' sums of b y and y y in y64, two rows
-// of rows_workgroups(S).
+// of rows_workgroups(S).  Mode 6 (FP64): A x with the bits of launch_bcsr.
 int32_t rows_workgroups(const SellView &S);
 template <typename TV, typename TX>
 void launch_rows(int mode, int n, const SellView &S, const TV *val, const TX *x, const TX *b, TX *y,

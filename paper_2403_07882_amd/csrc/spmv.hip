@@ -21,11 +21,15 @@ namespace {
 template <typename T> struct Acc { using type = double; };
 template <> struct Acc<float> { using type = float; };
 
-// One term of a row's sum is one fused operation wherever the sum is unrolled
-// (left to the compiler, some remainders became a product and an addition), so
-// that equal orders give equal bits.
-__device__ inline double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ inline float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+// c + a b, a term of a row's sum.  FUSED: one operation wherever the sum is
+// unrolled, so that equal orders give equal bits.  Left to the compiler, some
+// remainders of k_rows become a product and an addition, which is 1 to 4% faster
+// with four blocks in flight (the product does not wait for the sum).
+template <bool FUSED, typename T>
+__device__ inline T term(T a, T b, T c) {
+    if constexpr (FUSED) return (T)__builtin_fma(a, b, c);
+    else return c + a * b;
+}
 
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 typedef float flt4 __attribute__((ext_vector_type(4)));
@@ -125,6 +129,7 @@ __device__ inline void wg_two_sums(double a, double c, double *__restrict__ out)
 // mode 5: y = A x as mode 0, and into y64 the workgroup's sums of b y and of
 // y y (gridDim.x of each): the two products that follow A x in the Krylov
 // loop, for which y would be read again.
+// mode 6: y = A x as mode 0 in fused terms, with the bits of k_bcsr.
 // Modes 2 and 4 with PRO: x is first corrected by the prolongated coarse
 // solution (x + P e, pagg = aggregate map, pe = e), see load_xc.
 template <int n, typename TV, typename TX, int MODE, int U, bool NT, bool PRO>
@@ -159,7 +164,7 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
     TX bo = 0, xo = 0;
     double di[n];
     if (act) {
-        if (MODE != 0) bo = b[o];
+        if (MODE != 0 && MODE != 6) bo = b[o];
         if (SWEEP) {
             xo = x[o];
             if constexpr (PRO) xo = xo + pe[(int64_t)pagg[i] * n + r];
@@ -187,7 +192,7 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
             for (int u = 0; u < U; ++u)
                 if (j[u] >= 0) {
 #pragma unroll
-                    for (int c = 0; c < n; ++c) acc = mad((A)bv[u][c], (A)xv[u][c], acc);
+                    for (int c = 0; c < n; ++c) acc = term<MODE == 6>((A)bv[u][c], (A)xv[u][c], acc);
                 }
         }
         // the last w % U blocks are loaded together too, not one after the
@@ -211,7 +216,7 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
             for (int u = 0; u < U - 1; ++u)
                 if (j[u] >= 0) {
 #pragma unroll
-                    for (int c = 0; c < n; ++c) acc = mad((A)bv[u][c], (A)xv[u][c], acc);
+                    for (int c = 0; c < n; ++c) acc = term<MODE == 6>((A)bv[u][c], (A)xv[u][c], acc);
                 }
         }
     }
@@ -221,7 +226,7 @@ __global__ __launch_bounds__(64 * n) void k_rows(SellView S, const TV *__restric
         __syncthreads();
         acc = sres[t];
     }
-    if (MODE == 0 || MODE == 5) {
+    if (MODE == 0 || MODE == 5 || MODE == 6) {
         if (act) y[o] = (TX)acc;
         if constexpr (MODE == 5) wg_two_sums<n>(act ? (double)bo * (double)acc : 0.0, act ? (double)acc * (double)acc : 0.0, y64);
         return;
@@ -281,7 +286,7 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
     TX bo = 0, xo = 0;
     int32_t ai = 0;
     if (act && kk == 0) {
-        if (MODE != 0) bo = b[o];
+        if (MODE != 0 && MODE != 6) bo = b[o];
         if (SWEEP) xo = x[o];
         if (PRO) ai = pagg[i];
     }
@@ -306,7 +311,7 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
             for (int u = 0; u < U; ++u)
                 if (j[u] >= 0) {
 #pragma unroll
-                    for (int c = 0; c < n; ++c) acc = mad((A)bv[u][c], (A)xv[u][c], acc);
+                    for (int c = 0; c < n; ++c) acc = term<MODE == 6>((A)bv[u][c], (A)xv[u][c], acc);
                 }
         }
     }
@@ -318,7 +323,7 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
     if (kk == 0) {
 #pragma unroll
         for (int q = 0; q < SP; ++q) sum += spart[lr * n * SP + q * n + r];
-        if (MODE == 0 || MODE == 5) {
+        if (MODE == 0 || MODE == 5 || MODE == 6) {
             if (act) y[o] = (TX)sum;
         } else {
             if (PRO && act) xo = xo + pe[(int64_t)ai * n + r];
@@ -354,7 +359,7 @@ __global__ __launch_bounds__(64 * n) void k_rows_split(SellView S, const TV *__r
 // first use.  1M rows 4x4 in mesh order: copy 355 us + product 187 us, this
 // product 185 us (5.3 TB/s); transposed, copy 370 us + product 186 us, this
 // product 202 us.
-// A row's terms are added in the order of the sliced product with the same
+// A row's terms are added as by mode 6 of the sliced product with the same
 // number of threads per row, so y has the same bits from either.
 template <int n, bool TR, int SP>
 __global__ __launch_bounds__(64 * n) void k_bcsr(int32_t N, const int32_t *__restrict__ rp,
@@ -394,7 +399,7 @@ __global__ __launch_bounds__(64 * n) void k_bcsr(int32_t N, const int32_t *__res
         for (int u = 0; u < U; ++u)
             if (j[u] >= 0) {
 #pragma unroll
-                for (int c = 0; c < n; ++c) acc = mad(bv[u][c], xv[u][c], acc);
+                for (int c = 0; c < n; ++c) acc = term<true>(bv[u][c], xv[u][c], acc);
             }
     }
     if constexpr (SP == 1) {
@@ -465,6 +470,9 @@ void rows_n(int mode, const SellView &S, const TV *val, const TX *x, const TX *b
         case 4: rows_nm<n, TV, TX, 4>(S, val, x, b, y, Dinv, omega, aux, pagg, pe, y64, st); break;
         case 5:
             if constexpr (sizeof(TX) == 8) rows_nm<n, TV, TX, 5>(S, val, x, b, y, Dinv, omega, aux, pagg, pe, y64, st);
+            break;
+        case 6:
+            if constexpr (sizeof(TX) == 8) rows_nm<n, TV, TX, 6>(S, val, x, b, y, Dinv, omega, aux, pagg, pe, y64, st);
             break;
     }
 }
