@@ -121,8 +121,9 @@ typedef struct cbs_options {
                                 down to the coarsest and back, the cycle runs
                                 as one dense FP64 operator per system, formed
                                 at setup (one kernel instead of about five
-                                per level; at most 32 MB of operators and no
+                                per level; at most 32 MB of operators, no
                                 smoothed level of 32,768 rows of all systems,
+                                and in batches not the coarsest level alone,
                                 else it starts further down); 0 = 256, < 0 =
                                 never. Changes only the order of the row
                                 sums                                 [0] */
@@ -304,7 +305,9 @@ int cbs_setup(cbs_handle h, const cbs_options *opt /* host */);
  * start, as Algorithm amgxFoam uploads the current solution) and the
  * solution on exit.  st: host, may be NULL; for a batch, an array of n_sys.
  * b = 0 returns x = 0 with 0 iterations.  Returns CBS_NOT_CONVERGED (x
- * written) at the iteration cap. */
+ * written) at the iteration cap.  If the FP64 rebuild of a mixed solve that did
+ * not converge fails (its code is returned), the handle needs cbs_setup before
+ * the next solve. */
 int cbs_solve(cbs_handle h, const double *b, double *x, cbs_stats *st /* host */);
 
 /* The batched solve of a handle from cbs_create_batch_from_ldu: the same
